@@ -61,9 +61,10 @@
  *            hstu_complete_cumsum are bitwise deterministic, and so are
  *            dQ, dK and dV of hstu_attn_bwd for HSTU_BF16 (dQ is summed
  *            from per-key-block partials in a fixed order), and of
- *            hstu_layer_bwd for HSTU_BF16 with d_qk, d_v <= 64.  The bias
- *            gradients, the layer-norm parameter gradients, and dQ of
- *            hstu_layer_bwd at d_qk or d_v = 128 are accumulated with
+ *            hstu_layer_bwd for HSTU_BF16 with d_qk, d_v <= 64; the
+ *            layer-norm parameter gradients are summed in a fixed order from
+ *            those calls' dO.  The bias gradients, and dQ of
+ *            hstu_layer_bwd at d_qk or d_v = 128, are accumulated with
  *            atomics, so their last bits may vary between runs.
  */
 #ifndef HSTU_H_
@@ -238,8 +239,8 @@ hstu_status_t hstu_layer_fwd(const hstu_problem_t* p, const hstu_jagged_t* j,
  * weight / bias NULL for the identity affine).  d_y, du: dense [T][h*d_v]
  * in the problem's dtype
  * (du overwritten).  d_ln_weight, d_ln_bias: fp32 [h*d_v], overwritten
- * with the gradients (summed over tokens by float atomics, so their last
- * bits may vary between runs), or NULL to skip them.  Other arguments and
+ * with the gradients (summed over tokens in a fixed order), or NULL to skip
+ * them.  Other arguments and
  * outputs as hstu_attn_bwd.  h*d_v <= 4096. */
 hstu_status_t hstu_layer_bwd(const hstu_problem_t* p, const hstu_jagged_t* j,
                              const void* q, int64_t q_stride,

@@ -288,7 +288,8 @@ hstu_status_t attn_fwd_run(const hstu_problem_t* p, const hstu_jagged_t* j, cons
     return ok();
   }
   ja.seq_trange = trange;
-  HSTU_HIP(launch_prep(ja, 0, items, counts, trange, PrepFills{}, nullptr, s), "prep launch");
+  HSTU_HIP(launch_prep(ja, 0, items, counts, trange, PrepFills{}, ColSums{}, nullptr, s),
+           "prep launch");
   TimedScope ts(timed ? "attn_fwd" : nullptr, s);
   HSTU_HIP(launch_attn_fwd_bf16(ja, t, p->d_qk, p->d_v, out, out_f32, out_f32, items, counts,
                                 max_items, s),
@@ -853,8 +854,8 @@ hstu_status_t hstu_attn_fwd_cached(const hstu_problem_t* p, const hstu_jagged_t*
     WorkItem* items = (WorkItem*)(w + l.items);
     float* o32 = (float*)(w + l.partial);  // fp32 partial outputs, one slot per key chunk
     ja.seq_trange = (const int64_t*)(w + l.trange);
-    HSTU_HIP(launch_prep(ja, 0, items, counts, (int64_t*)(w + l.trange), PrepFills{}, nullptr,
-                         s),
+    HSTU_HIP(launch_prep(ja, 0, items, counts, (int64_t*)(w + l.trange), PrepFills{},
+                         ColSums{}, nullptr, s),
              "prep launch");
     TimedScope ts("attn_fwd_cached", s);
     const Tensors keys{q, q_stride, k_cache, kc_stride, v_cache, vc_stride};
@@ -891,28 +892,31 @@ hstu_status_t attn_bwd_check(const hstu_problem_t* p, const hstu_jagged_t* j, co
 }
 
 // d_out_lo: null, or the low bf16 terms of a dO given as two terms (bf16
-// problems only).
+// problems only).  sums: column sums for the prep launch to finish.
 hstu_status_t attn_bwd_impl(const hstu_problem_t* p, const hstu_jagged_t* j, const Tensors& t,
                             const void* d_out, const void* d_out_lo, void* dq, void* dk,
                             void* dv, float* d_rab_pos, float* d_rab_time, void* ws,
-                            size_t ws_bytes, hipStream_t s) {
+                            size_t ws_bytes, const ColSums& sums, hipStream_t s) {
   Layout l;
   HSTU_TRY(attn_bwd_check(p, j, t, d_out, dq, dk, dv, d_rab_pos, d_rab_time, ws, ws_bytes, &l));
   const int64_t T = p->total_tokens;
   const int H = p->num_heads;
   const int N = p->max_seq_len;
-  if (T == 0 || p->dtype == HSTU_F32) {
+  if (T == 0) {
     HSTU_HIP(launch_fill_f32(d_rab_pos, 2 * (int64_t)N - 1, 0.0f, s), "fill launch");
     HSTU_HIP(launch_fill_f32(d_rab_time, p->num_time_buckets, 0.0f, s), "fill launch");
+    return ok();
   }
-  if (T == 0) return ok();
   JaggedArgs ja = make_args(p, j);
   char* w = (char*)ws;
   if (p->dtype == HSTU_F32) {
     // Bias gradients summed in fp64 in the workspace, then stored as fp32.
     double* rab64 = (double*)(w + l.rab64);
     const int64_t nrab = 2 * (int64_t)N - 1 + p->num_time_buckets;
-    HSTU_HIP(launch_fill_f32((float*)rab64, 2 * nrab, 0.0f, s), "fill launch");
+    HSTU_HIP(launch_prep(ja, 1, nullptr, nullptr, nullptr,
+                         PrepFills{{(float*)rab64, nullptr, nullptr}, {2 * nrab, 0, 0}, 1}, sums,
+                         nullptr, s),
+             "prep launch");
     TimedScope ts("attn_bwd", s);
     HSTU_HIP(launch_attn_bwd_f32(ja, t, p->d_qk, p->d_v, d_out, dq, dk, dv, rab64,
                                  rab64 + (2 * (int64_t)N - 1), s),
@@ -942,7 +946,7 @@ hstu_status_t attn_bwd_impl(const hstu_problem_t* p, const hstu_jagged_t* j, con
                          {ndq, 2 * (int64_t)N - 1, (int64_t)p->num_time_buckets}, 3}
              : PrepFills{{d_rab_pos, d_rab_time, nullptr},
                          {2 * (int64_t)N - 1, (int64_t)p->num_time_buckets, 0}, 2};
-  HSTU_HIP(launch_prep(ja, 1, items, counts + 1, (int64_t*)(w + l.trange), fills,
+  HSTU_HIP(launch_prep(ja, 1, items, counts + 1, (int64_t*)(w + l.trange), fills, sums,
                        single ? nullptr : bases, s),
            "prep launch");
   {
@@ -971,7 +975,7 @@ hstu_status_t hstu_attn_bwd(const hstu_problem_t* p, const hstu_jagged_t* j, con
   try {
     Tensors t{q, q_stride, k, k_stride, v, v_stride};
     return attn_bwd_impl(p, j, t, d_out, nullptr, dq, dk, dv, d_rab_pos, d_rab_time, ws,
-                         ws_bytes, (hipStream_t)hip_stream);
+                         ws_bytes, ColSums{}, (hipStream_t)hip_stream);
   } catch (...) {
     return fail(HSTU_ERR_INVALID_ARGUMENT, "internal error");
   }
@@ -1008,17 +1012,24 @@ hstu_status_t hstu_layer_bwd(const hstu_problem_t* p, const hstu_jagged_t* j, co
     if (p->total_tokens > 0 && (!ln_mean || !ln_rstd))
       return fail(HSTU_ERR_INVALID_ARGUMENT,
                   "ln_mean and ln_rstd (saved by hstu_layer_fwd) are required");
-    if (d_ln_weight) HSTU_HIP(launch_fill_f32(d_ln_weight, D, 0.0f, s), "fill launch");
-    if (d_ln_bias) HSTU_HIP(launch_fill_f32(d_ln_bias, D, 0.0f, s), "fill launch");
-    if (p->total_tokens > 0) {
+    ColSums sums;
+    if (p->total_tokens == 0) {
+      if (d_ln_weight) HSTU_HIP(launch_fill_f32(d_ln_weight, D, 0.0f, s), "fill launch");
+      if (d_ln_bias) HSTU_HIP(launch_fill_f32(d_ln_bias, D, 0.0f, s), "fill launch");
+    } else {
+      // The partial sums of d_ln_weight / d_ln_bias pass through dq, which
+      // nothing else touches before the attention backward's last launch.
+      const int64_t dq_floats =
+          p->total_tokens * p->num_heads * p->d_qk * (int64_t)elem_size(p) / 4;
       TimedScope ts("ln_gate_bwd", s);
       HSTU_HIP(launch_ln_gate_bwd(p->dtype == HSTU_BF16, p->total_tokens, (int32_t)D, attn_out, u,
                                   u_stride, d_y, ln_weight, ln_bias, ln_mean, ln_rstd, du, dout,
-                                  dout_lo, d_ln_weight, d_ln_bias, s),
+                                  dout_lo, d_ln_weight, d_ln_bias, (float*)dq, dq_floats, &sums,
+                                  s),
                "ln_gate_bwd launch");
     }
     return attn_bwd_impl(p, j, t, dout, dout_lo, dq, dk, dv, d_rab_pos, d_rab_time, ws, ws_bytes,
-                         s);
+                         sums, s);
   } catch (...) {
     return fail(HSTU_ERR_INVALID_ARGUMENT, "internal error");
   }

@@ -67,6 +67,15 @@ struct PrepFills {
   int n;
 };
 
+// Column sums left to finish: out[0] and out[1] (either may be null), D
+// floats each, are the sums over `rows` rows of the partials [rows][2 D].
+struct ColSums {
+  const float* part = nullptr;
+  int32_t rows = 0;  // 0: nothing to do
+  int32_t D = 0;
+  float* out[2] = {nullptr, nullptr};
+};
+
 // The work an attention call does before its main kernel, in one launch:
 //  - the scheduler: the work list (longest first) into `items` and its
 //    length into `count`; mode 0: forward (seq, q-block of kFwdBM rows;
@@ -75,10 +84,13 @@ struct PrepFills {
 //  - per-sequence timestamp min / max into trange[2b], trange[2b+1] (0, 0
 //    for an empty sequence);
 //  - zeroing the arrays in `fills`;
+//  - the column sums `sums` (rows in a fixed order: reproducible);
 //  - if `bases` is set, the slot tables of the two-role backward's partial
 //    dQ blocks (int64 [2 (B + 1)]: row-block and partial-slot prefixes).
+// items null (the fp32 kernels): only the fills and the column sums.
 hipError_t launch_prep(const JaggedArgs& ja, int mode, WorkItem* items, int32_t* count,
-                       int64_t* trange, const PrepFills& fills, int64_t* bases, hipStream_t s);
+                       int64_t* trange, const PrepFills& fills, const ColSums& sums,
+                       int64_t* bases, hipStream_t s);
 
 hipError_t launch_fill_f32(float* p, int64_t n, float value, hipStream_t s);
 hipError_t launch_complete_cumsum(int32_t n, const int64_t* in, int64_t* out, int square_of_diff,
@@ -157,14 +169,17 @@ hipError_t launch_mfma_probe(int32_t iters, int32_t waves_per_simd, float* sink,
                              hipStream_t s);
 
 // Backward of LayerNorm(x) (.) u: du, dx (dense [T][D]) and, when non-null,
-// dw / db accumulated into fp32 [D] (zeroed by the caller).  x is fp32;
+// the fp32 [D] dw / db: written by the launch, or left to the column sums it
+// returns in *sums, with partials in `part` (part_floats of space, 16-byte
+// aligned; any amount serves).  x is fp32;
 // u, dy, du, dx are bf16 when is_bf16, else fp32; with is_bf16 and a
 // non-null dx_lo, dx = bf16(v) and dx_lo = bf16(v - dx) hold the fp32 v
 // as two terms.
 hipError_t launch_ln_gate_bwd(int is_bf16, int64_t T, int32_t D, const void* x, const void* u,
                               int64_t u_stride, const void* dy, const float* w, const float* b,
                               const float* mean, const float* rstd, void* du, void* dx,
-                              void* dx_lo, float* dw, float* db, hipStream_t s);
+                              void* dx_lo, float* dw, float* db, float* part,
+                              int64_t part_floats, ColSums* sums, hipStream_t s);
 
 // LayerNorm(x) (.) u per token over D features; x fp32, u and y bf16 when
 // is_bf16, else fp32.

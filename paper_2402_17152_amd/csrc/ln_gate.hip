@@ -4,9 +4,9 @@
 // variance and optional affine weight/bias; the result gates U
 // elementwise.  Saves per-token mean and 1/sqrt(var + eps) for a backward.
 //
-// HBM-bound: one wave per token, each lane holds its 8-element chunks in
-// registers (16-byte loads for bf16), two-pass mean/variance in fp32 with
-// wave reductions, one pass of stores.  The attention output x is read in
+// HBM-bound: one wave per token (several tokens per wave for D <= 256), each
+// lane holds its 8-element chunks in registers (16-byte loads for bf16),
+// two-pass mean/variance in fp32 with wave reductions, one pass of stores.  The attention output x is read in
 // fp32 for both dtypes: normalising divides by the row's spread, which can
 // be far smaller than its magnitude, so a bf16-rounded x would carry
 // errors of several percent into Y.
@@ -15,12 +15,6 @@
 namespace hstu {
 
 namespace {
-
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 template <bool BF16>
 __device__ __forceinline__ void load8(const void* base, int64_t idx, float* out) {
@@ -62,8 +56,63 @@ __device__ __forceinline__ void store8(void* base, int64_t idx, const float* v) 
   }
 }
 
-// CH = chunks of 8 elements per lane (D <= 512 * CH).
-template <bool BF16, int CH>
+// CH chunks of 8 elements per lane, LPR lanes per token row (64 / LPR rows
+// per wave; LPR < 64 only with CH = 1): D <= 8 LPR CH.  Narrow rows share a
+// wave, so its lanes are not idle past D.
+template <int LPR>
+__device__ __forceinline__ float row_sum(float v) {
+#pragma unroll
+  for (int off = LPR / 2; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// The affine parameters of a lane's features, kept in registers over its
+// rows where they fit (CH <= 2), else re-read (from cache) per row.  16-byte
+// loads: read one by one per token they cost the forward 133 us instead of
+// 40 us on 62 K tokens of 512 features.
+template <int CH>
+struct Affine {
+  static constexpr bool kHeld = CH <= 2;
+  const float* p;  // may be null: `fill` instead
+  float fill;
+  float v[kHeld ? CH : 1][8];
+  __device__ __forceinline__ void read(int idx, float (&o)[8]) const {
+    if (p) {
+      // The caller's parameter arrays are only known to be 4-byte aligned.
+      typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+      const f32x4u a = *reinterpret_cast<const f32x4u*>(p + idx);
+      const f32x4u c = *reinterpret_cast<const f32x4u*>(p + idx + 4);
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        o[e] = a[e];
+        o[4 + e] = c[e];
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < 8; e++) o[e] = fill;
+    }
+  }
+  __device__ __forceinline__ Affine(const float* ptr, float f, int D, int sub, int lpr)
+      : p(ptr), fill(f) {
+    if constexpr (kHeld) {
+#pragma unroll
+      for (int c = 0; c < CH; c++) {
+        const int idx = (c * lpr + sub) * 8;
+        if (idx < D) read(idx, v[c]);
+      }
+    }
+  }
+  __device__ __forceinline__ void get(int c, int idx, float (&o)[8]) const {
+    if constexpr (kHeld) {
+#pragma unroll
+      for (int e = 0; e < 8; e++) o[e] = v[c][e];
+    } else {
+      read(idx, o);
+    }
+  }
+};
+
+template <bool BF16, int CH, int LPR>
 __global__ __launch_bounds__(256) void ln_gate_kernel(int64_t T, int D, const void* __restrict__ x,
                                                       const void* __restrict__ u, int64_t u_stride,
                                                       const float* __restrict__ w,
@@ -71,54 +120,61 @@ __global__ __launch_bounds__(256) void ln_gate_kernel(int64_t T, int D, const vo
                                                       void* __restrict__ y,
                                                       float* __restrict__ mean,
                                                       float* __restrict__ rstd) {
+  constexpr int RPW = 64 / LPR;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t t = (int64_t)blockIdx.x * 4 + wave;
-  if (t >= T) return;
-  float v[CH][8];
-  float sum = 0.0f;
+  const int sub = lane % LPR, row = lane / LPR;
+  const Affine<CH> aw(w, 1.0f, D, sub, LPR), ab(b, 0.0f, D, sub, LPR);
+  const int64_t step = (int64_t)gridDim.x * (4 * RPW);
+  for (int64_t t0 = ((int64_t)blockIdx.x * 4 + wave) * RPW; t0 < T; t0 += step) {
+    const int64_t t = t0 + row;
+    const bool ok = t < T;
+    // u is loaded with x where both fit in registers, else when it is used.
+    constexpr bool kEarly = CH <= 2;
+    float v[CH][8], g[kEarly ? CH : 1][8];
+    float sum = 0.0f;
 #pragma unroll
-  for (int c = 0; c < CH; c++) {
-    const int idx = (c * 64 + lane) * 8;
-    if (idx < D) {
-      load8<false>(x, t * D + idx, v[c]);
+    for (int c = 0; c < CH; c++) {
+      const int idx = (c * LPR + sub) * 8;
+      if (ok && idx < D) {
+        load8<false>(x, t * D + idx, v[c]);
+        if constexpr (kEarly) load8<BF16>(u, t * u_stride + idx, g[c]);
 #pragma unroll
-      for (int e = 0; e < 8; e++) sum += v[c][e];
-    }
-  }
-  const float mu = wave_sum(sum) / (float)D;
-  float sq = 0.0f;
-#pragma unroll
-  for (int c = 0; c < CH; c++) {
-    const int idx = (c * 64 + lane) * 8;
-    if (idx < D) {
-#pragma unroll
-      for (int e = 0; e < 8; e++) {
-        const float d = v[c][e] - mu;
-        sq += d * d;
+        for (int e = 0; e < 8; e++) sum += v[c][e];
       }
     }
-  }
-  const float var = wave_sum(sq) / (float)D;
-  const float rs = 1.0f / sqrtf(var + eps);
+    const float mu = row_sum<LPR>(sum) / (float)D;
+    float sq = 0.0f;
 #pragma unroll
-  for (int c = 0; c < CH; c++) {
-    const int idx = (c * 64 + lane) * 8;
-    if (idx < D) {
-      float g[8], out[8];
-      load8<BF16>(u, t * u_stride + idx, g);
+    for (int c = 0; c < CH; c++) {
+      const int idx = (c * LPR + sub) * 8;
+      if (ok && idx < D) {
 #pragma unroll
-      for (int e = 0; e < 8; e++) {
-        float z = (v[c][e] - mu) * rs;
-        if (w) z *= w[idx + e];
-        if (b) z += b[idx + e];
-        out[e] = z * g[e];
+        for (int e = 0; e < 8; e++) {
+          const float d = v[c][e] - mu;
+          sq += d * d;
+        }
       }
-      store8<BF16>(y, t * D + idx, out);
     }
-  }
-  if (lane == 0) {
-    if (mean) mean[t] = mu;
-    if (rstd) rstd[t] = rs;
+    const float var = row_sum<LPR>(sq) / (float)D;
+    const float rs = 1.0f / sqrtf(var + eps);
+#pragma unroll
+    for (int c = 0; c < CH; c++) {
+      const int idx = (c * LPR + sub) * 8;
+      if (ok && idx < D) {
+        float ww[8], bb[8], out[8];
+        aw.get(c, idx, ww);
+        ab.get(c, idx, bb);
+        const int gc = kEarly ? c : 0;
+        if constexpr (!kEarly) load8<BF16>(u, t * u_stride + idx, g[gc]);
+#pragma unroll
+        for (int e = 0; e < 8; e++) out[e] = ((v[c][e] - mu) * rs * ww[e] + bb[e]) * g[gc][e];
+        store8<BF16>(y, t * D + idx, out);
+      }
+    }
+    if (ok && sub == 0) {
+      if (mean) mean[t] = mu;
+      if (rstd) rstd[t] = rs;
+    }
   }
 }
 
@@ -126,55 +182,67 @@ __global__ __launch_bounds__(256) void ln_gate_kernel(int64_t T, int D, const vo
 // forward's saved statistics) and zn = z * w + b,
 //   du = zn (.) dy,  dzn = dy (.) u,  dw += dzn z,  db += dzn,
 //   dz = dzn (.) w,  dx = rstd (dz - mean(dz) - z mean(dz z)).
-// One wave per token in a grid-stride loop; dw / db partials stay in
-// registers across the wave's tokens and reach HBM with one float atomic
-// per feature and wave.
-template <bool BF16, int CH>
+// HBM-bound: 14 bytes per element in bf16.  A wave keeps the dw / db sums
+// of its rows in registers; at the end a workgroup adds its waves' sums in
+// LDS and stores one row of partials [2 D] (dw, then db), which the prep
+// launch of the attention backward sums over the workgroups in a fixed
+// order.  (One float atomic per feature and wave, 4096 waves on the same
+// 2 D addresses, took 860 us on 62 K tokens of 512 features, of which the
+// memory traffic is 75 us.)  A single workgroup stores the sums themselves.
+template <bool BF16, int CH, int LPR>
 __global__ __launch_bounds__(256) void ln_gate_bwd_kernel(
     int64_t T, int D, const void* __restrict__ x, const void* __restrict__ u, int64_t u_stride,
     const void* __restrict__ dy, const float* __restrict__ w, const float* __restrict__ b,
     const float* __restrict__ mean, const float* __restrict__ rstd, void* __restrict__ du,
-    void* __restrict__ dx, void* __restrict__ dx_lo, float* __restrict__ dw,
-    float* __restrict__ db) {
+    void* __restrict__ dx, void* __restrict__ dx_lo, float* __restrict__ dw_out,
+    float* __restrict__ db_out) {
+  constexpr int RPW = 64 / LPR, COLS = 8 * LPR;  // columns per chunk c
+  __shared__ __align__(16) float red[4][2][COLS];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int sub = lane % LPR, row = lane / LPR;
+  const Affine<CH> aw(w, 1.0f, D, sub, LPR), ab(b, 0.0f, D, sub, LPR);
   float pw[CH][8], pb[CH][8];
 #pragma unroll
   for (int c = 0; c < CH; c++)
 #pragma unroll
     for (int e = 0; e < 8; e++) pw[c][e] = pb[c][e] = 0.0f;
-  for (int64_t t = (int64_t)blockIdx.x * 4 + wave; t < T; t += (int64_t)gridDim.x * 4) {
-    const float mu = mean[t], rs = rstd[t];
+  const int64_t step = (int64_t)gridDim.x * (4 * RPW);
+  for (int64_t t0 = ((int64_t)blockIdx.x * 4 + wave) * RPW; t0 < T; t0 += step) {
+    const int64_t t = t0 + row;
+    const bool ok = t < T;
+    const float mu = ok ? mean[t] : 0.0f, rs = ok ? rstd[t] : 0.0f;
     float z[CH][8], dz[CH][8];
     float s1 = 0.0f, s2 = 0.0f;
 #pragma unroll
     for (int c = 0; c < CH; c++) {
-      const int idx = (c * 64 + lane) * 8;
-      if (idx < D) {
-        float xv[8], uv[8], gv[8], o[8];
+      const int idx = (c * LPR + sub) * 8;
+      if (ok && idx < D) {
+        float xv[8], uv[8], gv[8], ww[8], bb[8], o[8];
         load8<false>(x, t * D + idx, xv);
         load8<BF16>(u, t * u_stride + idx, uv);
         load8<BF16>(dy, t * D + idx, gv);
+        aw.get(c, idx, ww);
+        ab.get(c, idx, bb);
 #pragma unroll
         for (int e = 0; e < 8; e++) {
           const float zz = (xv[e] - mu) * rs;
-          const float ww = w ? w[idx + e] : 1.0f, bb = b ? b[idx + e] : 0.0f;
           const float dzn = gv[e] * uv[e];
           z[c][e] = zz;
-          o[e] = (zz * ww + bb) * gv[e];
+          o[e] = (zz * ww[e] + bb[e]) * gv[e];
           pw[c][e] += dzn * zz;
           pb[c][e] += dzn;
-          dz[c][e] = dzn * ww;
+          dz[c][e] = dzn * ww[e];
           s1 += dz[c][e];
           s2 += dz[c][e] * zz;
         }
         store8<BF16>(du, t * D + idx, o);
       }
     }
-    const float m1 = wave_sum(s1) / (float)D, m2 = wave_sum(s2) / (float)D;
+    const float m1 = row_sum<LPR>(s1) / (float)D, m2 = row_sum<LPR>(s2) / (float)D;
 #pragma unroll
     for (int c = 0; c < CH; c++) {
-      const int idx = (c * 64 + lane) * 8;
-      if (idx < D) {
+      const int idx = (c * LPR + sub) * 8;
+      if (ok && idx < D) {
         float o[8];
 #pragma unroll
         for (int e = 0; e < 8; e++) o[e] = rs * (dz[c][e] - m1 - z[c][e] * m2);
@@ -189,37 +257,57 @@ __global__ __launch_bounds__(256) void ln_gate_bwd_kernel(
       }
     }
   }
+  if (!dw_out && !db_out) return;
+  const int64_t out_row = gridDim.x > 1 ? (int64_t)blockIdx.x * 2 * D : 0;
 #pragma unroll
   for (int c = 0; c < CH; c++) {
-    const int idx = (c * 64 + lane) * 8;
-    if (idx < D) {
+    // Rows of the wave, then (in wave order) the four waves.
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1)
 #pragma unroll
       for (int e = 0; e < 8; e++) {
-        if (dw) unsafeAtomicAdd(&dw[idx + e], pw[c][e]);
-        if (db) unsafeAtomicAdd(&db[idx + e], pb[c][e]);
+        pw[c][e] += __shfl_xor(pw[c][e], off, 64);
+        pb[c][e] += __shfl_xor(pb[c][e], off, 64);
       }
+    if (row == 0) {
+      store8<false>(&red[wave][0][8 * sub], 0, pw[c]);
+      store8<false>(&red[wave][1][8 * sub], 0, pb[c]);
     }
+    __syncthreads();
+    for (int i = threadIdx.x; i < 2 * COLS; i += 256) {
+      const int which = i / COLS, col = i % COLS;
+      const float s = red[0][which][col] + red[1][which][col] + red[2][which][col] +
+                      red[3][which][col];
+      float* o = which ? db_out : dw_out;
+      if (o && c * COLS + col < D) o[out_row + c * COLS + col] = s;
+    }
+    __syncthreads();
   }
 }
+
+// The instance for D features: lanes per row for D <= 512, chunks above.
+#define LN_DISPATCH(CALL)           \
+  if (D <= 64) { CALL(1, 8) }       \
+  if (D <= 128) { CALL(1, 16) }     \
+  if (D <= 256) { CALL(1, 32) }     \
+  if (D <= 512) { CALL(1, 64) }     \
+  if (D <= 1024) { CALL(2, 64) }    \
+  if (D <= 2048) { CALL(4, 64) }    \
+  if (D <= 4096) { CALL(8, 64) }
+
+int64_t rows_per_block(int32_t D) { return D <= 64 ? 32 : D <= 128 ? 16 : D <= 256 ? 8 : 4; }
 
 template <bool BF16>
 hipError_t ln_bwd_case(int64_t T, int32_t D, const void* x, const void* u, int64_t u_stride,
                        const void* dy, const float* w, const float* b, const float* mean,
                        const float* rstd, void* du, void* dx, void* dx_lo, float* dw,
-                       float* db, hipStream_t s) {
-  // Enough waves to fill the device; each walks several tokens so the
-  // per-feature atomics stay few.
-  const int64_t blocks = min((T + 3) / 4, (int64_t)1024);
-  dim3 grid((unsigned)blocks);
-  const int ch = (D + 511) / 512;
-#define LN_BWD_CALL(C)                                                                        \
-  hipLaunchKernelGGL((ln_gate_bwd_kernel<BF16, C>), grid, dim3(256), 0, s, T, D, x, u,         \
+                       float* db, int64_t blocks, hipStream_t s) {
+  const dim3 grid((unsigned)blocks);
+#define LN_BWD_CALL(C, LPR)                                                                   \
+  hipLaunchKernelGGL((ln_gate_bwd_kernel<BF16, C, LPR>), grid, dim3(256), 0, s, T, D, x, u,    \
                      u_stride, dy, w, b, mean, rstd, du, dx, dx_lo, dw, db);                  \
   return hipGetLastError();
-  if (ch <= 1) { LN_BWD_CALL(1) }
-  if (ch <= 2) { LN_BWD_CALL(2) }
-  if (ch <= 4) { LN_BWD_CALL(4) }
-  if (ch <= 8) { LN_BWD_CALL(8) }
+  LN_DISPATCH(LN_BWD_CALL)
 #undef LN_BWD_CALL
   return hipErrorInvalidValue;
 }
@@ -228,16 +316,14 @@ template <bool BF16>
 hipError_t ln_case(int64_t T, int32_t D, const void* x, const void* u, int64_t u_stride,
                    const float* w, const float* b, float eps, void* y, float* mean, float* rstd,
                    hipStream_t s) {
-  dim3 grid((unsigned)((T + 3) / 4));
-  const int ch = (D + 511) / 512;
-#define LN_CALL(C)                                                                          \
-  hipLaunchKernelGGL((ln_gate_kernel<BF16, C>), grid, dim3(256), 0, s, T, D, x, u, u_stride, \
-                     w, b, eps, y, mean, rstd);                                             \
+  // At most the 8 workgroups a CU holds; each keeps the affine in registers.
+  const int64_t rows = rows_per_block(D);
+  dim3 grid((unsigned)min((T + rows - 1) / rows, (int64_t)2048));
+#define LN_CALL(C, LPR)                                                                     \
+  hipLaunchKernelGGL((ln_gate_kernel<BF16, C, LPR>), grid, dim3(256), 0, s, T, D, x, u,      \
+                     u_stride, w, b, eps, y, mean, rstd);                                   \
   return hipGetLastError();
-  if (ch <= 1) { LN_CALL(1) }
-  if (ch <= 2) { LN_CALL(2) }
-  if (ch <= 4) { LN_CALL(4) }
-  if (ch <= 8) { LN_CALL(8) }
+  LN_DISPATCH(LN_CALL)
 #undef LN_CALL
   return hipErrorInvalidValue;
 }
@@ -247,13 +333,28 @@ hipError_t ln_case(int64_t T, int32_t D, const void* x, const void* u, int64_t u
 hipError_t launch_ln_gate_bwd(int is_bf16, int64_t T, int32_t D, const void* x, const void* u,
                               int64_t u_stride, const void* dy, const float* w, const float* b,
                               const float* mean, const float* rstd, void* du, void* dx,
-                              void* dx_lo, float* dw, float* db, hipStream_t s) {
+                              void* dx_lo, float* dw, float* db, float* part,
+                              int64_t part_floats, ColSums* sums, hipStream_t s) {
+  *sums = ColSums{};
   if (T <= 0) return hipSuccess;
+  // Two passes of rows per workgroup before more workgroups only add
+  // partials, and at most five workgroups on each of the 256 CUs.
+  const int64_t rows = 2 * rows_per_block(D);
+  int64_t blocks = min((T + rows - 1) / rows, (int64_t)1280);
+  float *dw_out = dw, *db_out = db;
+  if (dw || db) {
+    blocks = max(min(blocks, part_floats / (2 * D)), (int64_t)1);
+    if (blocks > 1) {
+      *sums = ColSums{part, (int32_t)blocks, D, {dw, db}};
+      dw_out = dw ? part : nullptr;
+      db_out = db ? part + D : nullptr;
+    }
+  }
   if (is_bf16)
-    return ln_bwd_case<true>(T, D, x, u, u_stride, dy, w, b, mean, rstd, du, dx, dx_lo, dw, db,
-                             s);
-  return ln_bwd_case<false>(T, D, x, u, u_stride, dy, w, b, mean, rstd, du, dx, nullptr, dw, db,
-                            s);
+    return ln_bwd_case<true>(T, D, x, u, u_stride, dy, w, b, mean, rstd, du, dx, dx_lo, dw_out,
+                             db_out, blocks, s);
+  return ln_bwd_case<false>(T, D, x, u, u_stride, dy, w, b, mean, rstd, du, dx, nullptr, dw_out,
+                            db_out, blocks, s);
 }
 
 hipError_t launch_ln_gate(int is_bf16, int64_t T, int32_t D, const void* x, const void* u,

@@ -293,46 +293,81 @@ __device__ void bases_block(const JaggedArgs& ja, int64_t* bases, int64_t (*s)[k
   }
 }
 
+// Column sums: workgroup g of ceil(2 D / 32) owns 32 columns; its 32 row
+// groups each sum every 32nd row, then the group sums are added in order.
+__device__ void col_sums_block(const ColSums& cs, int g, float (*red)[33]) {
+  const int col = threadIdx.x & 31, grp = threadIdx.x >> 5;
+  const int i = 32 * g + col, n = 2 * cs.D;
+  float s = 0.0f;
+  if (i < n) {
+#pragma unroll 8
+    for (int r = grp; r < cs.rows; r += 32) s += cs.part[(int64_t)r * n + i];
+  }
+  red[grp][col] = s;
+  __syncthreads();
+  if (grp == 0 && i < n) {
+    float t = 0.0f;
+#pragma unroll
+    for (int q = 0; q < 32; q++) t += red[q][col];
+    float* o = cs.out[i / cs.D];
+    if (o) o[i % cs.D] = t;
+  }
+}
+
 // Everything an attention call needs before its main kernel, in one
 // launch: workgroup 0 builds the work list, workgroups 1..B take one
-// sequence's timestamp range each, the next ones zero the fills, and (if
-// `bases` is set) the last one writes the backward's slot tables.
+// sequence's timestamp range each (both only with `items`), the next ones
+// zero the fills, the next take the column sums, and (if `bases` is set)
+// the last one writes the backward's slot tables.
 __global__ __launch_bounds__(kSchedThreads) void prep_kernel(JaggedArgs ja, int mode,
                                                              WorkItem* items, int32_t* count,
                                                              int64_t* trange, PrepFills fills,
-                                                             int nfill_blocks, int64_t* bases) {
+                                                             int nfill_blocks, ColSums sums,
+                                                             int nsum_blocks, int64_t* bases) {
   extern __shared__ int s_bins[];  // [maxw + 1]
   __shared__ int s_scan[kSchedThreads];
   __shared__ int64_t red[2][kSchedThreads / 64];
   __shared__ int64_t s_bases[2][kSchedThreads];
-  const int g = (int)blockIdx.x;
-  if (g == 0) {
-    schedule_block(ja, mode, items, count, s_bins, s_scan);
-  } else if (g <= ja.num_seqs) {
-    time_range_block(ja, g - 1, trange, red);
-  } else if (g <= ja.num_seqs + nfill_blocks) {
-    fill_blocks(fills, g - 1 - ja.num_seqs, nfill_blocks);
-  } else {
-    bases_block(ja, bases, s_bases);
+  __shared__ float s_sums[32][33];
+  int g = (int)blockIdx.x;
+  if (items) {
+    if (g == 0) {
+      schedule_block(ja, mode, items, count, s_bins, s_scan);
+      return;
+    }
+    if (g <= ja.num_seqs) {
+      time_range_block(ja, g - 1, trange, red);
+      return;
+    }
+    g -= 1 + ja.num_seqs;
   }
+  if (g < nfill_blocks)
+    fill_blocks(fills, g, nfill_blocks);
+  else if (g < nfill_blocks + nsum_blocks)
+    col_sums_block(sums, g - nfill_blocks, s_sums);
+  else
+    bases_block(ja, bases, s_bases);
 }
 
 }  // namespace
 
 hipError_t launch_prep(const JaggedArgs& ja, int mode, WorkItem* items, int32_t* count,
-                       int64_t* trange, const PrepFills& fills, int64_t* bases, hipStream_t s) {
+                       int64_t* trange, const PrepFills& fills, const ColSums& sums,
+                       int64_t* bases, hipStream_t s) {
   const int maxw = mode == 0 ? (ja.max_seq_len + kFwdBN - 1) / kFwdBN
                              : (ja.max_seq_len + kBwdBM - 1) / kBwdBM;
-  const size_t lds = sizeof(int) * (size_t)(maxw + 1);
+  const size_t lds = items ? sizeof(int) * (size_t)(maxw + 1) : 0;
   int64_t work4 = 0;
   for (int k = 0; k < fills.n; k++) work4 += (fills.count[k] + 3) / 4;
   // About four float4 stores per thread for large fills, at most 1024 blocks.
   int64_t nf = (work4 + 4 * kSchedThreads - 1) / (4 * kSchedThreads);
   nf = nf > 1024 ? 1024 : nf;
   if (work4 > 0 && nf < 1) nf = 1;
-  const int64_t grid = 1 + (int64_t)ja.num_seqs + nf + (bases ? 1 : 0);
+  const int nsum = sums.rows > 0 ? (2 * sums.D + 31) / 32 : 0;
+  const int64_t grid = (items ? 1 + (int64_t)ja.num_seqs : 0) + nf + nsum + (bases ? 1 : 0);
+  if (grid == 0) return hipSuccess;
   hipLaunchKernelGGL(prep_kernel, dim3((unsigned)grid), dim3(kSchedThreads), lds, s, ja, mode,
-                     items, count, trange, fills, (int)nf, bases);
+                     items, count, trange, fills, (int)nf, sums, nsum, bases);
   return hipGetLastError();
 }
 
