@@ -46,11 +46,9 @@
  *            timestamps in [0, 2^62)) are not checked by the hot calls;
  *            breaking them is undefined.  hstu_validate checks them.
  *   Precision HSTU_F32: fp32 storage and arithmetic (the bias-table
- *            gradients are summed in fp64 and stored as fp32).  Its
- *            kernels are plain SIMT loops, one thread per (token, head),
- *            meant for small problems and as an fp32 reference: every shape
- *            the ABI accepts runs, but long sequences are slow (the matrix
- *            cores serve HSTU_BF16 only).  HSTU_BF16: bf16 storage, fp32
+ *            gradients are summed in fp64 and stored as fp32), the
+ *            contractions on the fp32 matrix instructions: about 1/16 of
+ *            the bf16 rate.  HSTU_BF16: bf16 storage, fp32
  *            accumulation; in hstu_attn_fwd / hstu_attn_bwd the attention
  *            weights and dS are rounded to bf16 (nearest-even) where they
  *            enter the matrix cores; hstu_layer_fwd / hstu_layer_bwd carry

@@ -921,9 +921,7 @@ hstu_status_t attn_bwd_impl(const hstu_problem_t* p, const hstu_jagged_t* j, con
     HSTU_HIP(launch_attn_bwd_f32(ja, t, p->d_qk, p->d_v, d_out, dq, dk, dv, rab64,
                                  rab64 + (2 * (int64_t)N - 1), s),
              "attn_bwd_f32 launch");
-    HSTU_HIP(launch_f64_to_f32_scaled(rab64, d_rab_pos, 2 * (int64_t)N - 1, 1.0 / N, s),
-             "convert launch");
-    HSTU_HIP(launch_f64_to_f32_scaled(rab64 + (2 * (int64_t)N - 1), d_rab_time,
+    HSTU_HIP(launch_f64_to_f32_scaled(rab64, d_rab_pos, 2 * (int64_t)N - 1, d_rab_time,
                                       p->num_time_buckets, 1.0 / N, s),
              "convert launch");
     return ok();

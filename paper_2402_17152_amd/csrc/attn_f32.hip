@@ -1,190 +1,619 @@
-// fp32 jagged pointwise attention, forward and backward, plain SIMT
-// arithmetic (no matrix cores): the HSTU_F32 variant of the library,
-// meant for small problems where fp32 throughout is wanted.
+// fp32 jagged pointwise attention, forward and backward: the HSTU_F32
+// variant of the library, for problems where fp32 throughout is wanted.
 //
 // Same definitions as the bf16 kernels (Eq. 2 with the pointwise 1/N
-// normaliser, rab^{p,t} from the two tables, Algorithm 1 mask), one
-// thread per (token, head):
-//   forward       thread = query row i: O_i = (1/N) sum_j SiLU(s_ij) v_j;
-//   backward (a)  thread = query row i: dQ_i = (1/N) sum_j dS_ij k_j and
-//                 the bias gradients, summed in fp64 (one atomic per pair
-//                 for the position table; for the time table a running
-//                 sum per thread, added when the bucket changes, so that a
-//                 bucket's millions of terms do not pile up fp32 rounding);
-//   backward (b)  thread = key row j:   dK_j = (1/N) sum_i dS_ij q_i,
-//                                       dV_j = (1/N) sum_i SiLU(s_ij) dO_i.
+// normaliser, rab^{p,t} from the two tables, Algorithm 1 mask), with every
+// contraction on the fp32 matrix instruction v_mfma_f32_16x16x4_f32 (fp32
+// products and sums, the rounding of a plain multiply-add chain).
+//
+// A workgroup of 4 waves owns 32 consecutive token rows of one head and
+// walks 32-wide tiles of the other side, of each sequence that its rows
+// belong to in turn (rows of other sequences are masked, so one set of
+// accumulators serves them all and no work list is needed):
+//   forward    rows = queries, tiles = keys:  O += P V;
+//   backward   two kinds of workgroups in one launch,
+//     (a) rows = queries, tiles = keys:  dQ += dS K, and the bias gradients
+//         in fp64: one sum per diagonal of a tile (history rows) or per key
+//         (candidate rows, all at one position), and a running sum per
+//         thread and time bucket, so that a bucket's millions of terms do
+//         not pile up fp32 rounding;
+//     (b) rows = keys, tiles = queries:  dV += P^T dO, dK += dS^T Q.
+// Wave (wr, wc) computes the 16 x 16 quadrant of a tile's scores, which pass
+// through LDS to become the operand of the second contraction.
+//
+// Bound by the latency of one tile after another: a tile's loads (operand
+// rows, timestamps, the 64 entries of rab_pos it can use) are issued while
+// the tile before is computed.  One thread per (row, head) with the keys
+// one by one, as before, took 47 + 58 + 60 us (forward, dQ, dK / dV) on four
+// sequences of up to 128 tokens (2 heads of 32).
 #include "kernels.h"
 
 namespace hstu {
 
 namespace {
 
-struct Row {
-  int64_t o;
-  int L, n_h, idx;
-};
+constexpr int kRows = 32;      // token rows of a workgroup, and width of a tile
+constexpr int kScoreLd = 36;   // row pitch of the score tiles
+constexpr int kThreads = 256;
 
-// Sequence holding global token r: last b with seq_offsets[b] <= r.
-__device__ __forceinline__ Row locate(const JaggedArgs& ja, int64_t r) {
+__device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
+  return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
+}
+
+__device__ __forceinline__ bool not_finite(float x) {
+  return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u;
+}
+
+// Last sequence b with seq_offsets[b] <= r (64 probes at a time).
+__device__ __forceinline__ int find_seq(const JaggedArgs& ja, int64_t r) {
+  const int lane = threadIdx.x & 63;
   int lo = 0, hi = ja.num_seqs;  // seq_offsets[lo] <= r < seq_offsets[hi]
   while (hi - lo > 1) {
-    int mid = (lo + hi) >> 1;
-    if (ja.seq_offsets[mid] <= r) lo = mid; else hi = mid;
+    const int step = (hi - lo + 63) >> 6;
+    const int x = min(lo + (lane + 1) * step, hi);
+    const uint64_t above = __ballot(ja.seq_offsets[x] > r);  // lane 63's probe is hi: never empty
+    const int f = __builtin_ctzll(above);
+    hi = min(lo + (f + 1) * step, hi);
+    lo = lo + f * step;
   }
-  Row w;
-  w.o = ja.seq_offsets[lo];
-  w.L = (int)(ja.seq_offsets[lo + 1] - w.o);
-  w.n_h = w.L - (ja.num_targets ? (int)ja.num_targets[lo] : 0);
-  w.idx = (int)(r - w.o);
-  return w;
+  return __builtin_amdgcn_readfirstlane(lo);
 }
 
-__device__ __forceinline__ float bias_of(const JaggedArgs& ja, const Row& w, int i, int j,
-                                         int64_t ti, int64_t tj) {
-  const int idx = (ja.max_seq_len - 1) + bias_pos(j, w.n_h) - bias_pos(i, w.n_h);
-  return ja.rab_pos[idx] + ja.rab_time[time_bucket64(ti - tj, ja.num_buckets)];
-}
-
-template <int DQK, int DV>
-__global__ __launch_bounds__(64) void fwd_f32_kernel(JaggedArgs ja, Tensors t, float* out) {
-  const int64_t r = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (r >= ja.total_tokens) return;
-  const int head = blockIdx.y, H = ja.num_heads;
-  const Row w = locate(ja, r);
-  const int i = w.idx;
-  const float* qg = (const float*)t.q + r * t.q_stride + head * DQK;
-  float q[DQK], acc[DV];
-  for (int c = 0; c < DQK; c++) q[c] = qg[c];
-  for (int c = 0; c < DV; c++) acc[c] = 0.0f;
-  const int64_t ti = ja.timestamps[r];
-  for (int j = 0; j <= i; j++) {
-    if (!pair_valid(i, j, w.n_h)) continue;
-    const float* kj = (const float*)t.k + (w.o + j) * t.k_stride + head * DQK;
-    const float* vj = (const float*)t.v + (w.o + j) * t.v_stride + head * DV;
-    float s = bias_of(ja, w, i, j, ti, ja.timestamps[w.o + j]);
-    for (int c = 0; c < DQK; c++) s += q[c] * kj[c];
-    const float p = s * sigmoid_fast(s);
-    for (int c = 0; c < DV; c++) acc[c] += p * vj[c];
-  }
-  const float invN = 1.0f / (float)ja.max_seq_len;
-  float* og = out + (r * H + head) * DV;
-  for (int c = 0; c < DV; c++) og[c] = acc[c] * invN;
-}
-
-template <int DQK, int DV>
-__global__ __launch_bounds__(64) void bwd_dq_f32_kernel(JaggedArgs ja, Tensors t, const float* dO,
-                                                        float* dq, double* rab_pos_acc,
-                                                        double* rab_time_acc) {
-  const int64_t r = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (r >= ja.total_tokens) return;
-  const int head = blockIdx.y, H = ja.num_heads, N = ja.max_seq_len;
-  const Row w = locate(ja, r);
-  const int i = w.idx;
-  const float invN = 1.0f / (float)N;
-  const float* qg = (const float*)t.q + r * t.q_stride + head * DQK;
-  const float* dog = dO + (r * H + head) * DV;
-  float q[DQK], g[DV], acc[DQK];
-  for (int c = 0; c < DQK; c++) {
-    q[c] = qg[c];
-    acc[c] = 0.0f;
-  }
-  for (int c = 0; c < DV; c++) g[c] = dog[c];
-  const int64_t ti = ja.timestamps[r];
-  int run_b = -1;
-  double run = 0.0;
-  for (int j = 0; j <= i; j++) {
-    if (!pair_valid(i, j, w.n_h)) continue;
-    const float* kj = (const float*)t.k + (w.o + j) * t.k_stride + head * DQK;
-    const float* vj = (const float*)t.v + (w.o + j) * t.v_stride + head * DV;
-    const int64_t tj = ja.timestamps[w.o + j];
-    float s = bias_of(ja, w, i, j, ti, tj);
-    for (int c = 0; c < DQK; c++) s += q[c] * kj[c];
-    float dp = 0.0f;
-    for (int c = 0; c < DV; c++) dp += g[c] * vj[c];
-    const float sg = sigmoid_fast(s);
-    const float ds = dp * (sg + s * sg * (1.0f - sg));
-    for (int c = 0; c < DQK; c++) acc[c] += ds * kj[c];
-    const int kpos = bias_pos(i, w.n_h) - bias_pos(j, w.n_h);
-    unsafeAtomicAdd(&rab_pos_acc[(N - 1) - kpos], (double)ds);
-    const int b = time_bucket64(ti - tj, ja.num_buckets);
-    if (b != run_b) {
-      if (run_b >= 0) unsafeAtomicAdd(&rab_time_acc[run_b], run);
-      run_b = b;
-      run = 0.0;
+// One operand tile of 32 rows of D floats: global -> registers -> LDS rows
+// of D + 4 floats.  Rows outside [0, L) read as zeros.
+template <int D>
+struct TileRegs {
+  static constexpr int kPer = D / 32, kLd = D + 4;
+  f32x4 v[kPer];
+  __device__ __forceinline__ void load(const float* base, int64_t stride, int row0, int L,
+                                       int tid) {
+#pragma unroll
+    for (int e = 0; e < kPer; e++) {
+      const int c = tid + kThreads * e, r = row0 + c / (D / 4);
+      v[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      if (r >= 0 && r < L)
+        v[e] = *reinterpret_cast<const f32x4*>(base + (int64_t)r * stride + 4 * (c % (D / 4)));
     }
-    run += (double)ds;
   }
-  if (run_b >= 0) unsafeAtomicAdd(&rab_time_acc[run_b], run);
-  float* out = dq + (r * H + head) * DQK;
-  for (int c = 0; c < DQK; c++) out[c] = acc[c] * invN;
+  // Stores the tile; sets *bad if it holds an infinity or a NaN.
+  __device__ __forceinline__ void store(float* t, int tid, int* bad) const {
+    bool b = false;
+#pragma unroll
+    for (int e = 0; e < kPer; e++) {
+      const int c = tid + kThreads * e;
+      *reinterpret_cast<f32x4*>(t + (c / (D / 4)) * kLd + 4 * (c % (D / 4))) = v[e];
+#pragma unroll
+      for (int m = 0; m < 4; m++) b |= not_finite(v[e][m]);
+    }
+    if (b) *bad = 1;
+  }
+};
+
+// c[m][n] += sum over d of a[m0 + m][d] b[n0 + n][d]: the lane's 4
+// consecutive d of a 16-byte read feed four matrix instructions (any order
+// of the contraction index serves, as long as both operands share it).
+template <int D>
+__device__ __forceinline__ f32x4 dot_tile(const float* a, const float* b, int lane, f32x4 c) {
+  const int off = (lane & 15) * (D + 4) + 4 * (lane >> 4);
+#pragma unroll
+  for (int s = 0; s < D / 16; s++) {
+    const f32x4 av = *reinterpret_cast<const f32x4*>(a + off + 16 * s);
+    const f32x4 bv = *reinterpret_cast<const f32x4*>(b + off + 16 * s);
+#pragma unroll
+    for (int e = 0; e < 4; e++) c = mfma16x16x4(av[e], bv[e], c);
+  }
+  return c;
+}
+
+// acc[f] += sum over x of w[m][x] t[x][f] for 16 rows m of the score tile w
+// and the wave's D / 2 features of the 32 tile rows x (acc element r of
+// block nb: row 4 (lane / 16) + r, feature 16 nb + lane % 16).  A pair that
+// the mask drops has w = 0, which a non-finite t would turn into NaN, so a
+// tile holding one takes the plain loop over the pairs that `keep(r, x)`s.
+template <int D, typename Keep>
+__device__ __forceinline__ void outer_tile(const float* w, const float* t, int f0, int lane,
+                                           bool plain, Keep&& keep, f32x4 (&acc)[D / 32]) {
+  const int n = lane & 15, g = lane >> 4;
+  if (!plain) {
+#pragma unroll
+    for (int s = 0; s < 2; s++) {
+      const f32x4 a = *reinterpret_cast<const f32x4*>(w + n * kScoreLd + 16 * s + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; e++)
+#pragma unroll
+        for (int nb = 0; nb < D / 32; nb++)
+          acc[nb] = mfma16x16x4(a[e], t[(16 * s + 4 * g + e) * (D + 4) + f0 + 16 * nb + n],
+                                acc[nb]);
+    }
+  } else {
+    for (int x = 0; x < kRows; x++)
+#pragma unroll
+      for (int r = 0; r < 4; r++)
+        if (keep(4 * g + r, x))
+#pragma unroll
+          for (int nb = 0; nb < D / 32; nb++)
+            acc[nb][r] += w[(4 * g + r) * kScoreLd + x] * t[x * (D + 4) + f0 + 16 * nb + n];
+  }
+}
+
+// The (sequence, tile) pairs a workgroup visits: rows r0 .. r0 + 31 (global
+// tokens), tiles of 32 of the other side.  All values are uniform.
+struct Walk {
+  int seq, seq_end;        // sequence index; B
+  int64_t o, r0;           // first token of the sequence; of the rows
+  int L, n_h;              // its length and history tokens
+  int ra, rb;              // rows of this sequence: indices ra .. rb
+  int x0, xend;            // current tile's first index, end of the tiles
+  bool rows_are_keys;
+
+  __device__ __forceinline__ void enter(const JaggedArgs& ja) {
+    for (;; seq++) {
+      if (seq >= seq_end) return;
+      o = ja.seq_offsets[seq];
+      if (o > r0 + kRows - 1) {
+        seq = seq_end;
+        return;
+      }
+      L = (int)(ja.seq_offsets[seq + 1] - o);
+      if (L <= 0) continue;
+      n_h = L - (ja.num_targets ? (int)ja.num_targets[seq] : 0);
+      ra = (int)max(r0 - o, (int64_t)0);
+      rb = (int)min(r0 + kRows - 1 - o, (int64_t)L - 1);
+      if (rb < ra) continue;
+      if (rows_are_keys) {
+        x0 = ra;
+        xend = ra >= n_h ? rb + 1 : L;  // a candidate key is seen by itself only
+      } else {
+        x0 = 0;
+        xend = rb + 1;
+        skip();
+      }
+      return;
+    }
+  }
+  // Key tiles made only of candidates before every row: nothing is kept.
+  __device__ __forceinline__ void skip() {
+    if (!rows_are_keys && x0 >= n_h && x0 + kRows - 1 < ra) x0 = max(x0, ra & ~(kRows - 1));
+  }
+  __device__ __forceinline__ void start(const JaggedArgs& ja, int64_t first_row, bool keys) {
+    rows_are_keys = keys;
+    r0 = first_row;
+    seq_end = ja.num_seqs;
+    seq = find_seq(ja, first_row);
+    enter(ja);
+  }
+  __device__ __forceinline__ bool done() const { return seq >= seq_end; }
+  __device__ __forceinline__ void next(const JaggedArgs& ja) {
+    x0 += kRows;
+    skip();
+    if (x0 >= xend) {
+      seq++;
+      enter(ja);
+    }
+  }
+  // Index of rab_pos that entry 0 of the tile's 64-entry window holds:
+  // p(j) - p(i) spans at most 63 values from p(first key) - p(last row).
+  __device__ __forceinline__ int window_base(int N) const {
+    const int j = rows_are_keys ? ra : x0, i = rows_are_keys ? x0 + kRows - 1 : rb;
+    return (N - 1) + bias_pos(j, n_h) - bias_pos(i, n_h);
+  }
+};
+
+// What a tile brings besides its operand rows, one element per thread.
+struct SideRegs {
+  int64_t t;   // threads 0..31: timestamp of a tile row
+  float win;   // threads 64..127: rab_pos window entry
+  __device__ __forceinline__ void load(const JaggedArgs& ja, const Walk& w, int tid) {
+    if (tid < kRows) {
+      const int x = min(w.x0 + tid, w.L - 1);
+      t = ja.timestamps[w.o + x];
+    } else if (tid >= 64 && tid < 128) {
+      const int idx = w.window_base(ja.max_seq_len) + tid - 64;
+      win = ja.rab_pos[min(max(idx, 0), 2 * ja.max_seq_len - 2)];
+    }
+  }
+  __device__ __forceinline__ void store(int64_t* st, float* sw, int tid) const {
+    if (tid < kRows)
+      st[tid] = t;
+    else if (tid >= 64 && tid < 128)
+      sw[tid - 64] = win;
+  }
+};
+
+template <int DQK, int DV>
+struct FwdLds {
+  __align__(16) float q[kRows * (DQK + 4)];
+  __align__(16) float k[kRows * (DQK + 4)];
+  __align__(16) float v[2][kRows * (DV + 4)];
+  __align__(16) float p[kRows * kScoreLd];
+  int64_t t[kRows];
+  float win[64];
+  float tab[256];
+  int bad;
+};
+
+template <int DQK, int DV>
+__global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensors t,
+                                                           float* __restrict__ out) {
+  __shared__ FwdLds<DQK, DV> sm;
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave >> 1, wc = wave & 1;
+  const int64_t r0 = (int64_t)blockIdx.x * kRows, T = ja.total_tokens;
+  const int head = blockIdx.y, H = ja.num_heads, N = ja.max_seq_len;
+  const float* kg = (const float*)t.k + head * DQK;
+  const float* vg = (const float*)t.v + head * DV;
+  Walk w;
+  w.start(ja, r0, false);
+  TileRegs<DQK> kr;
+  TileRegs<DV> vr;
+  SideRegs sr;
+  auto load = [&](const Walk& x) {
+    kr.load(kg + x.o * t.k_stride, t.k_stride, x.x0, x.L, tid);
+    vr.load(vg + x.o * t.v_stride, t.v_stride, x.x0, x.L, tid);
+    sr.load(ja, x, tid);
+  };
+  if (!w.done()) load(w);
+  {
+    TileRegs<DQK> qr;
+    int ignored;
+    qr.load((const float*)t.q + head * DQK + r0 * t.q_stride, t.q_stride, 0,
+            (int)min((int64_t)kRows, T - r0), tid);
+    qr.store(sm.q, tid, &ignored);
+  }
+  if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
+  if (tid == 0) sm.bad = 0;
+  __syncthreads();
+  const int64_t my_r = r0 + 16 * wr + n;
+  const int64_t ti = ja.timestamps[min(my_r, T - 1)];
+  f32x4 acc[DV / 32];
+#pragma unroll
+  for (int nb = 0; nb < DV / 32; nb++) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  // Per tile: K, V (two buffers: the slower waves may still read the last
+  // one), timestamps and window to LDS; scores; their weights to LDS; O.
+  for (int par = 0; !w.done(); par ^= 1) {
+    const Walk cur = w;
+    kr.store(sm.k, tid, &sm.bad);
+    vr.store(sm.v[par], tid, &sm.bad);
+    sr.store(sm.t, sm.win, tid);
+    __syncthreads();
+    w.next(ja);
+    if (!w.done()) load(w);
+    const f32x4 s = dot_tile<DQK>(sm.k + 16 * wc * (DQK + 4), sm.q + 16 * wr * (DQK + 4), lane,
+                                  f32x4{0.0f, 0.0f, 0.0f, 0.0f});
+    const int i = (int)(my_r - cur.o);
+    const int wbase = (N - 1) - bias_pos(i, cur.n_h) - cur.window_base(N);
+    const bool row_ok = i >= 0 && i < cur.L;
+    f32x4 p;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int x = 16 * wc + 4 * g + r, j = cur.x0 + x;
+      float pv = 0.0f;
+      if (row_ok && pair_valid(i, j, cur.n_h)) {
+        const float b = sm.win[wbase + bias_pos(j, cur.n_h)] +
+                        sm.tab[time_bucket64(ti - sm.t[x], ja.num_buckets)];
+        const float sc = s[r] + b;
+        pv = sc * sigmoid_fast(sc);
+      }
+      p[r] = pv;
+    }
+    *reinterpret_cast<f32x4*>(sm.p + (16 * wr + n) * kScoreLd + 16 * wc + 4 * g) = p;
+    __syncthreads();
+    outer_tile<DV>(sm.p + 16 * wr * kScoreLd, sm.v[par], wc * (DV / 2), lane, sm.bad != 0,
+                   [&](int row, int x) {
+                     const int ii = (int)(r0 + 16 * wr + row - cur.o);
+                     return ii >= 0 && ii < cur.L && pair_valid(ii, cur.x0 + x, cur.n_h);
+                   },
+                   acc);
+  }
+  const float invN = 1.0f / (float)N;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int64_t row = r0 + 16 * wr + 4 * g + r;
+    if (row < T)
+#pragma unroll
+      for (int nb = 0; nb < DV / 32; nb++)
+        out[(row * H + head) * DV + wc * (DV / 2) + 16 * nb + n] = acc[nb][r] * invN;
+  }
 }
 
 template <int DQK, int DV>
-__global__ __launch_bounds__(64) void bwd_dkv_f32_kernel(JaggedArgs ja, Tensors t, const float* dO,
-                                                         float* dk, float* dv) {
-  const int64_t r = (int64_t)blockIdx.x * 64 + threadIdx.x;
-  if (r >= ja.total_tokens) return;
-  const int head = blockIdx.y, H = ja.num_heads;
-  const Row w = locate(ja, r);
-  const int j = w.idx;
-  const float* kg = (const float*)t.k + r * t.k_stride + head * DQK;
-  const float* vg = (const float*)t.v + r * t.v_stride + head * DV;
-  float k[DQK], v[DV], ak[DQK], av[DV];
-  for (int c = 0; c < DQK; c++) {
-    k[c] = kg[c];
-    ak[c] = 0.0f;
+struct BwdLds {
+  // Rows of the workgroup and of the tile: (q, dO) against (k, v).  Tiles
+  // that the second contraction reads have two buffers.
+  __align__(16) float own_qk[kRows * (DQK + 4)];
+  __align__(16) float own_v[kRows * (DV + 4)];
+  __align__(16) float tile_qk[2][kRows * (DQK + 4)];
+  __align__(16) float tile_v[2][kRows * (DV + 4)];
+  __align__(16) float p[kRows * kScoreLd];
+  __align__(16) float ds[kRows * kScoreLd];
+  int64_t t[kRows];
+  float win[64];
+  float tab[256];
+  double time_acc[256];
+  int bad;
+};
+
+// Weight SiLU(s) and dS = dP SiLU'(s) of one pair (0, 0 if masked).
+__device__ __forceinline__ void pair_grad(float s, float dp, float* p, float* ds) {
+  const float sg = sigmoid_fast(s);
+  *p = s * sg;
+  *ds = dp * (sg + *p * (1.0f - sg));
+}
+
+// Kind (a): dQ and the bias gradients of 32 query rows.
+template <int DQK, int DV>
+__device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& ja,
+                                         const Tensors& t, const float* __restrict__ dO,
+                                         float* __restrict__ dq, double* __restrict__ pos_acc,
+                                         double* __restrict__ time_acc, int64_t r0, int head) {
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave >> 1, wc = wave & 1;
+  const int64_t T = ja.total_tokens;
+  const int H = ja.num_heads, N = ja.max_seq_len;
+  const float* kg = (const float*)t.k + head * DQK;
+  const float* vg = (const float*)t.v + head * DV;
+  Walk w;
+  w.start(ja, r0, false);
+  TileRegs<DQK> kr;
+  TileRegs<DV> vr;
+  SideRegs sr;
+  auto load = [&](const Walk& x) {
+    kr.load(kg + x.o * t.k_stride, t.k_stride, x.x0, x.L, tid);
+    vr.load(vg + x.o * t.v_stride, t.v_stride, x.x0, x.L, tid);
+    sr.load(ja, x, tid);
+  };
+  if (!w.done()) load(w);
+  {
+    const int rows = (int)min((int64_t)kRows, T - r0);
+    TileRegs<DQK> qr;
+    TileRegs<DV> gr;
+    int ignored;
+    qr.load((const float*)t.q + head * DQK + r0 * t.q_stride, t.q_stride, 0, rows, tid);
+    gr.load(dO + (r0 * H + head) * DV, (int64_t)H * DV, 0, rows, tid);
+    qr.store(sm.own_qk, tid, &ignored);
+    gr.store(sm.own_v, tid, &ignored);
   }
-  for (int c = 0; c < DV; c++) {
-    v[c] = vg[c];
-    av[c] = 0.0f;
+  if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
+  sm.time_acc[tid] = 0.0;
+  if (tid == 0) sm.bad = 0;
+  __syncthreads();
+  const int64_t my_r = r0 + 16 * wr + n;
+  const int64_t ti = ja.timestamps[min(my_r, T - 1)];
+  f32x4 acc[DQK / 32];
+#pragma unroll
+  for (int nb = 0; nb < DQK / 32; nb++) acc[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  int run_b = -1;
+  double run = 0.0;  // time-table sum of the thread's current bucket
+  // Diagonals (wave 3): lane l % 32 = d owns offset i - j = (ra - x0) + d of
+  // each tile, complete when the tile's d and the tile before's d - 32 are
+  // added; the halves of the wave take 16 rows each.
+  double carry = 0.0;
+  const int dg = lane & 31;
+
+  for (int par = 0; !w.done(); par ^= 1) {
+    const Walk cur = w;
+    kr.store(sm.tile_qk[par], tid, &sm.bad);
+    vr.store(sm.tile_v[0], tid, &sm.bad);
+    sr.store(sm.t, sm.win, tid);
+    __syncthreads();
+    w.next(ja);
+    if (!w.done()) load(w);
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const f32x4 s = dot_tile<DQK>(sm.tile_qk[par] + 16 * wc * (DQK + 4),
+                                  sm.own_qk + 16 * wr * (DQK + 4), lane, zero);
+    const f32x4 dp = dot_tile<DV>(sm.tile_v[0] + 16 * wc * (DV + 4),
+                                  sm.own_v + 16 * wr * (DV + 4), lane, zero);
+    const int i = (int)(my_r - cur.o);
+    const int wbase = (N - 1) - bias_pos(i, cur.n_h) - cur.window_base(N);
+    const bool row_ok = i >= 0 && i < cur.L;
+    f32x4 dsv;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int x = 16 * wc + 4 * g + r, j = cur.x0 + x;
+      float ds = 0.0f;
+      if (row_ok && pair_valid(i, j, cur.n_h)) {
+        const int b = time_bucket64(ti - sm.t[x], ja.num_buckets);
+        float p;
+        pair_grad(s[r] + (sm.win[wbase + bias_pos(j, cur.n_h)] + sm.tab[b]), dp[r], &p, &ds);
+        if (b != run_b) {
+          if (run_b >= 0) unsafeAtomicAdd(&sm.time_acc[run_b], run);
+          run_b = b;
+          run = 0.0;
+        }
+        run += (double)ds;
+      }
+      dsv[r] = ds;
+    }
+    *reinterpret_cast<f32x4*>(sm.ds + (16 * wr + n) * kScoreLd + 16 * wc + 4 * g) = dsv;
+    __syncthreads();
+    outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane,
+                    sm.bad != 0,
+                    [&](int row, int x) {
+                      const int ii = (int)(r0 + 16 * wr + row - cur.o);
+                      return ii >= 0 && ii < cur.L && pair_valid(ii, cur.x0 + x, cur.n_h);
+                    },
+                    acc);
+    // Position table.  Tile row a (0..31) is row index ra' + a, ra' = r0 - o
+    // (rows before the sequence hold zeros); only history rows and keys at
+    // distinct positions enter the diagonals.
+    const int base = (int)(r0 - cur.o);  // may be negative
+    const int hist = min(max(cur.n_h - base, 0), kRows);  // rows a < hist are history
+    if (wave == 3) {
+      double now = 0.0, before = 0.0;
+      for (int a = 16 * (lane >> 5); a < min(16 * (lane >> 5) + 16, hist); a++) {
+        // offset (base + a) - (x0 + x) = (base - x0) + d, d = dg or dg - 32
+        const int x = a - dg;
+        if (x >= 0)
+          now += (double)sm.ds[a * kScoreLd + x];
+        else
+          before += (double)sm.ds[a * kScoreLd + x + 32];
+      }
+      now += __shfl_xor(now, 32, 64);
+      before += __shfl_xor(before, 32, 64);
+      const double sum = now + carry;
+      const int off = base - cur.x0 + dg;  // i - j
+      if (lane < 32 && sum != 0.0 && off >= 0 && off < N)
+        unsafeAtomicAdd(&pos_acc[(N - 1) - off], sum);
+      // (sum may be NaN: it compares unequal to 0 and is added)
+      carry = before;
+      // The walk's last tile of this sequence: what was carried is complete.
+      if (w.done() || w.seq != cur.seq || w.x0 != cur.x0 + kRows) {
+        const int last = off - 32;
+        if (lane < 32 && carry != 0.0 && last >= 0 && last < N)
+          unsafeAtomicAdd(&pos_acc[(N - 1) - last], carry);
+        carry = 0.0;
+      }
+    } else if (wave == 2 && hist < kRows && cur.rb >= cur.n_h) {
+      // Candidate rows: key x at offset n_h - p(x).
+      double sum = 0.0;
+      for (int a = max(hist, 0) + (lane >> 5); a < kRows; a += 2)
+        sum += (double)sm.ds[a * kScoreLd + dg];
+      sum += __shfl_xor(sum, 32, 64);
+      const int off = cur.n_h - bias_pos(cur.x0 + dg, cur.n_h);
+      if (lane < 32 && sum != 0.0) unsafeAtomicAdd(&pos_acc[(N - 1) - off], sum);
+    }
   }
-  const int64_t tj = ja.timestamps[r];
-  const int i_end = j >= w.n_h ? j + 1 : w.L;  // a candidate key is seen by itself only
-  for (int i = j; i < i_end; i++) {
-    if (!pair_valid(i, j, w.n_h)) continue;
-    const float* qi = (const float*)t.q + (w.o + i) * t.q_stride + head * DQK;
-    const float* gi = dO + ((w.o + i) * H + head) * DV;
-    float s = bias_of(ja, w, i, j, ja.timestamps[w.o + i], tj);
-    for (int c = 0; c < DQK; c++) s += qi[c] * k[c];
-    float dp = 0.0f;
-    for (int c = 0; c < DV; c++) dp += gi[c] * v[c];
-    const float sg = sigmoid_fast(s);
-    const float p = s * sg;
-    const float ds = dp * (sg + p * (1.0f - sg));
-    for (int c = 0; c < DQK; c++) ak[c] += ds * qi[c];
-    for (int c = 0; c < DV; c++) av[c] += p * gi[c];
+  if (run_b >= 0) unsafeAtomicAdd(&sm.time_acc[run_b], run);
+  const float invN = 1.0f / (float)N;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int64_t row = r0 + 16 * wr + 4 * g + r;
+    if (row < T)
+#pragma unroll
+      for (int nb = 0; nb < DQK / 32; nb++)
+        dq[(row * H + head) * DQK + wc * (DQK / 2) + 16 * nb + n] = acc[nb][r] * invN;
   }
-  const float invN = 1.0f / (float)ja.max_seq_len;
-  float* ok = dk + (r * H + head) * DQK;
-  float* ov = dv + (r * H + head) * DV;
-  for (int c = 0; c < DQK; c++) ok[c] = ak[c] * invN;
-  for (int c = 0; c < DV; c++) ov[c] = av[c] * invN;
+  __syncthreads();
+  const double tsum = sm.time_acc[tid];
+  if (tsum != 0.0) unsafeAtomicAdd(&time_acc[tid], tsum);
+}
+
+// Kind (b): dK and dV of 32 key rows.
+template <int DQK, int DV>
+__device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& ja,
+                                         const Tensors& t, const float* __restrict__ dO,
+                                         float* __restrict__ dk, float* __restrict__ dv,
+                                         int64_t r0, int head) {
+  const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), wr = wave >> 1, wc = wave & 1;
+  const int64_t T = ja.total_tokens;
+  const int H = ja.num_heads, N = ja.max_seq_len;
+  const float* qg = (const float*)t.q + head * DQK;
+  const float* gg = dO + head * DV;
+  const int64_t g_stride = (int64_t)H * DV;
+  Walk w;
+  w.start(ja, r0, true);
+  TileRegs<DQK> qr;
+  TileRegs<DV> gr;
+  SideRegs sr;
+  auto load = [&](const Walk& x) {
+    qr.load(qg + x.o * t.q_stride, t.q_stride, x.x0, x.L, tid);
+    gr.load(gg + x.o * g_stride, g_stride, x.x0, x.L, tid);
+    sr.load(ja, x, tid);
+  };
+  if (!w.done()) load(w);
+  {
+    const int rows = (int)min((int64_t)kRows, T - r0);
+    TileRegs<DQK> kr;
+    TileRegs<DV> vr;
+    int ignored;
+    kr.load((const float*)t.k + head * DQK + r0 * t.k_stride, t.k_stride, 0, rows, tid);
+    vr.load((const float*)t.v + head * DV + r0 * t.v_stride, t.v_stride, 0, rows, tid);
+    kr.store(sm.own_qk, tid, &ignored);
+    vr.store(sm.own_v, tid, &ignored);
+  }
+  if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
+  if (tid == 0) sm.bad = 0;
+  __syncthreads();
+  const int64_t my_r = r0 + 16 * wr + n;  // the lane's key
+  const int64_t tj = ja.timestamps[min(my_r, T - 1)];
+  f32x4 ak[DQK / 32], av[DV / 32];
+#pragma unroll
+  for (int nb = 0; nb < DQK / 32; nb++) ak[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int nb = 0; nb < DV / 32; nb++) av[nb] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+
+  for (int par = 0; !w.done(); par ^= 1) {
+    const Walk cur = w;
+    qr.store(sm.tile_qk[par], tid, &sm.bad);
+    gr.store(sm.tile_v[par], tid, &sm.bad);
+    sr.store(sm.t, sm.win, tid);
+    __syncthreads();
+    w.next(ja);
+    if (!w.done()) load(w);
+    const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
+    const f32x4 s = dot_tile<DQK>(sm.tile_qk[par] + 16 * wc * (DQK + 4),
+                                  sm.own_qk + 16 * wr * (DQK + 4), lane, zero);
+    const f32x4 dp = dot_tile<DV>(sm.tile_v[par] + 16 * wc * (DV + 4),
+                                  sm.own_v + 16 * wr * (DV + 4), lane, zero);
+    const int j = (int)(my_r - cur.o);
+    const int wbase = (N - 1) + bias_pos(j, cur.n_h) - cur.window_base(N);
+    const bool key_ok = j >= 0 && j < cur.L;
+    f32x4 pv, dsv;
+#pragma unroll
+    for (int r = 0; r < 4; r++) {
+      const int x = 16 * wc + 4 * g + r, i = cur.x0 + x;
+      float p = 0.0f, ds = 0.0f;
+      if (key_ok && i < cur.L && pair_valid(i, j, cur.n_h)) {
+        const int b = time_bucket64(sm.t[x] - tj, ja.num_buckets);
+        pair_grad(s[r] + (sm.win[wbase - bias_pos(i, cur.n_h)] + sm.tab[b]), dp[r], &p, &ds);
+      }
+      pv[r] = p;
+      dsv[r] = ds;
+    }
+    const int so = (16 * wr + n) * kScoreLd + 16 * wc + 4 * g;  // [key][row]
+    *reinterpret_cast<f32x4*>(sm.p + so) = pv;
+    *reinterpret_cast<f32x4*>(sm.ds + so) = dsv;
+    __syncthreads();
+    const bool plain = sm.bad != 0;
+    auto keep = [&](int row, int x) {
+      const int jj = (int)(r0 + 16 * wr + row - cur.o), i = cur.x0 + x;
+      return jj >= 0 && i < cur.L && pair_valid(i, jj, cur.n_h);
+    };
+    outer_tile<DV>(sm.p + 16 * wr * kScoreLd, sm.tile_v[par], wc * (DV / 2), lane, plain, keep,
+                   av);
+    outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane, plain,
+                    keep, ak);
+  }
+  const float invN = 1.0f / (float)N;
+#pragma unroll
+  for (int r = 0; r < 4; r++) {
+    const int64_t row = r0 + 16 * wr + 4 * g + r;
+    if (row < T) {
+#pragma unroll
+      for (int nb = 0; nb < DQK / 32; nb++)
+        dk[(row * H + head) * DQK + wc * (DQK / 2) + 16 * nb + n] = ak[nb][r] * invN;
+#pragma unroll
+      for (int nb = 0; nb < DV / 32; nb++)
+        dv[(row * H + head) * DV + wc * (DV / 2) + 16 * nb + n] = av[nb][r] * invN;
+    }
+  }
 }
 
 template <int DQK, int DV>
-hipError_t fwd_case(const JaggedArgs& ja, const Tensors& t, void* out, hipStream_t s) {
-  dim3 grid((unsigned)((ja.total_tokens + 63) / 64), (unsigned)ja.num_heads);
-  hipLaunchKernelGGL((fwd_f32_kernel<DQK, DV>), grid, dim3(64), 0, s, ja, t, (float*)out);
-  return hipGetLastError();
+__global__ __launch_bounds__(kThreads) void bwd_f32_kernel(JaggedArgs ja, Tensors t,
+                                                           const float* dO, float* dq, float* dk,
+                                                           float* dv, double* pos_acc,
+                                                           double* time_acc) {
+  __shared__ BwdLds<DQK, DV> sm;
+  const int64_t r0 = (int64_t)blockIdx.x * kRows;
+  if (blockIdx.z == 0)
+    bwd_rows<DQK, DV>(sm, ja, t, dO, dq, pos_acc, time_acc, r0, blockIdx.y);
+  else
+    bwd_keys<DQK, DV>(sm, ja, t, dO, dk, dv, r0, blockIdx.y);
 }
 
-__global__ __launch_bounds__(256) void f64_to_f32_kernel(const double* in, float* out, int64_t n,
-                                                        double scale) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
-    out[i] = (float)(in[i] * scale);
-}
-
-template <int DQK, int DV>
-hipError_t bwd_case(const JaggedArgs& ja, const Tensors& t, const void* d_out, void* dq, void* dk,
-                    void* dv, double* drp, double* drt, hipStream_t s) {
-  dim3 grid((unsigned)((ja.total_tokens + 63) / 64), (unsigned)ja.num_heads);
-  hipLaunchKernelGGL((bwd_dq_f32_kernel<DQK, DV>), grid, dim3(64), 0, s, ja, t,
-                     (const float*)d_out, (float*)dq, drp, drt);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL((bwd_dkv_f32_kernel<DQK, DV>), grid, dim3(64), 0, s, ja, t,
-                     (const float*)d_out, (float*)dk, (float*)dv);
-  return hipGetLastError();
+__global__ __launch_bounds__(256) void f64_to_f32_kernel(const double* in, float* a, int64_t na,
+                                                         float* b, int64_t nb, double scale) {
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < na + nb;
+       i += (int64_t)gridDim.x * 256) {
+    const float v = (float)(in[i] * scale);
+    if (i < na)
+      a[i] = v;
+    else
+      b[i - na] = v;
+  }
 }
 
 }  // namespace
@@ -203,18 +632,24 @@ hipError_t bwd_case(const JaggedArgs& ja, const Tensors& t, const void* d_out, v
 hipError_t launch_attn_fwd_f32(const JaggedArgs& ja, const Tensors& t, int dqk, int dv, void* out,
                                hipStream_t s) {
   if (ja.total_tokens <= 0) return hipSuccess;
-#define CALL(A, B) return fwd_case<A, B>(ja, t, out, s);
+  const dim3 grid((unsigned)((ja.total_tokens + kRows - 1) / kRows), (unsigned)ja.num_heads);
+#define CALL(A, B)                                                                           \
+  {                                                                                          \
+    hipLaunchKernelGGL((fwd_f32_kernel<A, B>), grid, dim3(kThreads), 0, s, ja, t,             \
+                       (float*)out);                                                         \
+    return hipGetLastError();                                                                \
+  }
   HSTU_F32_DISPATCH(CALL)
 #undef CALL
   return hipErrorInvalidValue;
 }
 
-hipError_t launch_f64_to_f32_scaled(const double* in, float* out, int64_t n, double scale,
-                                    hipStream_t s) {
-  if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 255) / 256;
+hipError_t launch_f64_to_f32_scaled(const double* in, float* a, int64_t na, float* b, int64_t nb,
+                                    double scale, hipStream_t s) {
+  if (na + nb <= 0) return hipSuccess;
+  const int64_t blocks = (na + nb + 255) / 256;
   hipLaunchKernelGGL(f64_to_f32_kernel, dim3((unsigned)(blocks < 1024 ? blocks : 1024)), dim3(256),
-                     0, s, in, out, n, scale);
+                     0, s, in, a, na, b, nb, scale);
   return hipGetLastError();
 }
 
@@ -222,8 +657,14 @@ hipError_t launch_attn_bwd_f32(const JaggedArgs& ja, const Tensors& t, int dqk, 
                                const void* d_out, void* dq, void* dk, void* dv_out,
                                double* rab_pos_acc, double* rab_time_acc, hipStream_t s) {
   if (ja.total_tokens <= 0) return hipSuccess;
-#define CALL(A, B) \
-  return bwd_case<A, B>(ja, t, d_out, dq, dk, dv_out, rab_pos_acc, rab_time_acc, s);
+  const dim3 grid((unsigned)((ja.total_tokens + kRows - 1) / kRows), (unsigned)ja.num_heads, 2);
+#define CALL(A, B)                                                                            \
+  {                                                                                           \
+    hipLaunchKernelGGL((bwd_f32_kernel<A, B>), grid, dim3(kThreads), 0, s, ja, t,              \
+                       (const float*)d_out, (float*)dq, (float*)dk, (float*)dv_out,           \
+                       rab_pos_acc, rab_time_acc);                                            \
+    return hipGetLastError();                                                                 \
+  }
   HSTU_F32_DISPATCH(CALL)
 #undef CALL
   return hipErrorInvalidValue;

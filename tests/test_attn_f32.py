@@ -1,0 +1,76 @@
+"""The fp32 attention kernels at the edges of their 32-row blocks and 32-wide
+tiles: lengths around multiples of 32, several sequences and empty ones
+inside a block, candidates whose history ends inside a tile or a block,
+candidate tiles that are skipped, every head size, more than 64 sequences,
+and infinities that masked pairs must not spread."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2402_17152_amd import inputs
+from tests import gpu_util as gu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def hs():
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2402_17152_amd import hstu
+    return hstu
+
+
+CASES = {
+    "edges": dict(lengths=(31, 32, 33, 63, 64, 65, 1, 97)),
+    "packed": dict(lengths=(3, 0, 1, 7, 0, 5, 2, 40, 0, 11, 0), num_targets=(1, 0, 1, 0, 0, 5, 1,
+                                                                         13, 0, 4, 0)),
+    "candidates": dict(lengths=(130, 96, 64, 70), num_targets=(70, 64, 33, 69)),
+    "all_candidates": dict(lengths=(40, 33), num_targets=(40, 33)),
+    "one_long": dict(lengths=(300,), num_targets=(1,)),
+    "many": dict(lengths=tuple(1 + (7 * i) % 13 for i in range(150))),
+}
+
+
+@pytest.mark.parametrize("dqk,dv", [(32, 32), (64, 128), (128, 64)])
+@pytest.mark.parametrize("case", sorted(CASES))
+def test_f32_tiles(hs, oracle_mod, case, dqk, dv):
+    c = CASES[case]
+    batch = inputs.make_batch(2, seed=40 + len(case), num_heads=2, d_qk=dqk, d_v=dv,
+                              max_seq_len=max(c["lengths"]), dtype="f32", **c)
+    d = gu.dev_inputs(batch)
+    gu.assert_close("out", gu.to_f64(gu.gpu_fwd(hs, d, batch)), gu.oracle_fwd(oracle_mod, batch),
+                    1e-5, "f32")
+    for name, g, r in zip(("dq", "dk", "dv", "d_rab_pos", "d_rab_time"), gu.gpu_bwd(hs, d, batch),
+                          gu.oracle_bwd(oracle_mod, batch)):
+        gu.assert_close(name, gu.to_f64(g), r, 1e-5, "f32")
+
+
+@pytest.mark.parametrize("name,value", [("v", np.inf), ("k", np.nan), ("q", np.inf),
+                                        ("do", np.nan)])
+def test_f32_masked_pairs_do_not_spread_infinities(hs, name, value):
+    """One token's q, k, v or dO not finite: outputs that no kept pair with
+    that token reaches are those of the finite batch (up to the order of the
+    sums, 1e-5 of the largest)."""
+    lengths, tok = (20, 50, 9), 20 + 17  # token 17 of the second sequence
+    batch = inputs.make_batch(2, seed=9, lengths=lengths, num_heads=2, d_qk=32, d_v=32,
+                              max_seq_len=50, dtype="f32")
+    d = gu.dev_inputs(batch)
+    ref = [gu.gpu_fwd(hs, d, batch), *gu.gpu_bwd(hs, d, batch)[:3]]
+    d[name] = d[name].clone()
+    d[name][tok, 1] = value
+    got = [gu.gpu_fwd(hs, d, batch), *gu.gpu_bwd(hs, d, batch)[:3]]
+    torch.cuda.synchronize()
+    rows = torch.arange(sum(lengths), device="cuda")
+    later = (rows >= tok) & (rows < 70)     # rows that see the token as a key
+    earlier = (rows >= 20) & (rows <= tok)  # keys that the token's row sees
+    none = torch.zeros_like(later)
+    only = rows == tok
+    # Which rows of out, dq, dk, dv the token's value may reach.
+    reach = {"v": (later, later, only, none), "k": (later, later, only, only),
+             "q": (only, only, earlier, earlier), "do": (none, only, earlier, earlier)}[name]
+    for a, b, r in zip(ref, got, reach):
+        assert torch.equal(a[:, 0], b[:, 0])
+        assert torch.isfinite(b[~r, 1]).all()
+        assert (a[~r, 1] - b[~r, 1]).abs().max() <= 1e-5 * a.abs().max()
+        if r.any():
+            assert not torch.isfinite(b[r, 1]).all()
