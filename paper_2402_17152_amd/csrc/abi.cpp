@@ -554,17 +554,11 @@ hstu_status_t hstu_stochastic_length(int32_t num_seqs, const int64_t* seq_offset
       return fail(HSTU_ERR_WORKSPACE, "workspace too small: %zu < %zu bytes", ws_bytes, need);
     if ((uintptr_t)ws % kAlign)
       return fail(HSTU_ERR_WORKSPACE, "workspace must be 256-byte aligned");
-    char* w = (char*)ws;
-    int64_t* new_len = (int64_t*)w;
-    int32_t* whole = (int32_t*)(w + align_up(sizeof(int64_t) * (size_t)num_seqs));
     TimedScope ts("stochastic_length", s);
-    HSTU_HIP(launch_sl_lengths(num_seqs, seq_offsets, num_targets, subseq_len, keep_numerator,
-                               u_keep, new_len, whole, s),
-             "sl lengths launch");
-    HSTU_HIP(launch_complete_cumsum(num_seqs, new_len, new_offsets, 0, s), "sl offsets launch");
-    HSTU_HIP(launch_sl_select(num_seqs, seq_offsets, timestamps, num_targets, subseq_len,
-                              selection, e_rand, whole, new_offsets, gather, s),
-             "sl select launch");
+    HSTU_HIP(launch_stochastic_length(num_seqs, seq_offsets, timestamps, num_targets, subseq_len,
+                                      keep_numerator, selection, u_keep, e_rand, (int64_t*)ws,
+                                      new_offsets, gather, s),
+             "stochastic length launch");
     return ok();
   } catch (...) {
     return fail(HSTU_ERR_INVALID_ARGUMENT, "internal error");

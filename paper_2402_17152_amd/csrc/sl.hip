@@ -14,31 +14,46 @@
 // history, which orders the items as the exponential-race keys e_i / w_i
 // of weighted sampling without replacement with w_i = 1 - f_i / F.  Keys
 // are non-negative, so their bit patterns order like their values, and
-// one workgroup per sequence finds the L-th smallest by an 8-pass radix
-// select over the 64-bit patterns (LDS histograms of 8-bit digits), then
-// writes the chosen indices in order with block prefix sums.
+// one workgroup per sequence finds the L-th smallest by a radix select over
+// the 64-bit patterns (LDS histograms of 8-bit digits, at most 8 passes:
+// it ends once every key sharing the known digits is chosen, for random
+// keys after 3 or 4), then writes the chosen indices in order.
+//
+// Bound by the latency of the longest sequence's passes.  Keys of up to
+// 8192 history tokens stay in the registers of 1024 threads, and one wave
+// scans the histogram; a pass is two barriers.  (Recomputing the keys of 256
+// threads from memory in each of 8 passes, with one thread scanning the
+// bins, took 126 us on 64 sequences of up to 4096 tokens.)
 #include "kernels.h"
 
 namespace hstu {
 
 namespace {
 
-constexpr int kSlThreads = 256;
+constexpr int kSlThreads = 1024;
+constexpr int kSlWaves = kSlThreads / 64;
+constexpr int kSlHeld = 8;  // keys a thread holds
+// Up to this many sequences a select workgroup adds up the new lengths of
+// the sequences before its own by itself, four per thread, instead of two
+// launches before it (the keep decisions, their prefix sum: 9 us of 141).
+constexpr int32_t kSlFusedSeqs = 4 * kSlThreads;
+
+__device__ __forceinline__ bool keep_whole(int64_t n, int64_t t, int32_t L, double keep_num,
+                                           double u) {
+  const int64_t nh = n - t;
+  return nh <= L || u < keep_num / ((double)nh * (double)nh);
+}
 
 __global__ __launch_bounds__(256) void sl_lengths_kernel(int32_t B,
                                                          const int64_t* __restrict__ offs,
                                                          const int64_t* __restrict__ nt, int32_t L,
                                                          double keep_num,
                                                          const double* __restrict__ u_keep,
-                                                         int64_t* __restrict__ new_len,
-                                                         int32_t* __restrict__ whole) {
+                                                         int64_t* __restrict__ new_len) {
   for (int b = blockIdx.x * 256 + threadIdx.x; b < B; b += gridDim.x * 256) {
     const int64_t n = offs[b + 1] - offs[b];
     const int64_t t = nt ? nt[b] : 0;
-    const int64_t nh = n - t;
-    const bool w = nh <= L || u_keep[b] < keep_num / ((double)nh * (double)nh);
-    new_len[b] = w ? n : (int64_t)L + t;
-    whole[b] = w ? 1 : 0;
+    new_len[b] = keep_whole(n, t, L, keep_num, u_keep[b]) ? n : (int64_t)L + t;
   }
 }
 
@@ -50,172 +65,369 @@ struct SlKey {
   int64_t tmax, F;
   int mode;
   __device__ __forceinline__ uint64_t operator()(int i) const {
-    const int64_t f = tmax - ts[i];
-    if (mode == kSlGreedy) return (uint64_t)f;
+    if (mode == kSlGreedy) return (uint64_t)(tmax - ts[i]);
     const double ei = e[i] > 0.0 ? e[i] : 0.0;
-    if (mode == kSlRandom) return dbits(ei);
-    if (F == 0) return dbits(ei);
-    const int64_t den = F - f;
+    if (mode == kSlRandom || F == 0) return dbits(ei);
+    const int64_t den = F - (tmax - ts[i]);
     if (den == 0) return dbits(__builtin_inf());
     return dbits(ei / (double)den);
   }
 };
 
-// Exclusive prefix count of `flag` over the 256 threads in thread order;
-// *total receives the block's count.  Uses sc[0..3].
+__device__ __forceinline__ int lanes_below(uint64_t m, int lane) {
+  return __popcll(m & ((1ull << lane) - 1ull));
+}
+
+// Exclusive prefix count of `flag` over the workgroup in thread order;
+// *total receives the workgroup's count.  Uses sc[0 .. kSlWaves - 1].
 __device__ __forceinline__ int block_excl_count(bool flag, int* sc, int* total) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const uint64_t m = __ballot(flag);
-  const int below = __popcll(m & ((lane ? (~0ull >> (64 - lane)) : 0ull)));
   if (lane == 0) sc[wave] = __popcll(m);
   __syncthreads();
   int before = 0, tot = 0;
 #pragma unroll
-  for (int w = 0; w < 4; w++) {
+  for (int w = 0; w < kSlWaves; w++) {
     before += w < wave ? sc[w] : 0;
     tot += sc[w];
   }
   __syncthreads();
   *total = tot;
-  return before + below;
+  return before + lanes_below(m, lane);
 }
 
+// Wave-wide reductions of 64-bit values.
+__device__ __forceinline__ int64_t wave_add(int64_t v) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+  return v;
+}
+
+// Counts the digit of every active lane: the lanes that share the first
+// active lane's digit (all of them, while the keys agree) add once.
+__device__ __forceinline__ void count_digit(int* hist, bool active, int d, int lane) {
+  const uint64_t act = __ballot(active);
+  if (!act) return;
+  const int first = __builtin_ctzll(act);
+  const int d0 = __builtin_amdgcn_readlane(d, first);
+  const uint64_t same = __ballot(active && d == d0);
+  if (lane == first) atomicAdd(&hist[d0], __popcll(same));
+  if (active && d != d0) atomicAdd(&hist[d], 1);
+}
+
+struct SlShared {
+  int hist[256];
+  int sc[kSlWaves];
+  int64_t red[2][kSlWaves];
+  int cnt[kSlHeld][kSlWaves];
+  uint64_t prefix;
+  int k, eq;
+};
+
+// Sum of v over the workgroup (`slot` of sm.red must not be in use).
+__device__ __forceinline__ int64_t block_add(SlShared& sm, int slot, int64_t v) {
+  v = wave_add(v);
+  if ((threadIdx.x & 63) == 0) sm.red[slot][threadIdx.x >> 6] = v;
+  __syncthreads();
+  int64_t s = 0;
+#pragma unroll
+  for (int w = 0; w < kSlWaves; w++) s += sm.red[slot][w];
+  return s;
+}
+
+// Exclusive prefix over the (chunk, wave) counts in sm.cnt, in place.
+__device__ __forceinline__ void scan_counts(SlShared& sm) {
+  __syncthreads();
+  if (threadIdx.x < 64) {
+    int* c = &sm.cnt[0][0] + 2 * threadIdx.x;
+    static_assert(kSlHeld * kSlWaves == 128, "two counts per lane");
+    const int a = c[0], s = a + c[1];
+    int run = s;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int x = __shfl_up(run, off, 64);
+      if ((int)threadIdx.x >= off) run += x;
+    }
+    c[0] = run - s;
+    c[1] = run - s + a;
+  }
+  __syncthreads();
+}
+
+// HELD: the history has at most kSlHeld * kSlThreads tokens, whose keys
+// stay in registers; else they are recomputed in each pass.
+template <bool HELD>
+__device__ void select_tokens(SlShared& sm, const SlKey& key, int nh, int L, int64_t o,
+                              int64_t* out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int chunks = (nh + kSlThreads - 1) / kSlThreads;
+  uint64_t held[HELD ? kSlHeld : 1];
+  if constexpr (HELD) {
+#pragma unroll
+    for (int c = 0; c < kSlHeld; c++) {
+      const int i = c * kSlThreads + tid;
+      held[c] = i < nh ? key(i) : ~0ull;
+    }
+  }
+  if (tid < 256) sm.hist[tid] = 0;
+  __syncthreads();
+
+  // Radix select: after pass p the top 8 (p + 1) bits of the L-th smallest
+  // key are known; k is its rank among the keys sharing those bits.
+  uint64_t prefix = 0, mask = 0;
+  int k = L, eq = 0;
+  for (int shift = 56; shift >= 0; shift -= 8) {
+    auto count = [&](int i, uint64_t kv) {
+      count_digit(sm.hist, i < nh && (kv & mask) == prefix, (int)(kv >> shift) & 255, lane);
+    };
+    if constexpr (HELD) {
+#pragma unroll
+      for (int c = 0; c < kSlHeld; c++)
+        if (c < chunks) count(c * kSlThreads + tid, held[c]);
+    } else {
+      for (int c = 0; c < chunks; c++) {
+        const int i = c * kSlThreads + tid;
+        count(i, i < nh ? key(i) : ~0ull);
+      }
+    }
+    __syncthreads();
+    if (wave == 0) {
+      // Lane l owns bins 4 l .. 4 l + 3; the digit is the first with k keys
+      // in it and the bins before it.
+      int h[4], sum = 0;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        h[e] = sm.hist[4 * lane + e];
+        sm.hist[4 * lane + e] = 0;
+        sum += h[e];
+      }
+      int run = sum;
+#pragma unroll
+      for (int off = 1; off < 64; off <<= 1) {
+        const int x = __shfl_up(run, off, 64);
+        if (lane >= off) run += x;
+      }
+      int before = run - sum;
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        if (before < k && before + h[e] >= k) {
+          sm.prefix = prefix | ((uint64_t)(4 * lane + e) << shift);
+          sm.k = k - before;
+          sm.eq = h[e];
+        }
+        before += h[e];
+      }
+    }
+    __syncthreads();
+    prefix = sm.prefix;
+    k = sm.k;
+    eq = sm.eq;
+    mask |= 255ull << shift;
+    if (eq == k) break;  // every key with these digits is chosen
+  }
+
+  // Of the eq tokens whose masked key equals prefix, the k with the largest
+  // indices are chosen (with every smaller key).
+  const int skip_eq = eq - k;
+  if constexpr (HELD) {
+    int rank[kSlHeld];
+    if (skip_eq > 0) {
+#pragma unroll
+      for (int c = 0; c < kSlHeld; c++) {
+        const uint64_t m = __ballot(c * kSlThreads + tid < nh && (held[c] & mask) == prefix);
+        if (lane == 0) sm.cnt[c][wave] = __popcll(m);
+        rank[c] = lanes_below(m, lane);
+      }
+      scan_counts(sm);
+#pragma unroll
+      for (int c = 0; c < kSlHeld; c++) rank[c] += sm.cnt[c][wave];
+      __syncthreads();
+    }
+    uint32_t sel = 0;
+    int pos[kSlHeld];
+#pragma unroll
+    for (int c = 0; c < kSlHeld; c++) {
+      const bool is_eq = (held[c] & mask) == prefix;
+      const bool take = c * kSlThreads + tid < nh &&
+                        (is_eq ? (skip_eq == 0 || rank[c] >= skip_eq) : held[c] < prefix);
+      const uint64_t m = __ballot(take);
+      if (lane == 0) sm.cnt[c][wave] = __popcll(m);
+      pos[c] = lanes_below(m, lane);
+      sel |= take ? 1u << c : 0u;
+    }
+    scan_counts(sm);
+#pragma unroll
+    for (int c = 0; c < kSlHeld; c++) {
+      const int x = pos[c] + sm.cnt[c][wave];
+      if ((sel >> c & 1) && x < L) out[x] = o + c * kSlThreads + tid;
+    }
+  } else {
+    int seen_eq = 0, written = 0;
+    for (int c = 0; c < chunks; c++) {
+      const int i = c * kSlThreads + tid;
+      const uint64_t kv = i < nh ? key(i) : ~0ull;
+      const bool is_eq = i < nh && (kv & mask) == prefix;
+      int tot_eq, tot_sel;
+      const int eq_before = seen_eq + block_excl_count(is_eq, sm.sc, &tot_eq);
+      const bool take = i < nh && (is_eq ? eq_before >= skip_eq : kv < prefix);
+      const int x = written + block_excl_count(take, sm.sc, &tot_sel);
+      if (take && x < L) out[x] = o + i;
+      seen_eq += tot_eq;
+      written += tot_sel;
+    }
+  }
+  __syncthreads();
+}
+
+// One workgroup per sequence.  FUSED: it also adds up the new lengths before
+// its own and writes its new offset; else new_offs holds them.
+template <bool FUSED>
 __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
     int32_t B, const int64_t* __restrict__ offs, const int64_t* __restrict__ ts,
-    const int64_t* __restrict__ nt, int32_t L, int32_t mode, const double* __restrict__ e_rand,
-    const int32_t* __restrict__ whole, const int64_t* __restrict__ new_offs,
-    int64_t* __restrict__ gather) {
-  __shared__ int hist[256];
-  __shared__ int sc[4];
-  __shared__ int64_t red[2][4];
-  __shared__ uint64_t s_prefix;
-  __shared__ int s_k, s_eq;
+    const int64_t* __restrict__ nt, int32_t L, double keep_num, int32_t mode,
+    const double* __restrict__ u_keep, const double* __restrict__ e_rand,
+    int64_t* __restrict__ new_offs, int64_t* __restrict__ gather) {
+  __shared__ SlShared sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   for (int b = blockIdx.x; b < B; b += gridDim.x) {
     const int64_t o = offs[b];
     const int n = (int)(offs[b + 1] - o);
     const int t = nt ? (int)nt[b] : 0;
     const int nh = n - t;
-    int64_t* out = gather + new_offs[b];
-    if (whole[b]) {
+    const bool whole = keep_whole(n, t, L, keep_num, u_keep[b]);
+    int64_t start;
+    if constexpr (FUSED) {
+      int64_t sum = 0;
+      for (int x = tid; x < b; x += kSlThreads) {
+        const int64_t xn = offs[x + 1] - offs[x], xt = nt ? nt[x] : 0;
+        sum += keep_whole(xn, xt, L, keep_num, u_keep[x]) ? xn : (int64_t)L + xt;
+      }
+      start = block_add(sm, 0, sum);
+      if (tid == 0) {
+        if (b == 0) new_offs[0] = 0;
+        new_offs[b + 1] = start + (whole ? n : (int64_t)L + t);
+      }
+    } else {
+      start = new_offs[b];
+    }
+    int64_t* out = gather + start;
+    if (whole) {
       for (int i = tid; i < n; i += kSlThreads) out[i] = o + i;
+      __syncthreads();
       continue;
     }
     // Candidates follow the L chosen history tokens.
     for (int c = tid; c < t; c += kSlThreads) out[L + c] = o + nh + c;
 
-    // t_max and (feature-weighted) F = sum of t_max - t_i over the history.
+    // t_max and (feature-weighted) F = sum of t_max - t_i over the history;
+    // random selection reads no timestamps.
     const int64_t* th = ts + o;
-    int64_t mx = (int64_t)(~0ull >> 1) * -1 - 1;
-    for (int i = tid; i < nh; i += kSlThreads) mx = th[i] > mx ? th[i] : mx;
+    int64_t tmax = 0, F = 0;
+    if (mode != kSlRandom) {
+      int64_t mx = (int64_t)(~0ull >> 1) * -1 - 1;
+      for (int i = tid; i < nh; i += kSlThreads) mx = th[i] > mx ? th[i] : mx;
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      const int64_t x = __shfl_xor(mx, off, 64);
-      mx = x > mx ? x : mx;
+      for (int off = 32; off > 0; off >>= 1) {
+        const int64_t x = __shfl_xor(mx, off, 64);
+        mx = x > mx ? x : mx;
+      }
+      if (lane == 0) sm.red[1][wave] = mx;
+      __syncthreads();
+      tmax = sm.red[1][0];
+#pragma unroll
+      for (int w = 1; w < kSlWaves; w++) tmax = max(tmax, sm.red[1][w]);
+      __syncthreads();
     }
-    if (lane == 0) red[0][wave] = mx;
-    __syncthreads();
-    const int64_t tmax = max(max(red[0][0], red[0][1]), max(red[0][2], red[0][3]));
-    int64_t F = 0;
     if (mode == kSlWeighted) {
       int64_t sum = 0;
       for (int i = tid; i < nh; i += kSlThreads) sum += tmax - th[i];
-#pragma unroll
-      for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-      if (lane == 0) red[1][wave] = sum;
-      __syncthreads();
-      F = red[1][0] + red[1][1] + red[1][2] + red[1][3];
+      F = block_add(sm, 1, sum);
     }
     const SlKey key{th, e_rand ? e_rand + o : nullptr, tmax, F, mode};
-
-    // Radix select: after pass p the top 8(p+1) bits of the L-th smallest
-    // key are known; k is its rank among the keys sharing those bits.
-    uint64_t prefix = 0;
-    int k = L, eq = 0;
-    for (int p = 0; p < 8; p++) {
-      const int shift = 56 - 8 * p;
-      const uint64_t hi_mask = p == 0 ? 0ull : ~((1ull << (shift + 8)) - 1ull);
-      hist[tid] = 0;
-      __syncthreads();
-      for (int i = tid; i < nh; i += kSlThreads) {
-        const uint64_t kv = key(i);
-        if ((kv & hi_mask) == prefix) atomicAdd(&hist[(kv >> shift) & 255], 1);
-      }
-      __syncthreads();
-      if (tid == 0) {
-        int before = 0, d = 0;
-        while (d < 255 && before + hist[d] < k) before += hist[d++];
-        s_prefix = prefix | ((uint64_t)d << shift);
-        s_k = k - before;
-        s_eq = hist[d];
-      }
-      __syncthreads();
-      prefix = s_prefix;
-      k = s_k;
-      eq = s_eq;
-      __syncthreads();
-    }
-    // prefix = the L-th smallest key; eq tokens carry it, of which the k
-    // with the largest indices are chosen (with every smaller key).
-    const int skip_eq = eq - k;
-    int seen_eq = 0, written = 0;
-    for (int c0 = 0; c0 < nh; c0 += kSlThreads) {
-      const int i = c0 + tid;
-      const uint64_t kv = i < nh ? key(i) : ~0ull;
-      const bool is_eq = i < nh && kv == prefix;
-      int tot_eq, tot_sel;
-      const int eq_before = seen_eq + block_excl_count(is_eq, sc, &tot_eq);
-      const bool sel = i < nh && (kv < prefix || (is_eq && eq_before >= skip_eq));
-      const int pos = written + block_excl_count(sel, sc, &tot_sel);
-      if (sel && pos < L) out[pos] = o + i;
-      seen_eq += tot_eq;
-      written += tot_sel;
-    }
-    __syncthreads();
+    if (nh <= kSlHeld * kSlThreads)
+      select_tokens<true>(sm, key, nh, L, o, out);
+    else
+      select_tokens<false>(sm, key, nh, L, o, out);
   }
 }
 
 // dst row r = src row index[r] for r < *count (count read on the device).
+// A row's words (of type W) are taken by 2^lg lanes; a workgroup takes
+// kGatherUnroll sweeps of 256 >> lg consecutive rows, so that a lane has that
+// many rows' loads in flight.  HBM-bound.
+constexpr int kGatherUnroll = 4;
+
+template <typename W>
 __global__ __launch_bounds__(256) void gather_rows_kernel(const char* __restrict__ src,
-                                                          int64_t src_stride, int64_t words,
-                                                          int wbytes,
+                                                          int64_t src_stride, int64_t words, int lg,
                                                           const int64_t* __restrict__ index,
                                                           const int64_t* __restrict__ count,
                                                           int64_t max_rows, char* __restrict__ dst,
                                                           int64_t dst_stride) {
+  constexpr int U = kGatherUnroll;
   const int64_t rows = min(*count, max_rows);
-  const int64_t total = rows * words;
-  for (int64_t x = (int64_t)blockIdx.x * 256 + threadIdx.x; x < total;
-       x += (int64_t)gridDim.x * 256) {
-    const int64_t r = x / words, w = x - r * words;
-    const char* s = src + index[r] * src_stride + w * wbytes;
-    char* d = dst + r * dst_stride + w * wbytes;
-    if (wbytes == 16)
-      *reinterpret_cast<u32x4*>(d) = *reinterpret_cast<const u32x4*>(s);
-    else
-      *reinterpret_cast<uint32_t*>(d) = *reinterpret_cast<const uint32_t*>(s);
+  const int sub = threadIdx.x & ((1 << lg) - 1);
+  const int step = 256 >> lg;
+  for (int64_t r = (int64_t)blockIdx.x * (U * step) + (threadIdx.x >> lg); r < rows;
+       r += (int64_t)gridDim.x * (U * step)) {
+    int64_t from[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int64_t x = r + u * step;
+      from[u] = x < rows ? index[x] : 0;
+    }
+    for (int64_t w = sub; w < words; w += 1 << lg) {
+      W v[U];
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (r + u * step < rows)
+          v[u] = *reinterpret_cast<const W*>(src + from[u] * src_stride + w * (int)sizeof(W));
+#pragma unroll
+      for (int u = 0; u < U; u++)
+        if (r + u * step < rows)
+          *reinterpret_cast<W*>(dst + (r + u * step) * dst_stride + w * (int)sizeof(W)) = v[u];
+    }
   }
+}
+
+template <typename W>
+hipError_t gather_case(const void* src, int64_t src_stride, int64_t row_bytes,
+                       const int64_t* index, const int64_t* count, int64_t max_rows, void* dst,
+                       int64_t dst_stride, hipStream_t s) {
+  const int64_t words = row_bytes / (int64_t)sizeof(W);
+  int lg = 0;
+  while (lg < 6 && (1 << lg) < words) lg++;
+  const int64_t per_block = kGatherUnroll * (256 >> lg);
+  int64_t blocks = (max_rows + per_block - 1) / per_block;
+  if (blocks > 65536) blocks = 65536;
+  hipLaunchKernelGGL((gather_rows_kernel<W>), dim3((unsigned)blocks), dim3(256), 0, s,
+                     (const char*)src, src_stride, words, lg, index, count, max_rows, (char*)dst,
+                     dst_stride);
+  return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_sl_lengths(int32_t B, const int64_t* offs, const int64_t* nt, int32_t L,
-                             double keep_num, const double* u_keep, int64_t* new_len,
-                             int32_t* whole, hipStream_t s) {
+hipError_t launch_stochastic_length(int32_t B, const int64_t* offs, const int64_t* ts,
+                                    const int64_t* nt, int32_t L, double keep_num, int32_t mode,
+                                    const double* u_keep, const double* e_rand, int64_t* new_len,
+                                    int64_t* new_offs, int64_t* gather, hipStream_t s) {
   if (B <= 0) return hipSuccess;
+  const dim3 grid((unsigned)(B < 65535 ? B : 65535));
+  if (B <= kSlFusedSeqs) {
+    hipLaunchKernelGGL(sl_select_kernel<true>, grid, dim3(kSlThreads), 0, s, B, offs, ts, nt, L,
+                       keep_num, mode, u_keep, e_rand, new_offs, gather);
+    return hipGetLastError();
+  }
   const int blocks = (B + 255) / 256 < 1024 ? (B + 255) / 256 : 1024;
   hipLaunchKernelGGL(sl_lengths_kernel, dim3(blocks), dim3(256), 0, s, B, offs, nt, L, keep_num,
-                     u_keep,
-                     new_len, whole);
-  return hipGetLastError();
-}
-
-hipError_t launch_sl_select(int32_t B, const int64_t* offs, const int64_t* ts, const int64_t* nt,
-                            int32_t L, int32_t mode, const double* e_rand, const int32_t* whole,
-                            const int64_t* new_offs, int64_t* gather, hipStream_t s) {
-  if (B <= 0) return hipSuccess;
-  hipLaunchKernelGGL(sl_select_kernel, dim3((unsigned)(B < 65535 ? B : 65535)), dim3(kSlThreads), 0,
-                     s, B, offs, ts, nt, L, mode, e_rand, whole, new_offs, gather);
+                     u_keep, new_len);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  e = launch_complete_cumsum(B, new_len, new_offs, 0, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(sl_select_kernel<false>, grid, dim3(kSlThreads), 0, s, B, offs, ts, nt, L,
+                     keep_num, mode, u_keep, e_rand, new_offs, gather);
   return hipGetLastError();
 }
 
@@ -223,16 +435,17 @@ hipError_t launch_gather_rows(const void* src, int64_t src_stride, int64_t row_b
                               const int64_t* index, const int64_t* count, int64_t max_rows,
                               void* dst, int64_t dst_stride, hipStream_t s) {
   if (max_rows <= 0 || row_bytes <= 0) return hipSuccess;
-  const bool v16 = row_bytes % 16 == 0 && src_stride % 16 == 0 && dst_stride % 16 == 0 &&
-                   (uintptr_t)src % 16 == 0 && (uintptr_t)dst % 16 == 0;
-  const int wb = v16 ? 16 : 4;
-  const int64_t words = row_bytes / wb;
-  const int64_t total = max_rows * words;
-  const int64_t blocks = (total + 255) / 256;
-  hipLaunchKernelGGL(gather_rows_kernel, dim3((unsigned)(blocks < 8192 ? blocks : 8192)),
-                     dim3(256), 0, s, (const char*)src, src_stride, words, wb, index, count,
-                     max_rows, (char*)dst, dst_stride);
-  return hipGetLastError();
+  // The widest word that rows, strides and pointers are all multiples of.
+  const uintptr_t all = (uintptr_t)row_bytes | (uintptr_t)src_stride | (uintptr_t)dst_stride |
+                        (uintptr_t)src | (uintptr_t)dst;
+  if (all % 16 == 0)
+    return gather_case<u32x4>(src, src_stride, row_bytes, index, count, max_rows, dst,
+                              dst_stride, s);
+  if (all % 8 == 0)
+    return gather_case<uint64_t>(src, src_stride, row_bytes, index, count, max_rows, dst,
+                                 dst_stride, s);
+  return gather_case<uint32_t>(src, src_stride, row_bytes, index, count, max_rows, dst,
+                               dst_stride, s);
 }
 
 }  // namespace hstu
