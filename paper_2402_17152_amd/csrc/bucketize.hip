@@ -2,10 +2,11 @@
 // the L x L matrix of time buckets bkt(t_i - t_j) (notation table, entry
 // rab^{p,t}) as uint8, row-major, sequences concatenated at pair_offsets.
 //
-// HBM-write bound.  A workgroup owns 48 consecutive tokens of the batch,
-// i.e. 48 rows of one sequence (or the rows of two or more sequences that
-// meet inside the block), and walks the columns in slabs of 8192 (whole
-// rows, for sequences up to that length) whose timestamps it stages in
+// HBM-write bound.  A workgroup of 8 waves owns 64 consecutive tokens of
+// the batch (16 or 32 while those fill the chip), i.e. 64 rows of one
+// sequence (or the rows of two or more sequences that meet inside the
+// block), and walks the columns in slabs of 8192 (whole rows, for sequences
+// up to that length) whose timestamps it stages in
 // LDS.  When the
 // timestamps of its rows and of the slab lie within 2^30 of the sequence's
 // first one (always, for real event times), they are rebased to 32 bits
@@ -20,6 +21,15 @@
 // (or, for half of the alignments, eight 8-byte words), and each copy
 // inserts one padding word-quad every 64 entries, so that the lanes of a
 // read (64 bytes apart) spread over the LDS banks.
+// A wave takes four rows, 16 apart, together: their segments have one
+// alignment (16 L is a multiple of 16), so one set of LDS reads and
+// addresses serves all four.  Against one row at a time with 48 rows per
+// workgroup of 4 waves: batches of 1 to 10 K tokens 10 against 16 us; 8
+// sequences of 4096-8192 tokens (312 MB) 66 against 73 us into a buffer that
+// the last-level cache holds part of, 76 us both into changing buffers,
+// where the order of the writes binds (the stores alone, without reads or
+// arithmetic, take 70 us; a plain fill 46).  More workgroups per CU only
+// spread them further: two 83 us, five with 4096-column slabs 93.
 #include "bias.h"
 #include "kernels.h"
 
@@ -27,8 +37,10 @@ namespace hstu {
 
 namespace {
 
-constexpr int kBktThreads = 256;
-constexpr int kBktRows = 48;    // rows per workgroup
+constexpr int kBktThreads = 512;
+constexpr int kBktWaves = kBktThreads / 64;
+constexpr int kBktStep = 16;                // rows a wave takes together are this far apart
+constexpr int kBktMaxRows = 4 * kBktStep;   // rows per workgroup, at most
 constexpr int kBktCols = 8192;  // columns staged per slab
 // Entry y of a copy sits at y + 4 (y >> kPadShift); y <= kBktCols.
 constexpr int kPadShift = 6;
@@ -42,7 +54,7 @@ struct __align__(16) BktShared {
     uint32_t t32[2][kBktLd];  // copy s holds column x at bkt_pidx(x + s)
     int64_t t64[kBktCols];
   };
-  int64_t rowt[kBktRows];     // the workgroup's row timestamps
+  int64_t rowt[kBktMaxRows];    // the workgroup's row timestamps
 };
 
 // Leading-zero count of |ti - tj| < 2^31 (0xffffffff for 0), raised to
@@ -78,12 +90,17 @@ __device__ __forceinline__ uint32_t bkt4(uint32_t ti, uint32_t a, uint32_t b, ui
   return r;
 }
 
-template <bool CLAMP>
-__device__ __forceinline__ void row_segment32(const BktShared& sm, uint32_t ti, int nb, int64_t P,
-                                              int ncols, uint8_t* __restrict__ out, int lane) {
-  // Flat bytes [P, P + ncols) hold columns 0 .. ncols-1 of the slab;
-  // relative to P: the head [0, hend), nch aligned 16-byte chunks from h =
-  // (16 - P) mod 16, and the tail [tstart, ncols) (at most 15 bytes each).
+// NR rows of the slab at once, 16 rows apart: 16 L is a multiple of 16, so
+// their segments share one alignment, and with it the chunks' columns and
+// every LDS read.  The first `nv` of them exist (nv >= 1).
+template <bool CLAMP, int NR>
+__device__ __forceinline__ void row_segments32(const BktShared& sm, const uint32_t (&ti)[NR],
+                                               int nv, int nb, int64_t P, int64_t row_step,
+                                               int ncols, uint8_t* __restrict__ out, int lane) {
+  // Flat bytes [P, P + ncols) hold columns 0 .. ncols-1 of the slab in the
+  // first row; relative to P: the head [0, hend), nch aligned 16-byte chunks
+  // from h = (16 - P) mod 16, and the tail [tstart, ncols) (at most 15
+  // bytes each).
   const uint32_t zmin = CLAMP ? (uint32_t)(32 - nb) : 0u;
   const uint32_t c31 = 31u;
   const int64_t cfirst = (P + 15) >> 4;
@@ -96,10 +113,15 @@ __device__ __forceinline__ void row_segment32(const BktShared& sm, uint32_t ti, 
     const int r = lane < 32 ? lane : tstart + (lane - 32);
     const bool on = lane < 32 ? lane < hend : (lane < 48 && r < ncols);
     if (on) {
-      const uint32_t z = lz32<CLAMP>(ti, sm.t32[0][bkt_pidx(r)], zmin);
-      uint32_t b;
-      asm("v_sub_u32_e64 %0, 31, %1 clamp" : "=v"(b) : "v"(z));
-      row[r] = (uint8_t)b;
+      const uint32_t tj = sm.t32[0][bkt_pidx(r)];
+#pragma unroll
+      for (int k = 0; k < NR; k++)
+        if (k < nv) {
+          const uint32_t z = lz32<CLAMP>(ti[k], tj, zmin);
+          uint32_t b;
+          asm("v_sub_u32_e64 %0, 31, %1 clamp" : "=v"(b) : "v"(z));
+          row[r + k * row_step] = (uint8_t)b;
+        }
     }
   }
   if (lane >= nch) return;
@@ -108,42 +130,51 @@ __device__ __forceinline__ void row_segment32(const BktShared& sm, uint32_t ti, 
   // (16-byte reads), else 2 mod 4 (8-byte reads).  Moving 64 chunks on
   // adds 1024 entries, 16 whole pad periods: the offsets of the reads
   // from the first stay fixed and the first moves by 1088.
-  const int k = (int)(P & 3), sc = k & 1;
+  const int k4 = (int)(P & 3), sc = k4 & 1;
   const int y = h + sc + 16 * lane;
   const int p0 = bkt_pidx(y);
   const uint32_t* src = sm.t32[sc] + p0;
-  u32x4* dst = reinterpret_cast<u32x4*>(row + h + 16 * lane);
-  if (k < 2) {
-    const int d1 = bkt_pidx(y + 4) - p0, d2 = bkt_pidx(y + 8) - p0, d3 = bkt_pidx(y + 12) - p0;
+  uint8_t* dst = row + h + 16 * lane;
+  auto chunk = [&](const uint32_t (&t)[16]) {
+#pragma unroll
+    for (int k = 0; k < NR; k++)
+      if (k < nv) {
+        u32x4 v;
+#pragma unroll
+        for (int q = 0; q < 4; q++)
+          v[q] = bkt4<CLAMP>(ti[k], t[4 * q], t[4 * q + 1], t[4 * q + 2], t[4 * q + 3], zmin, c31);
+        *reinterpret_cast<u32x4*>(dst + k * row_step) = v;
+      }
+    src += kChunkStep;
+    dst += 64 * 16;
+  };
+  if (k4 < 2) {
+    int dd[4];
+#pragma unroll
+    for (int m = 0; m < 4; m++) dd[m] = bkt_pidx(y + 4 * m) - p0;
     for (int a = lane; a < nch; a += 64) {
-      const u32x4 t0 = *reinterpret_cast<const u32x4*>(src);
-      const u32x4 t1 = *reinterpret_cast<const u32x4*>(src + d1);
-      const u32x4 t2 = *reinterpret_cast<const u32x4*>(src + d2);
-      const u32x4 t3 = *reinterpret_cast<const u32x4*>(src + d3);
-      u32x4 v;
-      v[0] = bkt4<CLAMP>(ti, t0[0], t0[1], t0[2], t0[3], zmin, c31);
-      v[1] = bkt4<CLAMP>(ti, t1[0], t1[1], t1[2], t1[3], zmin, c31);
-      v[2] = bkt4<CLAMP>(ti, t2[0], t2[1], t2[2], t2[3], zmin, c31);
-      v[3] = bkt4<CLAMP>(ti, t3[0], t3[1], t3[2], t3[3], zmin, c31);
-      *dst = v;
-      src += kChunkStep;
-      dst += 64;
+      uint32_t t[16];
+#pragma unroll
+      for (int m = 0; m < 4; m++) {
+        const u32x4 w = *reinterpret_cast<const u32x4*>(src + dd[m]);
+#pragma unroll
+        for (int e = 0; e < 4; e++) t[4 * m + e] = w[e];
+      }
+      chunk(t);
     }
   } else {
     int dd[8];
 #pragma unroll
     for (int m = 0; m < 8; m++) dd[m] = bkt_pidx(y + 2 * m) - p0;
     for (int a = lane; a < nch; a += 64) {
-      uint2 t[8];
+      uint32_t t[16];
 #pragma unroll
-      for (int m = 0; m < 8; m++) t[m] = *reinterpret_cast<const uint2*>(src + dd[m]);
-      u32x4 v;
-#pragma unroll
-      for (int q = 0; q < 4; q++)
-        v[q] = bkt4<CLAMP>(ti, t[2 * q].x, t[2 * q].y, t[2 * q + 1].x, t[2 * q + 1].y, zmin, c31);
-      *dst = v;
-      src += kChunkStep;
-      dst += 64;
+      for (int m = 0; m < 8; m++) {
+        const uint2 w = *reinterpret_cast<const uint2*>(src + dd[m]);
+        t[2 * m] = w.x;
+        t[2 * m + 1] = w.y;
+      }
+      chunk(t);
     }
   }
 }
@@ -155,6 +186,7 @@ __device__ __forceinline__ void row_segment64(const BktShared& sm, int64_t ti, i
 
 // Rows r0 .. r0 + rows - 1 of one sequence (timestamps t, length L, pairs
 // from base), every column.
+template <int NR>
 __device__ __forceinline__ void bucketize_rows(BktShared& sm, int nb, const int64_t* __restrict__ t,
                                                int L, int64_t base, int r0, int rows,
                                                uint8_t* __restrict__ out, int tid, int wave,
@@ -201,24 +233,33 @@ __device__ __forceinline__ void bucketize_rows(BktShared& sm, int nb, const int6
       }
     }
     __syncthreads();
-    // Row set-up is wave-uniform (scalar unit).
-    for (int r = wave; r < rows; r += kBktThreads / 64) {
-      const int64_t ti = ((int64_t)__builtin_amdgcn_readfirstlane((int)(sm.rowt[r] >> 32)) << 32) |
-                         (uint32_t)__builtin_amdgcn_readfirstlane((int)sm.rowt[r]);
-      const int64_t P = base + (int64_t)(r0 + r) * L + c0;
-      if (!fast)
-        row_segment64(sm, ti, nb, P, ncols, out, lane);
-      else if (nb <= 31)
-        row_segment32<true>(sm, (uint32_t)(ti - t0), nb, P, ncols, out, lane);
-      else
-        row_segment32<false>(sm, (uint32_t)(ti - t0), nb, P, ncols, out, lane);
+    // A wave takes rows x, x + 16, ... for x = wave, wave + 8; row set-up is
+    // wave-uniform (scalar unit).
+    for (int x = wave; x < min(rows, kBktStep); x += kBktWaves) {
+      const int nv = (rows - x + kBktStep - 1) / kBktStep;
+      const int64_t P = base + (int64_t)(r0 + x) * L + c0, step = (int64_t)kBktStep * L;
+      if (fast) {
+        uint32_t ti[NR];
+#pragma unroll
+        for (int k = 0; k < NR; k++)
+          ti[k] = (uint32_t)__builtin_amdgcn_readfirstlane(
+              (int)(sm.rowt[min(x + k * kBktStep, rows - 1)] - t0));
+        if (nb <= 31)
+          row_segments32<true, NR>(sm, ti, nv, nb, P, step, ncols, out, lane);
+        else
+          row_segments32<false, NR>(sm, ti, nv, nb, P, step, ncols, out, lane);
+      } else {
+        for (int k = 0; k < nv; k++)
+          row_segment64(sm, sm.rowt[x + k * kBktStep], nb, P + k * step, ncols, out, lane);
+      }
     }
     __syncthreads();  // the slab (or the row timestamps) is restaged next
   }
 }
 
-// Workgroup g covers tokens [48 g, 48 g + 48) of the concatenated batch:
-// the rows of the sequence(s) those tokens belong to, every column.
+// Workgroup g covers tokens [R g, R g + R), R = 16 NR, of the concatenated
+// batch: the rows of the sequence(s) those tokens belong to, every column.
+template <int NR>
 __global__ __launch_bounds__(kBktThreads) void bucketize_kernel(
     int32_t num_seqs, int64_t total_tokens, int32_t nb, const int64_t* __restrict__ offs,
     const int64_t* __restrict__ ts, const int64_t* __restrict__ pair_offs,
@@ -226,9 +267,10 @@ __global__ __launch_bounds__(kBktThreads) void bucketize_kernel(
   __shared__ BktShared sm;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  for (int64_t g = blockIdx.x; g * kBktRows < total_tokens; g += gridDim.x) {
-    int64_t R0 = g * kBktRows;
-    const int64_t R1 = min(R0 + kBktRows, total_tokens);
+  constexpr int kRows = NR * kBktStep;
+  for (int64_t g = blockIdx.x; g * kRows < total_tokens; g += gridDim.x) {
+    int64_t R0 = g * kRows;
+    const int64_t R1 = min(R0 + kRows, total_tokens);
     // b = the last sequence with offs[b] <= R0 (offsets are non-decreasing).
     int lo = 0, hi = num_seqs - 1;
     while (lo < hi) {
@@ -239,7 +281,7 @@ __global__ __launch_bounds__(kBktThreads) void bucketize_kernel(
       const int64_t o = offs[b], e = offs[b + 1];
       if (e <= R0) continue;  // empty sequence
       const int rows = (int)(min(e, R1) - R0);
-      bucketize_rows(sm, nb, ts + o, (int)(e - o), pair_offs[b], (int)(R0 - o), rows, out, tid,
+      bucketize_rows<NR>(sm, nb, ts + o, (int)(e - o), pair_offs[b], (int)(R0 - o), rows, out, tid,
                      wave, lane);
       R0 += rows;
     }
@@ -253,10 +295,20 @@ hipError_t launch_bucketize(int32_t num_seqs, int64_t total_tokens, int32_t num_
                             const int64_t* pair_offsets, int64_t total_pairs, uint8_t* out,
                             hipStream_t s) {
   if (total_pairs <= 0 || num_seqs <= 0 || total_tokens <= 0) return hipSuccess;
-  const int64_t blocks = (total_tokens + kBktRows - 1) / kBktRows;
-  const unsigned grid = (unsigned)min(blocks, (int64_t)1 << 30);
-  hipLaunchKernelGGL(bucketize_kernel, dim3(grid), dim3(kBktThreads), 0, s, num_seqs, total_tokens,
-                     num_buckets, seq_offsets, timestamps, pair_offsets, out);
+  // Fewer rows per workgroup while that fills the 512 workgroups the chip
+  // holds.
+  auto launch = [&](auto kernel, int rows) {
+    const int64_t blocks = (total_tokens + rows - 1) / rows;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)min(blocks, (int64_t)1 << 30)), dim3(kBktThreads), 0,
+                       s, num_seqs, total_tokens, num_buckets, seq_offsets, timestamps,
+                       pair_offsets, out);
+  };
+  if (total_tokens <= 16 * 512)
+    launch(bucketize_kernel<1>, kBktStep);
+  else if (total_tokens <= 32 * 512)
+    launch(bucketize_kernel<2>, 2 * kBktStep);
+  else
+    launch(bucketize_kernel<4>, 4 * kBktStep);
   return hipGetLastError();
 }
 

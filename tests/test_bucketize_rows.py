@@ -1,0 +1,39 @@
+"""hstu_time_bucketize at the edges of its row grouping: the three row counts
+per workgroup (16, 32 and 64, chosen by the batch's tokens), sequences that
+begin and end inside a workgroup's rows, every alignment of a row's first
+byte, rows past one slab of 8192 columns, both timestamp widths and the
+clamped bucket counts.  Exact."""
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+
+def _reference(ts, nb):
+    d = np.abs(ts[:, None] - ts[None, :])
+    return np.minimum(np.frexp(np.maximum(d, 1).astype(np.float64))[1] - 1, nb - 1)
+
+
+@pytest.mark.parametrize("lengths", [
+    tuple(range(1, 70)),                       # 2415 tokens: 16 rows
+    tuple([7, 0, 129, 1000, 2049] * 3),        # 9555 tokens: 32 rows
+    tuple([63, 64, 65, 1023, 0, 17] * 14),     # 17248 tokens: 64 rows
+    (8191, 8193, 3)])
+@pytest.mark.parametrize("nb,gap", [(128, 600), (32, 600), (9, 600), (1, 600), (64, 1 << 34)])
+def test_bucketize_row_groups(lengths, nb, gap):
+    from paper_2402_17152_amd import hstu
+    if gap > 600 and max(lengths) > 3000:
+        pytest.skip("64-bit differences are covered by the shorter batches")
+    rng = np.random.default_rng(len(lengths) + nb)
+    offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
+    ts = np.concatenate([1_700_000_000 + np.cumsum(rng.integers(0, gap, n)) for n in lengths])
+    ts = ts.astype(np.int64)
+    dev = lambda a: torch.from_numpy(a).cuda()
+    got = hstu.hstu_time_bucketize(dev(offs), dev(ts), nb).cpu().numpy()
+    o = 0
+    for b, n in enumerate(lengths):
+        ref = _reference(ts[offs[b]:offs[b + 1]], nb)
+        assert np.array_equal(got[o:o + n * n].reshape(n, n), ref), f"sequence {b} of {n} tokens"
+        o += n * n
+    assert o == got.size
