@@ -7,16 +7,23 @@
 // accumulation on v_mfma_f32_32x32x16_bf16.  An operand is stored either
 // k-contiguous (A[m][k], B[n][k]: activations and [out][in] weights in the
 // forward) or k-major (A[k][m], B[k][n]: the transposed operands of the
-// gradients).  A workgroup of 4 waves computes a 256 x 128 tile, each wave
-// 128 x 64 (8 accumulator tiles), over k-steps of 32 staged in LDS (double
-// buffered, one barrier per step; global loads run two steps ahead through
-// two register sets); two workgroups share a CU, so one's epilogue and
-// staging overlap the other's matrix-core work.  A k-contiguous tile gives a
-// lane its 8 contraction elements in one 16-byte LDS read; a k-major tile
-// is read with two transposing reads (ds_read_b64_tr_b16) that return the
-// same 8 elements in the same order.  The products are computed
-// transposed (B's fragment as the matrix core's first operand), so a lane
-// owns one output row and 4 consecutive columns per register group.
+// gradients).  A workgroup of 4 waves computes a 256 x 128 tile (128 x 128
+// when the larger ones would not fill the chip), each wave 128 x 64 (64 x
+// 64), over k-steps of 32.  A k-contiguous tile gives a lane its 8
+// contraction elements in one 16-byte LDS read; a k-major tile is read with
+// two transposing reads (ds_read_b64_tr_b16) that return the same 8 elements
+// in the same order.  The products are computed transposed (B's fragment as
+// the matrix core's first operand), so a lane owns one output row and 4
+// consecutive columns per register group.
+//
+// Staging: LDS DMA into a ring of three k-steps, issued two to three steps
+// ahead, in a layout without padding whose 16-byte chunks are permuted so
+// that every LDS read spreads over all banks.  The fragments of a half step
+// are read while the matrix cores work on the half step before, across the
+// one barrier per step, so neither the LDS nor the memory latency is in the
+// chain; two workgroups per CU overlap one's epilogue with the other's
+// products.
+//
 // Weight gradients split the contraction over the tokens; each split
 // writes an fp32 slab and an ordered reduction sums the slabs, so results
 // do not depend on scheduling.
@@ -27,84 +34,103 @@ namespace hstu {
 
 namespace {
 
-constexpr int kGBM = 256, kGBN = 128, kGBK = 32;
-constexpr int kLdK = kGBK + 8;  // k-contiguous tile: row stride in elements (80 B)
-// k-major tile of R rows of m / n: row stride R + 8 elements.
-template <int R>
-struct TileDims {
-  static constexpr int kElemsK = R * kLdK;           // k-contiguous
-  static constexpr int kElemsN = kGBK * (R + 8);     // k-major
-  static constexpr int kElems = kElemsK > kElemsN ? kElemsK : kElemsN;
-};
+constexpr int kGBK = 32;
 
+// A workgroup of 2 x WN waves, each MB 32-row blocks by 64 columns: the tile
+// is BM = 64 MB rows by BN = 64 WN columns; ring of S k-steps in LDS.
+template <int MB, int WN, int S>
 struct GemmShared {
-  uint16_t a[2][TileDims<kGBM>::kElems];
-  uint16_t b[2][TileDims<kGBN>::kElems];
+  static constexpr int kA = 64 * MB * kGBK, kB = 64 * WN * kGBK;  // elements
+  __align__(16) uint16_t t[S][kA + kB];
 };
 
 __device__ __forceinline__ float silu_f(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x * -kLog2e));
 }
 
-// Staging of one operand tile (R rows of the m or n dimension x 32 of k)
-// through registers: R * 4 chunks of 16 bytes, R / 64 per thread.
-template <bool KMAJOR, int R>
-struct Stager {
-  static constexpr int kPer = R / 64;
-  static constexpr int kLdN = R + 8;
-  __amdgpu_buffer_rsrc_t rs;
-  uint32_t ld_b;  // row stride in bytes
-  __device__ __forceinline__ void load(u32x4 (&r)[kPer], int k0, int tid) const {
-#pragma unroll
-    for (int e = 0; e < kPer; e++) {
-      const int c = tid + 256 * e;
-      uint32_t off;
-      if constexpr (KMAJOR)  // row k0 + c / (R/8), chunk c % (R/8)
-        off = (uint32_t)(k0 + c / (R / 8)) * ld_b + (uint32_t)(c % (R / 8)) * 16u;
-      else                   // row c / 4, k chunk c % 4
-        off = (uint32_t)(c >> 2) * ld_b + (uint32_t)(k0 + 8 * (c & 3)) * 2u;
-      r[e] = buffer_load16(rs, off);
-    }
-  }
-  __device__ __forceinline__ static void store(uint16_t* t, const u32x4 (&r)[kPer], int tid) {
-#pragma unroll
-    for (int e = 0; e < kPer; e++) {
-      const int c = tid + 256 * e;
-      uint16_t* p = KMAJOR ? t + (c / (R / 8)) * kLdN + 8 * (c % (R / 8))
-                           : t + (c >> 2) * kLdK + 8 * (c & 3);
-      *reinterpret_cast<u32x4*>(p) = r[e];
-    }
-  }
-  // MFMA operand of 32 rows (row0 .. row0+31 of the tile) for the 16-wide
-  // contraction block s: lane -> row row0 + lane % 32, k = 16 s + 8 h .. +7.
-  __device__ __forceinline__ static u32x4 frag(const uint16_t* t, int row0, int s, int lane) {
+// One operand tile in LDS: R rows of the m or n dimension x 32 of k, in
+// 16-byte chunks.  k-contiguous: [row][4 chunks], chunk c of row r at
+// position c ^ (r / 4 % 4).  k-major: [k][R / 8 chunks], chunk c of row k at
+// c ^ 4 (k % 4).  Either way 16 (32) lanes of a 16-byte (transposing 8-byte)
+// read meet all 64 banks.
+template <bool KMAJOR, int R, int WAVES>
+struct Operand {
+  static constexpr int kOps = R * kGBK * 2 / 1024 / WAVES;  // 1 KB DMA operations per wave
+  u32x4 rs;           // buffer resource words
+  uint32_t ld_b;      // row stride in bytes
+  uint32_t off[kOps]; // the lane's byte offsets at k = 0
+  uint32_t rd[2];     // k-contiguous: LDS byte offsets of the two half steps
+                      // k-major: [0] the lane's, without its 32-row block
+  uint32_t x;         // k-major: the lane's k % 4
+
+  __device__ __forceinline__ void init(const uint16_t* base, uint32_t bytes, int64_t ld, int wave,
+                                       int lane) {
+    rs = rsrc_words(base, bytes);
+    ld_b = (uint32_t)ld * 2u;
     const int h = lane >> 5;
+#pragma unroll
+    for (int e = 0; e < kOps; e++) {
+      const int op = wave * kOps + e;
+      if constexpr (KMAJOR) {
+        constexpr int kRowChunks = R / 8, kRowsPerOp = 64 / kRowChunks;
+        const int k = op * kRowsPerOp + lane / kRowChunks;
+        const int c = (lane % kRowChunks) ^ (4 * (k & 3));
+        off[e] = (uint32_t)k * ld_b + 16u * (uint32_t)c;
+      } else {
+        const int row = 16 * op + (lane >> 2), c = (lane & 3) ^ ((row >> 2) & 3);
+        off[e] = (uint32_t)row * ld_b + 16u * (uint32_t)c;
+      }
+    }
     if constexpr (KMAJOR) {
-      const uint16_t* p = t + (16 * s + 8 * h + ((lane & 15) >> 2)) * kLdN + row0 +
-                          16 * ((lane >> 4) & 1) + 4 * (lane & 3);
-      const uint2 lo = lds_read_tr16(p), hi = lds_read_tr16(p + 4 * kLdN);
-      const u32x4 v = {lo.x, lo.y, hi.x, hi.y};
-      return v;
+      x = (uint32_t)(lane >> 2) & 3u;
+      rd[0] = (uint32_t)((8 * h + (int)x) * R * 2 + 32 * ((lane >> 4) & 1) + 8 * (lane & 3));
+      rd[1] = 0;
     } else {
-      return *reinterpret_cast<const u32x4*>(t + (row0 + (lane & 31)) * kLdK + 16 * s + 8 * h);
+#pragma unroll
+      for (int s = 0; s < 2; s++)
+        rd[s] = (uint32_t)((lane & 31) * 64 + 16 * ((2 * s + h) ^ ((lane >> 2) & 3)));
+      x = 0;
+    }
+  }
+  // Issues the wave's share of the k-step starting at k0 into tile `t`.
+  __device__ __forceinline__ void issue(uint16_t* t, int k0, int wave) const {
+    const uint32_t kb = KMAJOR ? (uint32_t)k0 * ld_b : 2u * (uint32_t)k0;
+#pragma unroll
+    for (int e = 0; e < kOps; e++)
+      dma_to_lds16_asm(rs, t + 512 * (wave * kOps + e), off[e] + kb);
+  }
+  // MFMA operand of the 32 rows of block `blk` for the half step s: lane ->
+  // row lane % 32, k = 16 s + 8 (lane / 32) .. +7.
+  __device__ __forceinline__ u32x4 frag(const uint16_t* t, int blk, int s) const {
+    const char* p = reinterpret_cast<const char*>(t);
+    if constexpr (KMAJOR) {
+      const char* q = p + rd[0] + 64u * ((uint32_t)blk ^ x) + 16 * s * R * 2;
+      const uint2 lo = lds_read_tr16(reinterpret_cast<const uint16_t*>(q));
+      const uint2 hi = lds_read_tr16(reinterpret_cast<const uint16_t*>(q + 4 * R * 2));
+      return u32x4{lo.x, lo.y, hi.x, hi.y};
+    } else {
+      return *reinterpret_cast<const u32x4*>(p + rd[s] + blk * (32 * 64));
     }
   }
 };
 
-template <bool A_KM, bool B_KM, int EPI>
-__global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs g) {
-  __shared__ GemmShared sm;
-  using SA = Stager<A_KM, kGBM>;
-  using SB = Stager<B_KM, kGBN>;
+template <int MB, int WN, int S, bool A_KM, bool B_KM, int EPI, bool STREAM>
+__global__ __launch_bounds__(128 * WN, 2) void gemm_bf16_kernel(GemmArgs g) {
+  using Sh = GemmShared<MB, WN, S>;
+  __shared__ Sh sm;
+  constexpr int BM = 64 * MB, BN = 64 * WN;
+  using OA = Operand<A_KM, BM, 2 * WN>;
+  using OB = Operand<B_KM, BN, 2 * WN>;
+  constexpr int kOps = OA::kOps + OB::kOps;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int wm = wave >> 1, wn = wave & 1;  // wave tile: rows 128 wm .., columns 64 wn ..
+  const int wm = wave / WN, wn = wave % WN;  // wave tile: rows 32 MB wm .., columns 64 wn ..
   // Tile order: consecutive tiles (same row panel of A, n fastest) go to
   // one XCD (workgroup ids are dealt to the 8 XCDs round robin).
-  const int tn = (g.N + kGBN - 1) / kGBN, nt = ((g.M + kGBM - 1) / kGBM) * tn;
+  const int tn = (g.N + BN - 1) / BN, nt = ((g.M + BM - 1) / BM) * tn;
   const int id = blockIdx.x, xcd = id & 7, per = nt >> 3, rem = nt & 7;
   const int tile = xcd * per + min(xcd, rem) + (id >> 3);
-  const int m0 = (tile / tn) * kGBM, n0 = (tile % tn) * kGBN;
+  const int m0 = (tile / tn) * BM, n0 = (tile % tn) * BN;
   const int kb = blockIdx.y * g.k_split;
   const int ke = min(g.K, kb + g.k_split);
   const int nk = (ke - kb + kGBK - 1) / kGBK;
@@ -112,99 +138,143 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs g) {
   // Buffer ranges: rows past M / N (k-contiguous) and contraction rows at
   // or past ke (k-major) read as zeros; k-major columns past M / N read
   // neighbouring data that only reaches outputs that are not stored.
-  SA sa;
-  SB sb;
-  if constexpr (A_KM) {
-    sa.rs = make_rsrc(g.a + m0, (uint32_t)(((int64_t)(ke - 1) * g.lda + (g.M - m0)) * 2));
-  } else {
-    sa.rs = make_rsrc(g.a + (int64_t)m0 * g.lda, (uint32_t)((int64_t)(g.M - m0) * g.lda * 2));
-  }
-  if constexpr (B_KM) {
-    sb.rs = make_rsrc(g.b + n0, (uint32_t)(((int64_t)(ke - 1) * g.ldb + (g.N - n0)) * 2));
-  } else {
-    sb.rs = make_rsrc(g.b + (int64_t)n0 * g.ldb, (uint32_t)((int64_t)(g.N - n0) * g.ldb * 2));
-  }
-  sa.ld_b = (uint32_t)g.lda * 2u;
-  sb.ld_b = (uint32_t)g.ldb * 2u;
+  OA oa;
+  OB ob;
+  if constexpr (A_KM)
+    oa.init(g.a + m0, (uint32_t)(((int64_t)(ke - 1) * g.lda + (g.M - m0)) * 2), g.lda, wave, lane);
+  else
+    oa.init(g.a + (int64_t)m0 * g.lda,
+            (uint32_t)(((int64_t)(min(g.M - m0, BM) - 1) * g.lda + g.K) * 2), g.lda, wave, lane);
+  if constexpr (B_KM)
+    ob.init(g.b + n0, (uint32_t)(((int64_t)(ke - 1) * g.ldb + (g.N - n0)) * 2), g.ldb, wave, lane);
+  else
+    ob.init(g.b + (int64_t)n0 * g.ldb,
+            (uint32_t)(((int64_t)(min(g.N - n0, BN) - 1) * g.ldb + g.K) * 2), g.ldb, wave, lane);
 
-  f32x16 acc[4][2];
+  f32x16 acc[MB][2];
 #pragma unroll
-  for (int i = 0; i < 4; i++)
+  for (int i = 0; i < MB; i++)
 #pragma unroll
     for (int j = 0; j < 2; j++)
 #pragma unroll
       for (int q = 0; q < 16; q++) acc[i][j][q] = 0.0f;
 
-  // Two register sets stage k-steps two ahead: while step kt is computed
-  // from LDS, the loads of step kt + 2 go into the set that step kt came
-  // through, and the set holding step kt + 1 (loaded during step kt - 1)
-  // is written to the other LDS buffer.
-  u32x4 ra0[SA::kPer], rb0[SB::kPer], ra1[SA::kPer], rb1[SB::kPer];
-  auto compute = [&](int cur) {
-    const uint16_t* ta = sm.a[cur];
-    const uint16_t* tb = sm.b[cur];
-    // Both contraction blocks' operands are read before the first MFMA.
-    u32x4 af[2][4], bf[2][2];
-#pragma unroll
-    for (int s = 0; s < 2; s++) {
-#pragma unroll
-      for (int i = 0; i < 4; i++) af[s][i] = SA::frag(ta, 128 * wm + 32 * i, s, lane);
-#pragma unroll
-      for (int j = 0; j < 2; j++) bf[s][j] = SB::frag(tb, 64 * wn + 32 * j, s, lane);
-    }
-#pragma unroll
-    for (int s = 0; s < 2; s++)
-#pragma unroll
-      for (int i = 0; i < 4; i++)
-#pragma unroll
-        for (int j = 0; j < 2; j++)
-          acc[i][j] = mfma32x32x16(as_bf16x8(bf[s][j]), as_bf16x8(af[s][i]), acc[i][j]);
+  // Row panels start at different steps of a k-contiguous contraction: rows
+  // lie a power of two apart, so that panels in step would all read the same
+  // few memory channels.
+  int kx = A_KM ? 0 : (m0 / BM * 3) % max(nk, 1);
+  auto issue = [&](int st) {
+    oa.issue(sm.t[st], kb + kx * kGBK, wave);
+    ob.issue(sm.t[st] + Sh::kA, kb + kx * kGBK, wave);
+    kx = kx + 1 == nk ? 0 : kx + 1;
   };
-  // One k-step: ra/rb_free receive step kt + 2, ra/rb_next (step kt + 1)
-  // go to LDS buffer (kt + 1) & 1.
-  auto kstep = [&](int kt, u32x4 (&ra_free)[SA::kPer], u32x4 (&rb_free)[SB::kPer],
-                   u32x4 (&ra_next)[SA::kPer], u32x4 (&rb_next)[SB::kPer]) {
-    if (kt + 2 < nk) {
-      sa.load(ra_free, kb + (kt + 2) * kGBK, tid);
-      sb.load(rb_free, kb + (kt + 2) * kGBK, tid);
-    }
-    compute(kt & 1);
-    if (kt + 1 < nk) {
-      SA::store(sm.a[(kt + 1) & 1], ra_next, tid);
-      SB::store(sm.b[(kt + 1) & 1], rb_next, tid);
-    }
-    __syncthreads();
+
+  u32x4 af[2][MB], bf[2][2];
+  auto read = [&](int st, int s) {
+    const uint16_t* ta = sm.t[st];
+#pragma unroll
+    for (int j = 0; j < 2; j++) bf[s][j] = ob.frag(ta + Sh::kA, 2 * wn + j, s);
+#pragma unroll
+    for (int i = 0; i < MB; i++) af[s][i] = oa.frag(ta, MB * wm + i, s);
   };
+  auto product = [&](int s) {
+#pragma unroll
+    for (int i = 0; i < MB; i++)
+#pragma unroll
+      for (int j = 0; j < 2; j++)
+        acc[i][j] = mfma32x32x16(as_bf16x8(bf[s][j]), as_bf16x8(af[s][i]), acc[i][j]);
+  };
+  // Every wave issues kOps operations per step, in step order, so a count
+  // of outstanding ones tells which steps have landed.
+  auto wait_all_but = [&](int steps) {  // until at most `steps` steps (< S) are in flight
+    if (S > 3 && steps >= 3)
+      wait_vmcnt_lgkmcnt0<3 * kOps>();
+    else if (steps >= 2)
+      wait_vmcnt_lgkmcnt0<2 * kOps>();
+    else if (steps == 1)
+      wait_vmcnt_lgkmcnt0<kOps>();
+    else
+      wait_vmcnt_lgkmcnt0<0>();
+  };
+  const int ahead = min(nk, S);
+  for (int kt = 0; kt < ahead; kt++) issue(kt);
+  wait_all_but(ahead - 1);
+  barrier_no_fence();
+  int st = 0;
   if (nk > 0) {
-    sa.load(ra0, kb, tid);
-    sb.load(rb0, kb, tid);
-    if (nk > 1) {
-      sa.load(ra1, kb + kGBK, tid);
-      sb.load(rb1, kb + kGBK, tid);
+    read(0, 0);
+    // (The last step stands outside the loop: on a path that joined it
+    // without the wait below, product(1) would wait for the reads after it.)
+    for (int kt = 0; kt + 1 < nk; kt++) {
+      read(st, 1);
+      product(0);
+      // Step kt + 1 has landed (later ones may be in flight), and this wave
+      // has its fragments of step kt; past the barrier every wave does, and
+      // the step's place in the ring is free.
+      if (kt + S <= nk)
+        wait_vmcnt_lgkmcnt0<(S - 2) * kOps>();
+      else
+        wait_all_but(nk - kt - 2);
+      barrier_no_fence();
+      if (kt + S < nk) issue(st);
+      st = st == S - 1 ? 0 : st + 1;
+      read(st, 0);
+      product(1);
     }
-    SA::store(sm.a[0], ra0, tid);
-    SB::store(sm.b[0], rb0, tid);
+    read(st, 1);
+    product(0);
+    product(1);
   }
-  __syncthreads();
-  int kt = 0;
-  for (; kt + 1 < nk; kt += 2) {
-    kstep(kt, ra0, rb0, ra1, rb1);      // step kt came through set 0
-    kstep(kt + 1, ra1, rb1, ra0, rb0);  // step kt + 1 through set 1
-  }
-  if (kt < nk) kstep(kt, ra0, rb0, ra1, rb1);
+  // The epilogue's LDS overlays the ring: no wave may still read it.
+  wait_vmcnt_lgkmcnt0<0>();
+  barrier_no_fence();
 
   // Epilogue, per group of 32 rows: the wave writes its 32 x 64 fp32 block
   // to a private LDS region (acc[i][j] register 4 g4 + e is row lane % 32,
   // column 32 j + 8 g4 + 4 h + e), then each lane takes 8 consecutive
   // columns of a row back, applies bias / SiLU / residual and stores 16
-  // bytes: a store instruction covers 8 rows x 128 contiguous bytes.  (The
-  // loop's last barrier has retired every read of the staging buffers; LDS
+  // bytes: a store instruction covers 8 rows x 128 contiguous bytes.  (LDS
   // operations of one wave complete in order.)
   constexpr int kEpLd = 64 + 4;
   float* ep = reinterpret_cast<float*>(&sm) + wave * (32 * kEpLd);
   const int h = lane >> 5;
+  const int mr = m0 + 32 * MB * wm + (lane >> 3);  // the lane's first row
+  const int cc = lane & 7, n = n0 + 64 * wn + 8 * cc;
+  const bool n_ok = n < g.N;
+  // The bias of the lane's columns, and the residual rows one 32-row block
+  // ahead of their use (loads only: clamped into range).
+  float bv[8] = {};
+  u32x4 rv[2][4] = {};
+  auto load_res = [&](int i) {
 #pragma unroll
-  for (int i = 0; i < 4; i++) {
+    for (int r = 0; r < 4; r++)
+      rv[i & 1][r] = *reinterpret_cast<const u32x4*>(
+          g.res + (int64_t)min(mr + 32 * i + 8 * r, g.M - 1) * g.ldr + min(n, g.N - 8));
+  };
+  const bool has_res = EPI == kEpiAdd && g.res;
+  if constexpr (EPI != kEpiSlab) {
+    if (has_res) load_res(0);
+    if (g.bias) {
+      const f32x4 b0 = *reinterpret_cast<const f32x4*>(g.bias + min(n, g.N - 8));
+      const f32x4 b1 = *reinterpret_cast<const f32x4*>(g.bias + min(n, g.N - 8) + 4);
+#pragma unroll
+      for (int e = 0; e < 4; e++) {
+        bv[e] = b0[e];
+        bv[4 + e] = b1[e];
+      }
+    }
+  }
+  auto store = [&](uint16_t* p, const float (&v)[8]) {
+    const u32x4 o = pack_bf16x8(v);
+    if constexpr (STREAM)
+      __builtin_nontemporal_store(o, reinterpret_cast<u32x4*>(p));
+    else
+      *reinterpret_cast<u32x4*>(p) = o;
+  };
+#pragma unroll
+  for (int i = 0; i < MB; i++) {
+    if constexpr (EPI == kEpiAdd)
+      if (has_res && i + 1 < MB) load_res(i + 1);
 #pragma unroll
     for (int j = 0; j < 2; j++)
 #pragma unroll
@@ -216,45 +286,30 @@ __global__ __launch_bounds__(256, 2) void gemm_bf16_kernel(GemmArgs g) {
     __builtin_amdgcn_wave_barrier();
 #pragma unroll
     for (int r = 0; r < 4; r++) {
-      const int c = lane + 64 * r, row = c >> 3, cc = c & 7;
-      const int m = m0 + 128 * wm + 32 * i + row, n = n0 + 64 * wn + 8 * cc;
+      const int row = (lane >> 3) + 8 * r, m = mr + 32 * i + 8 * r;
       const f32x4 lo = *reinterpret_cast<const f32x4*>(ep + row * kEpLd + 8 * cc);
       const f32x4 hi = *reinterpret_cast<const f32x4*>(ep + row * kEpLd + 8 * cc + 4);
-      if (m >= g.M || n >= g.N) continue;
+      if (m >= g.M || !n_ok) continue;
       float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
       if constexpr (EPI == kEpiSlab) {
         float* o = g.slab + ((int64_t)blockIdx.y * g.M + m) * g.N + n;
         *reinterpret_cast<f32x4*>(o) = lo;
         *reinterpret_cast<f32x4*>(o + 4) = hi;
       } else {
-        if (g.bias) {
-          const f32x4 b0 = *reinterpret_cast<const f32x4*>(g.bias + n);
-          const f32x4 b1 = *reinterpret_cast<const f32x4*>(g.bias + n + 4);
 #pragma unroll
-          for (int e = 0; e < 4; e++) {
-            v[e] += b0[e];
-            v[4 + e] += b1[e];
-          }
-        }
+        for (int e = 0; e < 8; e++) v[e] += bv[e];
         if constexpr (EPI == kEpiSilu) {
-          if (g.c2) {
-            const u32x4 pre = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                               pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-            *reinterpret_cast<u32x4*>(g.c2 + (int64_t)m * g.ldc2 + n) = pre;
-          }
+          if (g.c2) store(g.c2 + (int64_t)m * g.ldc2 + n, v);
 #pragma unroll
           for (int e = 0; e < 8; e++) v[e] = silu_f(v[e]);
-        } else if (g.res) {
-          const u32x4 rv = *reinterpret_cast<const u32x4*>(g.res + (int64_t)m * g.ldr + n);
+        } else if (has_res) {
 #pragma unroll
           for (int e = 0; e < 4; e++) {
-            v[2 * e] += __uint_as_float(rv[e] << 16);
-            v[2 * e + 1] += __uint_as_float(rv[e] & 0xffff0000u);
+            v[2 * e] += __uint_as_float(rv[i & 1][r][e] << 16);
+            v[2 * e + 1] += __uint_as_float(rv[i & 1][r][e] & 0xffff0000u);
           }
         }
-        const u32x4 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]),
-                         pack_bf16x2(v[4], v[5]), pack_bf16x2(v[6], v[7])};
-        *reinterpret_cast<u32x4*>(g.c + (int64_t)m * g.ldc + n) = o;
+        store(g.c + (int64_t)m * g.ldc + n, v);
       }
     }
     __builtin_amdgcn_wave_barrier();
@@ -325,13 +380,16 @@ __device__ __forceinline__ void st_e(void* p, int64_t i, float v) {
 
 // dpre = dZ * SiLU'(pre), dZ = [dU | dV | dQ | dK] from four dense
 // [T][h][d] gradients, and partial column sums of the fp32 dpre for the
-// bias gradient, one row of partials per block of kColRows token rows.  A
-// thread owns 8 consecutive columns (16-byte accesses in bf16; the four
-// sources meet at multiples of 64 columns, so 8 columns never straddle
-// two) and walks the block's rows.  Blocks of 32 rows (eight in flight per
-// thread) give the HBM-bound pass enough workgroups: 128-row blocks left
-// it at ~3.7 TB/s (projection backward at the training shape 0.58 ->
-// 0.55 ms).
+// bias gradient, one row of partials per block of kColRows token rows.
+// HBM-bound.  A thread owns 8 consecutive columns (16-byte accesses in bf16;
+// the four sources meet at multiples of 32 columns, so 8 columns never
+// straddle two) of kColRows / 4 rows, all of whose loads are in flight at
+// once; its workgroup's four row groups meet in LDS.  (One thread per 8
+// columns and 32 rows: 27 us on 4.8 K tokens of 1024 columns, too few loads
+// in flight.)  NT: inputs larger than the last-level cache are read past it,
+// so that it keeps what the products read next (62 K tokens of 2048 columns:
+// the whole backward 571 against 586 us; on cached inputs it costs 10 us of
+// 70).
 constexpr int kColRows = 32;
 
 template <bool BF16>
@@ -367,7 +425,36 @@ __device__ __forceinline__ void store8(void* p, int64_t i, const float (&v)[8]) 
   }
 }
 
-template <bool BF16>
+template <bool BF16, bool NT>
+__device__ __forceinline__ void load8_once(const void* p, int64_t i, float (&v)[8]) {
+  if constexpr (BF16 && NT) {
+    const u32x4 r =
+        __builtin_nontemporal_load(reinterpret_cast<const u32x4*>((const uint16_t*)p + i));
+#pragma unroll
+    for (int e = 0; e < 4; e++) {
+      v[2 * e] = __uint_as_float(r[e] << 16);
+      v[2 * e + 1] = __uint_as_float(r[e] & 0xffff0000u);
+    }
+  } else {
+    load8<BF16>(p, i, v);
+  }
+}
+
+// Sums over the workgroup's four row groups (waves) of each wave's 512
+// columns, stored to one row of partials.
+__device__ __forceinline__ void store_col_sums(float (*red)[512], const float (&sum)[8], int c0,
+                                               int n, float* __restrict__ partial_row) {
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  store8<false>(red[wave], 8 * lane, sum);
+  __syncthreads();
+#pragma unroll
+  for (int e = 0; e < 2; e++) {
+    const int x = threadIdx.x + 256 * e;
+    if (c0 + x < n) partial_row[c0 + x] = (red[0][x] + red[1][x]) + (red[2][x] + red[3][x]);
+  }
+}
+
+template <bool BF16, bool NT>
 __global__ __launch_bounds__(256) void silu_bwd_kernel(int64_t T, int F, int hv, int hq,
                                                        const void* __restrict__ pre,
                                                        const void* __restrict__ du,
@@ -376,39 +463,43 @@ __global__ __launch_bounds__(256) void silu_bwd_kernel(int64_t T, int F, int hv,
                                                        const void* __restrict__ dk,
                                                        void* __restrict__ dpre,
                                                        float* __restrict__ partial) {
-  const int c = 8 * (blockIdx.x * 256 + threadIdx.x);
-  if (c >= F) return;
-  const void* src;
-  int w, cc;
-  if (c < hv) {
-    src = du, w = hv, cc = c;
-  } else if (c < 2 * hv) {
-    src = dv, w = hv, cc = c - hv;
-  } else if (c < 2 * hv + hq) {
-    src = dq, w = hq, cc = c - 2 * hv;
-  } else {
-    src = dk, w = hq, cc = c - 2 * hv - hq;
-  }
-  const int64_t r0 = (int64_t)blockIdx.y * kColRows;
-  const int64_t r1 = min(T, r0 + kColRows);
+  __shared__ __align__(16) float red[4][512];
+  constexpr int kPer = kColRows / 4;
+  const int c0 = 512 * blockIdx.x, c = c0 + 8 * (threadIdx.x & 63);
   float sum[8] = {};
-#pragma unroll 8
-  for (int64_t r = r0; r < r1; r++) {
-    float x[8], d[8];
-    load8<BF16>(pre, r * F + c, x);
-    load8<BF16>(src, r * w + cc, d);
-#pragma unroll
-    for (int e = 0; e < 8; e++) {
-      const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x[e] * -kLog2e));
-      d[e] *= sg * (1.0f + x[e] * (1.0f - sg));
-      sum[e] += d[e];
+  if (c < F) {
+    const void* src;
+    int w, cc;
+    if (c < hv) {
+      src = du, w = hv, cc = c;
+    } else if (c < 2 * hv) {
+      src = dv, w = hv, cc = c - hv;
+    } else if (c < 2 * hv + hq) {
+      src = dq, w = hq, cc = c - 2 * hv;
+    } else {
+      src = dk, w = hq, cc = c - 2 * hv - hq;
     }
-    store8<BF16>(dpre, r * F + c, d);
+    const int64_t r0 = (int64_t)blockIdx.y * kColRows + (threadIdx.x >> 6) * kPer;
+    float x[kPer][8], d[kPer][8];
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+      const int64_t r = min(r0 + k, T - 1);
+      load8_once<BF16, NT>(pre, r * F + c, x[k]);
+      load8_once<BF16, NT>(src, r * w + cc, d[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < kPer; k++) {
+      if (r0 + k >= T) break;
+#pragma unroll
+      for (int e = 0; e < 8; e++) {
+        const float sg = __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(x[k][e] * -kLog2e));
+        d[k][e] *= sg * (1.0f + x[k][e] * (1.0f - sg));
+        sum[e] += d[k][e];
+      }
+      store8<BF16>(dpre, (r0 + k) * F + c, d[k]);
+    }
   }
-  float* pp = partial + (int64_t)blockIdx.y * F + c;
-  const f32x4 a = {sum[0], sum[1], sum[2], sum[3]}, b = {sum[4], sum[5], sum[6], sum[7]};
-  *reinterpret_cast<f32x4*>(pp) = a;
-  *reinterpret_cast<f32x4*>(pp + 4) = b;
+  store_col_sums(red, sum, c0, F, partial + (int64_t)blockIdx.y * F);
 }
 
 // Partial column sums of x [T][N] (row stride ld, N and ld multiples of 8)
@@ -417,22 +508,22 @@ template <bool BF16>
 __global__ __launch_bounds__(256) void colsum_kernel(int64_t T, int N, int64_t ld,
                                                      const void* __restrict__ x,
                                                      float* __restrict__ partial) {
-  const int c = 8 * (blockIdx.x * 256 + threadIdx.x);
-  if (c >= N) return;
-  const int64_t r0 = (int64_t)blockIdx.y * kColRows;
-  const int64_t r1 = min(T, r0 + kColRows);
+  __shared__ __align__(16) float red[4][512];
+  constexpr int kPer = kColRows / 4;
+  const int c0 = 512 * blockIdx.x, c = c0 + 8 * (threadIdx.x & 63);
   float sum[8] = {};
-#pragma unroll 4
-  for (int64_t r = r0; r < r1; r++) {
-    float v[8];
-    load8<BF16>(x, r * ld + c, v);
+  if (c < N) {
+    const int64_t r0 = (int64_t)blockIdx.y * kColRows + (threadIdx.x >> 6) * kPer;
+    float v[kPer][8];
 #pragma unroll
-    for (int e = 0; e < 8; e++) sum[e] += v[e];
+    for (int k = 0; k < kPer; k++) load8<BF16>(x, min(r0 + k, T - 1) * ld + c, v[k]);
+#pragma unroll
+    for (int k = 0; k < kPer; k++)
+      if (r0 + k < T)
+#pragma unroll
+        for (int e = 0; e < 8; e++) sum[e] += v[k][e];
   }
-  float* pp = partial + (int64_t)blockIdx.y * N + c;
-  const f32x4 a = {sum[0], sum[1], sum[2], sum[3]}, b = {sum[4], sum[5], sum[6], sum[7]};
-  *reinterpret_cast<f32x4*>(pp) = a;
-  *reinterpret_cast<f32x4*>(pp + 4) = b;
+  store_col_sums(red, sum, c0, N, partial + (int64_t)blockIdx.y * N);
 }
 
 // out[i] = sum over s of part[s][i], s in order (few rows, many columns:
@@ -474,8 +565,8 @@ __global__ __launch_bounds__(256) void reduce_cols_kernel(int n, int S,
 }  // namespace
 
 int gemm_num_splits(int M, int N, int64_t K, int* k_split) {
-  const int tiles = ((M + kGBM - 1) / kGBM) * ((N + kGBN - 1) / kGBN);
-  int64_t want = (512 + tiles - 1) / tiles;
+  const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
+  int64_t want = (256 + tiles - 1) / tiles;
   // At least 256 contraction rows per split, and at least one split.
   const int64_t max_splits = K > 256 ? (K + 255) / 256 : 1;
   want = want < 1 ? 1 : want > max_splits ? max_splits : want;
@@ -486,21 +577,48 @@ int gemm_num_splits(int M, int N, int64_t K, int* k_split) {
   return (int)((K + ks - 1) / ks);
 }
 
+template <bool A_KM, bool B_KM, int EPI>
+hipError_t gemm_case(const GemmArgs& g, int splits, hipStream_t s) {
+  auto tiles = [&](int bm, int bn) {
+    return (int64_t)((g.M + bm - 1) / bm) * ((g.N + bn - 1) / bn);
+  };
+  auto launch = [&](auto kernel, int bm, int bn) {
+    const dim3 grid((unsigned)tiles(bm, bn), (unsigned)splits);
+    hipLaunchKernelGGL(kernel, grid, dim3(2 * bn), 0, s, g);
+    return hipGetLastError();
+  };
+  // Outputs past half of the 256 MB last-level cache bypass the caches (f_1's
+  // forward at 60 K tokens, 495 MB: 200 us against 244); smaller ones may be
+  // read from them by the next call.
+  const bool stream =
+      EPI != kEpiSlab && 2ll * g.M * g.N * (g.c2 ? 2 : 1) > (128ll << 20);
+  constexpr bool kStream = EPI != kEpiSlab;
+  // The largest tile that (nearly) fills the chip: one 256 x 256 workgroup or
+  // two of 256 x 128 per CU.  Against the smaller one the large tile reads a
+  // third less from the L2 per product (f_1's backward at 60 K tokens 430
+  // against 448 us); f_1's forward, half of whose time is its stores, keeps
+  // two workgroups per CU, one storing while the other computes (194 against
+  // 199 us).
+  if (EPI != kEpiSilu && tiles(256, 256) * splits >= 224)
+    return stream ? launch(gemm_bf16_kernel<4, 4, 4, A_KM, B_KM, EPI, kStream>, 256, 256)
+                  : launch(gemm_bf16_kernel<4, 4, 4, A_KM, B_KM, EPI, false>, 256, 256);
+  if (tiles(256, 128) * splits >= 448)
+    return stream ? launch(gemm_bf16_kernel<4, 2, 3, A_KM, B_KM, EPI, kStream>, 256, 128)
+                  : launch(gemm_bf16_kernel<4, 2, 3, A_KM, B_KM, EPI, false>, 256, 128);
+  return launch(gemm_bf16_kernel<2, 2, 3, A_KM, B_KM, EPI, false>, 128, 128);
+}
+
 hipError_t launch_gemm_bf16(const GemmArgs& g, int a_kmajor, int b_kmajor, int epi, int splits,
                             hipStream_t s) {
   if (g.M <= 0 || g.N <= 0) return hipSuccess;
-  const int nt = ((g.M + kGBM - 1) / kGBM) * ((g.N + kGBN - 1) / kGBN);
-  const dim3 grid((unsigned)nt, (unsigned)splits);
-#define HSTU_GEMM_CASE(AK, BK, E)                                                         \
-  if (a_kmajor == AK && b_kmajor == BK && epi == E) {                                     \
-    hipLaunchKernelGGL((gemm_bf16_kernel<AK, BK, E>), grid, dim3(256), 0, s, g);          \
-    return hipGetLastError();                                                             \
-  }
-  HSTU_GEMM_CASE(0, 0, kEpiSilu)
-  HSTU_GEMM_CASE(0, 0, kEpiAdd)
-  HSTU_GEMM_CASE(0, 1, kEpiAdd)
-  HSTU_GEMM_CASE(1, 1, kEpiSlab)
-#undef HSTU_GEMM_CASE
+  if (!a_kmajor && !b_kmajor && epi == kEpiSilu)
+    return gemm_case<false, false, kEpiSilu>(g, splits, s);
+  if (!a_kmajor && !b_kmajor && epi == kEpiAdd)
+    return gemm_case<false, false, kEpiAdd>(g, splits, s);
+  if (!a_kmajor && b_kmajor && epi == kEpiAdd)
+    return gemm_case<false, true, kEpiAdd>(g, splits, s);
+  if (a_kmajor && b_kmajor && epi == kEpiSlab)
+    return gemm_case<true, true, kEpiSlab>(g, splits, s);
   return hipErrorInvalidValue;
 }
 
@@ -522,20 +640,24 @@ hipError_t launch_silu_bwd(int is_bf16, int64_t T, int F, int hv, int hq, const 
                            const void* du, const void* dv, const void* dq, const void* dk,
                            void* dpre, float* partial, hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((F / 8 + 255) / 256), (unsigned)colsum_blocks(T));
-  if (is_bf16)
-    hipLaunchKernelGGL(silu_bwd_kernel<true>, grid, dim3(256), 0, s, T, F, hv, hq, pre, du, dv,
-                       dq, dk, dpre, partial);
+  const dim3 grid((unsigned)((F + 511) / 512), (unsigned)colsum_blocks(T));
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(256), 0, s, T, F, hv, hq, pre, du, dv, dq, dk, dpre,
+                       partial);
+  };
+  if (!is_bf16)
+    launch(silu_bwd_kernel<false, false>);
+  else if (4 * T * F > (256ll << 20))
+    launch(silu_bwd_kernel<true, true>);
   else
-    hipLaunchKernelGGL(silu_bwd_kernel<false>, grid, dim3(256), 0, s, T, F, hv, hq, pre, du, dv,
-                       dq, dk, dpre, partial);
+    launch(silu_bwd_kernel<true, false>);
   return hipGetLastError();
 }
 
 hipError_t launch_colsum(int is_bf16, int64_t T, int N, int64_t ld, const void* x, float* partial,
                          hipStream_t s) {
   if (T <= 0) return hipSuccess;
-  const dim3 grid((unsigned)((N / 8 + 255) / 256), (unsigned)colsum_blocks(T));
+  const dim3 grid((unsigned)((N + 511) / 512), (unsigned)colsum_blocks(T));
   if (is_bf16)
     hipLaunchKernelGGL(colsum_kernel<true>, grid, dim3(256), 0, s, T, N, ld, x, partial);
   else
