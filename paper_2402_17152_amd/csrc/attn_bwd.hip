@@ -480,6 +480,11 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
       }
     }
   };
+  // Rows that keep the lane's key: my_j .. L-1 for a history key, itself for
+  // a candidate; one unsigned compare (the mask's conditions as a
+  // short-circuit cost jumps for every pair of a masked tile).
+  const uint32_t keep_count = !key_ok ? 0u : my_j < n_h ? (uint32_t)(L - my_j) : 1u;
+  auto pair_kept = [&](int i) -> bool { return (uint32_t)(i - my_j) < keep_count; };
   auto seed = [&](int u, const Path& pth, f32x16& acc) {
     if (pth.kind() == kUniform) {
       float w[16];
@@ -503,7 +508,7 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
 #pragma unroll
       for (int q = 0; q < 16; q++) {
         const int i = i0 + 8 * (q >> 2) + 4 * half + (q & 3);
-        ok[q] = key_ok && i < L && pair_valid(i, my_j, n_h);
+        ok[q] = pair_kept(i);
         y[q] = ok[q] ? (Pk - pj) + (bias_pos(i, n_h) - pi0) : 0;
       }
       float w[16], tv[16];
@@ -714,7 +719,7 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
       for (int q = 0; q < 16; q++) {
         const int i = i0 + 8 * (q >> 2) + 4 * half + (q & 3);
         dh[q] = i < n_h ? ds[q] : 0.0f;
-        if (i >= n_h && i < L && key_ok && pair_valid(i, my_j, n_h)) cs += ds[q];
+        cs += ((i >= n_h) & pair_kept(i)) ? ds[q] : 0.0f;
       }
       *cand_sum += cs;
       pos_step(u, dh);
@@ -958,9 +963,6 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
                                            const RsItem& it, int64_t tbase) {
   using Sh = BwdSharedRS<DQK, DV, SPLIT>;
   constexpr bool CF = TGT && !SPLIT;
-  // Masked tiles of history rows read the position window as full tiles
-  // do, where registers allow: at d_qk or d_v = 128 the other form spills.
-  constexpr bool kMaskedWindowReads = DQK <= 64 && DV <= 64;
   using QT = typename Sh::QT;
   using OT = typename Sh::OT;
   constexpr int BN = Sh::BN, BM = Sh::BM, DST_LD = Sh::DST_LD, kSlots = Sh::kSlots;
@@ -1188,6 +1190,11 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
       win_reads(u, w);
     }
   };
+  // Rows that keep the lane's key: my_j .. L-1 for a history key, itself for
+  // a candidate; one unsigned compare (the mask's conditions as a
+  // short-circuit cost jumps for every pair of a masked tile).
+  const uint32_t keep_count = !key_ok ? 0u : my_j < n_h ? (uint32_t)(L - my_j) : 1u;
+  auto pair_kept = [&](int i) -> bool { return (uint32_t)(i - my_j) < keep_count; };
   auto seed = [&](int u, const Path& pth, f32x16& acc) {
     if (pth.kind() == kUniform) {
       float w[16];
@@ -1202,7 +1209,7 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
       const uint32_t lim = tjr + pth.thr();
 #pragma unroll
       for (int q = 0; q < 16; q++) acc[q] = w[q] + (ti[q] >= lim ? pth.cb_far : pth.cb);
-    } else if (kMaskedWindowReads && (!TGT || row0(u) + BM - 1 < n_h)) {
+    } else if (!TGT || row0(u) + BM - 1 < n_h) {
       // Masked or ragged pairs of history rows (position = index): the
       // window reads of full tiles, then the mask.
       const int i0 = row0(u);
@@ -1215,7 +1222,7 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
 #pragma unroll
       for (int q = 0; q < 16; q++) {
         const int i = i0 + 8 * (q >> 2) + 4 * half + (q & 3);
-        acc[q] = key_ok && i < L && pair_valid(i, my_j, n_h) ? w[q] + tv[q] : kMaskedBias;
+        acc[q] = pair_kept(i) ? w[q] + tv[q] : kMaskedBias;
       }
     } else {
       const int i0 = row0(u), pi0 = min(i0, n_h);
@@ -1226,7 +1233,7 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
 #pragma unroll
       for (int q = 0; q < 16; q++) {
         const int i = i0 + 8 * (q >> 2) + 4 * half + (q & 3);
-        ok[q] = key_ok && i < L && pair_valid(i, my_j, n_h);
+        ok[q] = pair_kept(i);
         y[q] = ok[q] ? (Pk - pj) + (bias_pos(i, n_h) - pi0) : 0;
       }
       float w[16], tv[16];
@@ -1353,7 +1360,7 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
       for (int q = 0; q < 16; q++) {
         const int i = i0 + 8 * (q >> 2) + 4 * half + (q & 3);
         dh[q] = i < n_h ? ds[q] : 0.0f;
-        if (i >= n_h && i < L && key_ok && pair_valid(i, my_j, n_h)) cs += ds[q];
+        cs += ((i >= n_h) & pair_kept(i)) ? ds[q] : 0.0f;
       }
       *cand_sum += cs;
       if (CF && i0 >= n_h) {
