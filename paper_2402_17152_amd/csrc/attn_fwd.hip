@@ -45,8 +45,6 @@ namespace hstu {
 
 namespace {
 
-constexpr int64_t kI64Max = 0x7fffffffffffffffll;
-constexpr int64_t kI64Min = -kI64Max - 1;
 // Bias of a masked pair: SiLU(x) with x ~ -1e30 evaluates to exactly -0
 // (exp2 overflows to +inf, its reciprocal is 0).
 constexpr float kMaskedBias = -1.0e30f;
@@ -80,7 +78,6 @@ struct FwdShared {
   __align__(16) float sWin[3][4][WIN_LD];
   __align__(16) uint32_t sT[8][64];  // the tile's 32 int64 key timestamps
   __align__(16) uint32_t sTr[8][32];  // the same rebased to 32 bits (fast path)
-  uint32_t sKr32[4][2];              // rebased key timestamp min / max per tile
   float sTab[64];                    // time bias by slot (bias.h)
 };
 
@@ -106,8 +103,6 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
                                          int kt0, int kt1, int i0, int head, int64_t tbase) {
   using Sh = FwdShared<DQK, DV>;
   constexpr int BM = Sh::BM, BN = Sh::BN, K_LD = Sh::K_LD, V_LD = Sh::V_LD;
-  constexpr int KCH = BN * DQK / 8, VCH = BN * DV / 8;
-  constexpr int KPT = (KCH + 255) / 256, VPT = (VCH + 255) / 256;
   static_assert(BN == 32 && BM == 128, "4 waves x 32 rows, 32-key tiles");
   const int H = ja.num_heads, N = ja.max_seq_len;
   const int rows_end = min(i0 + BM, L);
@@ -133,10 +128,12 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     qf[s] = row_ok ? *reinterpret_cast<const u32x4*>(qg + (orow + my_i) * t.q_stride + head * DQK +
                                                      16 * s + 8 * half)
                    : zero_u32x4();
-  const int64_t ti64 = row_ok ? ts[my_i] : tbase;
+  // (rows past the sequence end: the last row's, so that they do not widen
+  // the wave's range)
+  const int64_t ti64 = ts[min(my_i, L - 1)];
   const uint32_t tir = (uint32_t)(ti64 - tbase);
   const int pi = bias_pos(my_i, n_h);
-  // Timestamp range of the wave's rows (used by full tiles, whose rows are all valid).
+  // Timestamp range of the wave's rows.
   const int64_t rlo = wave_min_i64(ti64), rhi = wave_max_i64(ti64);
   const uint32_t rlo32 = __builtin_amdgcn_readfirstlane((uint32_t)(rlo - tbase));
   const uint32_t rhi32 = __builtin_amdgcn_readfirstlane((uint32_t)(rhi - tbase));
@@ -230,36 +227,51 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
   auto issue_ts = [&](int u) {
     dma_to_lds4(trs, sm.sT[u & 7], (uint32_t)(kb_of(u) * BN) * 8u + 4u * (uint32_t)lane);
   };
-  // Wave 0: rebased min / max of a staged tile's key timestamps (zeros past
-  // the sequence end only enter ranges of tiles that are never full).
-  auto reduce_ts = [&](int u) {
-    if constexpr (FAST) {
-      if (wave == 0) {
-        const uint32_t v = sm.sT[u & 7][2 * (lane & 31)] - (uint32_t)tbase;
-        uint32_t lo = v, hi = v;
-        // Rows of 16 lanes by rotation, then the first two rows (the upper
-        // half of the wave holds the same values): by LDS permutes this
-        // stood in every step's chain (target-aware forward 232 -> 218 us).
-        auto ror = [](uint32_t x, auto n) {
-          return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + decltype(n)::value, 0xf,
-                                                       0xf, true);
-        };
-        auto fold = [&](auto n) {
-          lo = min(lo, ror(lo, n));
-          hi = max(hi, ror(hi, n));
-        };
-        fold(std::integral_constant<int, 8>{});
-        fold(std::integral_constant<int, 4>{});
-        fold(std::integral_constant<int, 2>{});
-        fold(std::integral_constant<int, 1>{});
-        lo = min((uint32_t)__builtin_amdgcn_readlane((int)lo, 0),
-                 (uint32_t)__builtin_amdgcn_readlane((int)lo, 16));
-        hi = max((uint32_t)__builtin_amdgcn_readlane((int)hi, 0),
-                 (uint32_t)__builtin_amdgcn_readlane((int)hi, 16));
-        sm.sTr[u & 7][lane & 31] = v;
-        if (lane < 2) sm.sKr32[u & 3][lane] = lane ? hi : lo;
-      }
-    }
+  // Range of a tile's rebased key timestamps (zeros past the sequence end only
+  // enter ranges of tiles that are never full), from the lane's one of them.
+  // Every wave folds its own: lane rotations in rows of 16, then the first
+  // two rows (the upper half of the wave holds the same values).  Against one
+  // wave folding for all, through LDS: 137 against 141 us on a sequence of
+  // 5041 tokens, level on full batches.
+  struct Range {
+    uint32_t lo, hi;
+  };
+  auto fold_range = [&](uint32_t v) -> Range {
+    uint32_t lo = v, hi = v;
+    auto ror = [](uint32_t x, auto n) {
+      return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + decltype(n)::value, 0xf, 0xf,
+                                                   true);
+    };
+    auto fold = [&](auto n) {
+      lo = min(lo, ror(lo, n));
+      hi = max(hi, ror(hi, n));
+    };
+    fold(std::integral_constant<int, 8>{});
+    fold(std::integral_constant<int, 4>{});
+    fold(std::integral_constant<int, 2>{});
+    fold(std::integral_constant<int, 1>{});
+    auto lane_of = [](uint32_t x, int l) { return __builtin_amdgcn_readlane((int)x, l); };
+    // (of full tiles, which are the only ones whose range is used, every
+    // value is below 2^31)
+    return Range{(uint32_t)min(lane_of(lo, 0), lane_of(lo, 16)),
+                 (uint32_t)max(lane_of(hi, 0), lane_of(hi, 16))};
+  };
+  // The lane's rebased timestamp of tile u; wave 0 keeps them for the
+  // per-pair paths.
+  auto tile_ts = [&](int u) -> uint32_t {
+    if constexpr (FAST)
+      return sm.sT[u & 7][2 * (lane & 31)] - (uint32_t)tbase;
+    else
+      return 0;
+  };
+  auto keep_ts = [&](int u, uint32_t v) {
+    if constexpr (FAST)
+      if (wave == 0) sm.sTr[u & 7][lane & 31] = v;
+  };
+  // Lane x holds the time bias of slot x: a uniform slot's is one readlane.
+  const int tab_reg = __float_as_int(sm.sTab[lane]);
+  auto tab_at = [&](int slot) {
+    return __int_as_float(__builtin_amdgcn_readlane(tab_reg, slot));
   };
 
   // ---- bias path of tile u for this wave, decided two steps ahead ----
@@ -270,19 +282,23 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
   // time term is a select on t_j <= t_i - 2^(b+1) ("two").  Everything
   // else evaluates each pair ("general").
   enum { kUniform = 0, kTwo = 1, kGeneral = 2 };
-  // Full tile: every pair valid, either history rows after every key
-  // (j0 + BN - 1 <= iw0), or candidate rows (all at position n_h) against
-  // history keys (j0 + BN - 1 < n_h); a wave mixing both has none.  Either
-  // way the tiles with j0 <= full_lim (wave-uniform).
+  // Full tile: every pair of the wave's existing rows valid, either history
+  // rows after every key (j0 + BN - 1 <= iw0), or candidate rows (all at
+  // position n_h) against history keys (j0 + BN - 1 < n_h); a wave mixing
+  // both has none.  Either way the tiles with j0 <= full_lim (wave-uniform).
+  // Rows past the sequence end go along (their window reads stay inside, and
+  // their outputs are not stored): as a reason for the per-pair path they
+  // slowed every tile of a ragged sequence's last, longest block (a sequence
+  // of 5041 tokens: 180 -> 137 us; 32 sequences of 8-1024 45 -> 39).
   const int full_lim = __builtin_amdgcn_readfirstlane(
-      iw0 + 31 >= L ? -1 : iw0 + 31 < n_h ? iw0 - (BN - 1) : iw0 >= n_h ? n_h - BN : -1);
+      wave_last < n_h ? iw0 - (BN - 1) : iw0 >= n_h ? n_h - BN : -1);
   auto full_tile = [&](int j0) { return j0 <= full_lim; };
   struct Path {
     int kind;
     float cb, cb_far;  // time term (nearer bucket) and, for "two", the farther one
     int thr;           // 2^(b+1) for "two"
   };
-  auto classify = [&](int u) -> Path {
+  auto classify = [&](int u, uint32_t ts_u) -> Path {
     Path r{kGeneral, 0.0f, 0.0f, 0};
     if (u >= n) {
       r.kind = kUniform;  // past the end: the seed is computed but never used
@@ -292,8 +308,8 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     const bool full = full_tile(j0);
     if constexpr (FAST) {
       if (full) {
-        const uint32_t klo = __builtin_amdgcn_readfirstlane(sm.sKr32[u & 3][0]);
-        const uint32_t khi = __builtin_amdgcn_readfirstlane(sm.sKr32[u & 3][1]);
+        const Range kr = fold_range(ts_u);
+        const uint32_t klo = kr.lo, khi = kr.hi;
         const bool ordered = rlo32 >= khi;
         uint32_t dmin, dmax;
         if (ordered) {
@@ -310,11 +326,11 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
         const int bnear = 31 - __clz((int)(dmin | 1u)), bfar = 31 - __clz((int)(dmax | 1u));
         if (bnear == bfar) {
           r.kind = kUniform;
-          r.cb = sm.sTab[63 - bnear];
+          r.cb = tab_at(63 - bnear);
         } else if (ordered && bfar == bnear + 1) {
           r.kind = kTwo;
-          r.cb = sm.sTab[63 - bnear];
-          r.cb_far = sm.sTab[63 - bfar];
+          r.cb = tab_at(63 - bnear);
+          r.cb_far = tab_at(63 - bfar);
           r.thr = 1 << bfar;
         }
       }
@@ -525,6 +541,8 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     issue_win(u + 3);
     issue_v(u + 2);
     issue_ts(u + 5);
+    const uint32_t ts_ahead = tile_ts(u + 2);
+    keep_ts(u + 2, ts_ahead);
     if (path_next.kind == kUniform)
       seed_uniform(u + 1, path_next.cb, s_next);
     else if (path_next.kind == kTwo)
@@ -538,12 +556,11 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     // towards its use in the next step, away from the MFMAs).
     asm volatile("" ::"v"(p_cur[0]), "v"(p_cur[1]));
     if constexpr (SPLIT) asm volatile("" ::"v"(p_cur[2]), "v"(p_cur[3]));
-    path_next = classify(u + 2);
-    reduce_ts(u + 3);
+    path_next = classify(u + 2, ts_ahead);
   };
 
-  // Prologue: stage timestamps 0..4, K / window 0..2, V 0..1; key ranges
-  // of tiles 0..2; then tile 0 is scored.
+  // Prologue: stage timestamps 0..4, K / window 0..2, V 0..1; then tile 0 is
+  // scored.
   for (int v = 0; v < 5; v++) issue_ts(v);
   for (int v = 0; v < 3; v++) {
     issue_k(v);
@@ -553,13 +570,15 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
   issue_v(1);
   wait_vmcnt_lgkmcnt0<0>();
   barrier_no_fence();
-  for (int v = 0; v < 3; v++) reduce_ts(v);
+  const uint32_t ts_0 = tile_ts(0), ts_1 = tile_ts(1);
+  keep_ts(0, ts_0);
+  keep_ts(1, ts_1);
   wait_vmcnt_lgkmcnt0<0>();
   barrier_no_fence();
   f32x16 sA, sB;
   u32x4 pA[NPA], pB[NPA];
   {
-    const Path p0 = classify(0);
+    const Path p0 = classify(0, ts_0);
     if (p0.kind == kUniform)
       seed_uniform(0, p0.cb, sA);
     else if (p0.kind == kTwo)
@@ -568,7 +587,7 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
       seed_general(0, sA);
     score(0, sA);
   }
-  path_next = classify(1);
+  path_next = classify(1, ts_1);
   step(std::false_type{}, 0, sA, sB, pB, pA);
   int u = 1;
   for (; u + 1 < n; u += 2) {
