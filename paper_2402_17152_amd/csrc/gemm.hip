@@ -527,14 +527,27 @@ __global__ __launch_bounds__(256) void colsum_kernel(int64_t T, int N, int64_t l
 }
 
 // out[i] = sum over s of part[s][i], s in order (few rows, many columns:
-// the split-K slabs).
+// the split-K slabs), n a multiple of 4.  Four columns per thread and eight
+// slabs' loads in flight: one column and one load at a time took 7 us for 19
+// slabs of 1 MB.
 __global__ __launch_bounds__(256) void reduce_slabs_kernel(int64_t n, int S,
                                                            const float* __restrict__ part,
                                                            float* __restrict__ out) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256) {
-    float s = 0.0f;
-    for (int k = 0; k < S; k++) s += part[(int64_t)k * n + i];
-    out[i] = s;
+  for (int64_t i = 4 * ((int64_t)blockIdx.x * 256 + threadIdx.x); i < n;
+       i += 4 * (int64_t)gridDim.x * 256) {
+    f32x4 s = {0.0f, 0.0f, 0.0f, 0.0f};
+    int k = 0;
+    for (; k + 8 <= S; k += 8) {
+      f32x4 v[8];
+#pragma unroll
+      for (int e = 0; e < 8; e++)
+        v[e] = *reinterpret_cast<const f32x4*>(part + (int64_t)(k + e) * n + i);
+#pragma unroll
+      for (int e = 0; e < 8; e++) s += v[e];
+    }
+#pragma unroll 4
+    for (; k < S; k++) s += *reinterpret_cast<const f32x4*>(part + (int64_t)k * n + i);
+    *reinterpret_cast<f32x4*>(out + i) = s;
   }
 }
 
@@ -674,7 +687,7 @@ hipError_t launch_reduce_cols(int n, int S, const float* part, float* out, hipSt
 
 hipError_t launch_reduce_slabs(int64_t n, int S, const float* part, float* out, hipStream_t s) {
   if (n <= 0) return hipSuccess;
-  const int64_t blocks = (n + 255) / 256;
+  const int64_t blocks = (n + 1023) / 1024;
   const dim3 grid((unsigned)(blocks < 4096 ? blocks : 4096));
   hipLaunchKernelGGL(reduce_slabs_kernel, grid, dim3(256), 0, s, n, S, part, out);
   return hipGetLastError();
