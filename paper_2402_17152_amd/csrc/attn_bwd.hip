@@ -1103,40 +1103,24 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
     return (i0 + BM - 1 < L) &&
            ((jw0 + 31 <= i0 && i0 + BM - 1 < n_h) || (CF && i0 >= n_h && jw0 + 31 < n_h));
   };
+  // Straight-line scalar code, as in the forward.
   auto classify = [&](int u) -> Path {
-    Path r{kGeneral, 0.0f, 0.0f};
-    if (u >= nsteps) {
-      r.code = kUniform;
-      return r;
+    if constexpr (!FAST) {
+      return Path{u >= nsteps ? kUniform : kGeneral, 0.0f, 0.0f};
+    } else {
+      const uint32_t rlo = __builtin_amdgcn_readfirstlane(sm.sRr[u & 3][0]);
+      const uint32_t rhi = __builtin_amdgcn_readfirstlane(sm.sRr[u & 3][1]);
+      const int after = (int)(rlo - khi32);
+      const int dmin = max(max(after, (int)(klo32 - rhi)), 0);
+      const int dmax = max((int)(rhi - klo32), (int)(khi32 - rlo));
+      const int bnear = 31 - __clz(dmin | 1), bfar = 31 - __clz(dmax | 1);
+      const bool two = (after >= 0) & (bfar == bnear + 1);
+      int kind = bnear == bfar ? kUniform : two ? kTwo : kGeneral;
+      kind = full_tile(row0(u)) ? kind : kGeneral;
+      kind = u >= nsteps ? kUniform : kind;
+      return Path{kind | (63 - bnear) << 2 | (63 - bfar) << 8 | bfar << 14, sm.sTab[63 - bnear],
+                  sm.sTab[63 - bfar]};
     }
-    if constexpr (FAST) {
-      if (full_tile(row0(u))) {
-        const uint32_t rlo = __builtin_amdgcn_readfirstlane(sm.sRr[u & 3][0]);
-        const uint32_t rhi = __builtin_amdgcn_readfirstlane(sm.sRr[u & 3][1]);
-        const bool ordered = rlo >= khi32;
-        uint32_t dmin, dmax;
-        if (ordered) {
-          dmin = rlo - khi32;
-          dmax = rhi - klo32;
-        } else if (klo32 >= rhi) {
-          dmin = klo32 - rhi;
-          dmax = khi32 - rlo;
-        } else {
-          dmin = 0;
-          dmax = max(rhi - klo32, khi32 - rlo);
-        }
-        const int bnear = 31 - __clz((int)(dmin | 1u)), bfar = 31 - __clz((int)(dmax | 1u));
-        if (bnear == bfar) {
-          r.code = kUniform | (63 - bnear) << 2;
-          r.cb = sm.sTab[63 - bnear];
-        } else if (ordered && bfar == bnear + 1) {
-          r.code = kTwo | (63 - bnear) << 2 | (63 - bfar) << 8 | bfar << 14;
-          r.cb = sm.sTab[63 - bnear];
-          r.cb_far = sm.sTab[63 - bfar];
-        }
-      }
-    }
-    return r;
   };
   const int a_y = Pk - my_j + 4 * half;
   auto win_reads = [&](int u, float (&w)[16]) {

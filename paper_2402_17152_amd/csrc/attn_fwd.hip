@@ -298,44 +298,27 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     float cb, cb_far;  // time term (nearer bucket) and, for "two", the farther one
     int thr;           // 2^(b+1) for "two"
   };
+  // Straight-line scalar code (branches for each case cost the target-aware
+  // forward 3 %).
   auto classify = [&](int u, uint32_t ts_u) -> Path {
-    Path r{kGeneral, 0.0f, 0.0f, 0};
-    if (u >= n) {
-      r.kind = kUniform;  // past the end: the seed is computed but never used
-      return r;
+    if constexpr (!FAST) {
+      return Path{u >= n ? kUniform : kGeneral, 0.0f, 0.0f, 0};
+    } else {
+      const Range kr = fold_range(ts_u);
+      // |t_i - t_j| over the tile: [dmin, dmax], all below 2^31.
+      const int after = (int)(rlo32 - kr.hi);  // >= 0: every t_i >= every t_j
+      const int dmin = max(max(after, (int)(kr.lo - rhi32)), 0);
+      const int dmax = max((int)(rhi32 - kr.lo), (int)(kr.hi - rlo32));
+      // floor(log2 |dt|), 0 for |dt| <= 1.
+      const int bnear = 31 - __clz(dmin | 1), bfar = 31 - __clz(dmax | 1);
+      const bool full = full_tile(kb_of(u) * BN);
+      const bool two = (after >= 0) & (bfar == bnear + 1);
+      int kind = bnear == bfar ? kUniform : two ? kTwo : kGeneral;
+      kind = full ? kind : kGeneral;
+      // (past the end: the seed is computed but never used)
+      kind = u >= n ? kUniform : kind;
+      return Path{kind, tab_at(63 - bnear), tab_at(63 - bfar), 1 << bfar};
     }
-    const int j0 = kb_of(u) * BN;
-    const bool full = full_tile(j0);
-    if constexpr (FAST) {
-      if (full) {
-        const Range kr = fold_range(ts_u);
-        const uint32_t klo = kr.lo, khi = kr.hi;
-        const bool ordered = rlo32 >= khi;
-        uint32_t dmin, dmax;
-        if (ordered) {
-          dmin = rlo32 - khi;
-          dmax = rhi32 - klo;
-        } else if (klo >= rhi32) {
-          dmin = klo - rhi32;
-          dmax = khi - rlo32;
-        } else {
-          dmin = 0;
-          dmax = max(rhi32 - klo, khi - rlo32);
-        }
-        // floor(log2 |dt|) over [dmin, dmax] (|dt| <= 1 -> 0); all < 31.
-        const int bnear = 31 - __clz((int)(dmin | 1u)), bfar = 31 - __clz((int)(dmax | 1u));
-        if (bnear == bfar) {
-          r.kind = kUniform;
-          r.cb = tab_at(63 - bnear);
-        } else if (ordered && bfar == bnear + 1) {
-          r.kind = kTwo;
-          r.cb = tab_at(63 - bnear);
-          r.cb_far = tab_at(63 - bfar);
-          r.thr = 1 << bfar;
-        }
-      }
-    }
-    return r;
   };
 
   // Keys the lane's row keeps: j <= keep_lim, and its own if it is a
