@@ -41,8 +41,35 @@ __device__ __forceinline__ int bwd_weight(int L, int n_h, int kb) {
   return ceil_div(i_end - j0, kBwdBM);
 }
 
+// Inclusive prefix sum over the workgroup's threads: shuffles inside a wave,
+// one LDS exchange of the waves' sums (two barriers; a doubling scan through
+// LDS took twenty).  `waves` holds a value per wave and may be used again
+// after the call; *total receives the sum.
+template <typename V>
+__device__ __forceinline__ V block_scan(V v, V* waves, V* total) {
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+  for (int off = 1; off < 64; off <<= 1) {
+    const V x = __shfl_up(v, off, 64);
+    if (lane >= off) v += x;
+  }
+  if (lane == 63) waves[wave] = v;
+  __syncthreads();
+  V before = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < kSchedThreads / 64; w++) {
+    const V x = waves[w];
+    before += w < wave ? x : 0;
+    all += x;
+  }
+  __syncthreads();
+  *total = all;
+  return v + before;
+}
+
 // One workgroup of kSchedThreads builds the whole list; s_bins holds
-// maxw + 1 ints (dynamic LDS), s_scan kSchedThreads.
+// maxw + 1 ints (dynamic LDS), s_scan one per wave.  Bound by latency: a
+// group keeps its first sequence's lengths over both passes.
 __device__ void schedule_block(const JaggedArgs& ja, int mode, WorkItem* items, int32_t* count,
                                int* s_bins, int* s_scan) {
   const int tid = threadIdx.x;
@@ -50,21 +77,27 @@ __device__ void schedule_block(const JaggedArgs& ja, int mode, WorkItem* items, 
   const int maxw = mode == 0 ? ceil_div(ja.max_seq_len, kFwdBN) : ceil_div(ja.max_seq_len, kBwdBM);
   // (cross mode: a chunk's weight is at most kCrossChunk / kFwdBN <= maxw)
   const int nbins = maxw + 1;
-  for (int i = tid; i < nbins; i += kSchedThreads) s_bins[i] = 0;
-  __syncthreads();
-
   // Sequences are handed to groups of G lanes (G a power of two up to a
   // wave, larger for fewer sequences); a group's lanes share its items.
   int G = 1;
   while (G < 64 && G * ja.num_seqs < kSchedThreads) G <<= 1;
   const int group = tid / G, sub = tid % G, ngroups = kSchedThreads / G;
+  const bool cross = mode == 0 && ja.key_offsets;
+  struct Lens {
+    int L, n_h;
+  };
+  auto lens_of = [&](int b) -> Lens {
+    const int L = (int)(ja.seq_offsets[b + 1] - ja.seq_offsets[b]);
+    const int n_h = cross ? (int)(ja.key_offsets[b + 1] - ja.key_offsets[b])
+                          : L - (ja.num_targets ? (int)ja.num_targets[b] : 0);
+    return Lens{L, n_h};
+  };
+  const Lens first = group < ja.num_seqs ? lens_of(group) : Lens{0, 0};
   // Calls f(seq, block, weight) for every item.
   auto for_items = [&](auto&& f) {
     for (int b = group; b < ja.num_seqs; b += ngroups) {
-      const int L = (int)(ja.seq_offsets[b + 1] - ja.seq_offsets[b]);
-      int n_h = L - (ja.num_targets ? (int)ja.num_targets[b] : 0);
-      const bool cross = mode == 0 && ja.key_offsets;
-      if (cross) n_h = (int)(ja.key_offsets[b + 1] - ja.key_offsets[b]);
+      const Lens len = b == group ? first : lens_of(b);
+      const int L = len.L, n_h = len.n_h;
       const int nblk = ceil_div(L, blk);
       // (chunks past key_chunks exist only if n_h >= N: they are not scheduled)
       const int nch = cross ? min(ceil_div(n_h, kCrossChunk), ja.key_chunks) : 1;
@@ -79,6 +112,8 @@ __device__ void schedule_block(const JaggedArgs& ja, int mode, WorkItem* items, 
     }
   };
 
+  for (int i = tid; i < nbins; i += kSchedThreads) s_bins[i] = 0;
+  __syncthreads();
   // Pass 1: histogram of item weights (bin index = maxw - weight, so that
   // an ascending scan orders items by descending weight).
   for_items([&](int, int, int w) { atomicAdd(&s_bins[maxw - w], 1); });
@@ -89,21 +124,14 @@ __device__ void schedule_block(const JaggedArgs& ja, int mode, WorkItem* items, 
   const int lo = tid * per, hi = min(lo + per, nbins);
   int local = 0;
   for (int i = lo; i < hi; i++) local += s_bins[i];
-  s_scan[tid] = local;
-  __syncthreads();
-  for (int off = 1; off < kSchedThreads; off <<= 1) {
-    int v = tid >= off ? s_scan[tid - off] : 0;
-    __syncthreads();
-    s_scan[tid] += v;
-    __syncthreads();
-  }
-  int run = s_scan[tid] - local;
+  int items_total;
+  int run = block_scan(local, s_scan, &items_total) - local;
   for (int i = lo; i < hi; i++) {
     int c = s_bins[i];
     s_bins[i] = run;
     run += c;
   }
-  if (tid == kSchedThreads - 1) *count = s_scan[tid];
+  if (tid == 0) *count = items_total;
   __syncthreads();
 
   // Pass 2: scatter the items to their sorted positions.
@@ -125,7 +153,7 @@ __global__ void fill_f32_kernel(float* p, int64_t n, float value) {
 // when square_of_diff (pair offsets of the bucket matrices).
 __global__ __launch_bounds__(kSchedThreads) void cumsum_kernel(int32_t n, const int64_t* in,
                                                                int64_t* out, int square_of_diff) {
-  __shared__ int64_t s[kSchedThreads];
+  __shared__ int64_t s[kSchedThreads / 64];
   const int tid = threadIdx.x;
   int64_t carry = 0;
   if (tid == 0) out[0] = 0;
@@ -140,17 +168,9 @@ __global__ __launch_bounds__(kSchedThreads) void cumsum_kernel(int32_t n, const 
         x = in[i];
       }
     }
-    s[tid] = x;
-    __syncthreads();
-    for (int off = 1; off < kSchedThreads; off <<= 1) {
-      int64_t v = tid >= off ? s[tid - off] : 0;
-      __syncthreads();
-      s[tid] += v;
-      __syncthreads();
-    }
-    if (i < n) out[i + 1] = carry + s[tid];
-    int64_t total = s[kSchedThreads - 1];
-    __syncthreads();
+    int64_t total;
+    const int64_t sum = block_scan(x, s, &total);
+    if (i < n) out[i + 1] = carry + sum;
     carry += total;
   }
 }
@@ -254,7 +274,8 @@ __device__ void fill_blocks(const PrepFills& fills, int f, int nf) {
 // sum over b' < b of ceil(L/32) (row blocks), bases[B + 1 + b] = sum over
 // b' < b of K S - 2 K (K - 1) with K = ceil(L/128), S = ceil(L/32) (the
 // 32-row steps of all 128-key blocks of a sequence).
-__device__ void bases_block(const JaggedArgs& ja, int64_t* bases, int64_t (*s)[kSchedThreads]) {
+__device__ void bases_block(const JaggedArgs& ja, int64_t* bases,
+                            int64_t (*s)[kSchedThreads / 64]) {
   const int tid = threadIdx.x, B = ja.num_seqs;
   int64_t* rbase = bases;
   int64_t* pbase = bases + B + 1;
@@ -272,24 +293,15 @@ __device__ void bases_block(const JaggedArgs& ja, int64_t* bases, int64_t (*s)[k
       r = S;
       q = K * S - 2 * K * (K - 1);
     }
-    s[0][tid] = r;
-    s[1][tid] = q;
-    __syncthreads();
-    for (int off = 1; off < kSchedThreads; off <<= 1) {
-      const int64_t a = tid >= off ? s[0][tid - off] : 0;
-      const int64_t c = tid >= off ? s[1][tid - off] : 0;
-      __syncthreads();
-      s[0][tid] += a;
-      s[1][tid] += c;
-      __syncthreads();
-    }
+    int64_t total_r, total_p;
+    r = block_scan(r, s[0], &total_r);
+    q = block_scan(q, s[1], &total_p);
     if (b < B) {
-      rbase[b + 1] = carry_r + s[0][tid];
-      pbase[b + 1] = carry_p + s[1][tid];
+      rbase[b + 1] = carry_r + r;
+      pbase[b + 1] = carry_p + q;
     }
-    carry_r += s[0][kSchedThreads - 1];
-    carry_p += s[1][kSchedThreads - 1];
-    __syncthreads();
+    carry_r += total_r;
+    carry_p += total_p;
   }
 }
 
@@ -325,9 +337,9 @@ __global__ __launch_bounds__(kSchedThreads) void prep_kernel(JaggedArgs ja, int 
                                                              int nfill_blocks, ColSums sums,
                                                              int nsum_blocks, int64_t* bases) {
   extern __shared__ int s_bins[];  // [maxw + 1]
-  __shared__ int s_scan[kSchedThreads];
+  __shared__ int s_scan[kSchedThreads / 64];
   __shared__ int64_t red[2][kSchedThreads / 64];
-  __shared__ int64_t s_bases[2][kSchedThreads];
+  __shared__ int64_t s_bases[2][kSchedThreads / 64];
   __shared__ float s_sums[32][33];
   int g = (int)blockIdx.x;
   if (items) {

@@ -15,16 +15,19 @@ def _reference(ts, nb):
     return np.minimum(np.frexp(np.maximum(d, 1).astype(np.float64))[1] - 1, nb - 1)
 
 
-@pytest.mark.parametrize("lengths", [
+SHORT = [
     tuple(range(1, 70)),                       # 2415 tokens: 16 rows
     tuple([7, 0, 129, 1000, 2049] * 3),        # 9555 tokens: 32 rows
     tuple([63, 64, 65, 1023, 0, 17] * 14),     # 17248 tokens: 64 rows
-    (8191, 8193, 3)])
-@pytest.mark.parametrize("nb,gap", [(128, 600), (32, 600), (9, 600), (1, 600), (64, 1 << 34)])
+]
+LONG = [(8191, 8193, 3)]
+CASES = [(n, nb, 600) for n in SHORT + LONG for nb in (128, 32, 9, 1)]
+CASES += [(n, 64, 1 << 34) for n in SHORT]     # 64-bit differences
+
+
+@pytest.mark.parametrize("lengths,nb,gap", CASES)
 def test_bucketize_row_groups(lengths, nb, gap):
     from paper_2402_17152_amd import hstu
-    if gap > 600 and max(lengths) > 3000:
-        pytest.skip("64-bit differences are covered by the shorter batches")
     rng = np.random.default_rng(len(lengths) + nb)
     offs = np.concatenate([[0], np.cumsum(lengths)]).astype(np.int64)
     ts = np.concatenate([1_700_000_000 + np.cumsum(rng.integers(0, gap, n)) for n in lengths])
