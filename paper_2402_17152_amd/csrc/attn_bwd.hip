@@ -331,23 +331,23 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
   };
   tile_offs(QT{}, qoffs, qstride_b);
   tile_offs(OT{}, ooffs, dostride_b);
-  auto issue_tiles = [&](int u) {
-    const int i0 = row0(u), slot = u & 3;
+  auto issue_tile = [&](auto tile_tag, const u32x4& rs, const uint8_t* tile, const uint32_t* offs,
+                        uint32_t first) {
+    using T = decltype(tile_tag);
+    uint32_t l[T::OPW], off[T::OPW];
 #pragma unroll
-    for (int k = 0; k < QT::OPW; k++)
-      dma_to_lds16_asm(qrs, sm.ring.t.q[slot] + QT::op_base(min(wave * QT::OPW + k, QT::OPS - 1)),
-                   qoffs[k] + (uint32_t)i0 * qstride_b);
-#pragma unroll
-    for (int k = 0; k < OT::OPW; k++)
-      dma_to_lds16_asm(ors, sm.ring.t.dO[slot] + OT::op_base(min(wave * OT::OPW + k, OT::OPS - 1)),
-                   ooffs[k] + (uint32_t)i0 * dostride_b);
-    if constexpr (SPLIT) {
-#pragma unroll
-      for (int k = 0; k < OT::OPW; k++)
-        dma_to_lds16_asm(orsl,
-                         sm.ring.t.dOl[slot] + OT::op_base(min(wave * OT::OPW + k, OT::OPS - 1)),
-                         ooffs[k] + (uint32_t)i0 * dostride_b);
+    for (int k = 0; k < T::OPW; k++) {
+      l[k] = lds_addr(tile + T::op_base(min(wave * T::OPW + k, T::OPS - 1)));
+      off[k] = offs[k] + first;
     }
+    dma_to_lds16_asm(rs, l, off);
+  };
+  auto issue_tiles = [&](int u) {
+    const uint32_t i0 = (uint32_t)row0(u);
+    const int slot = u & 3;
+    issue_tile(QT{}, qrs, sm.ring.t.q[slot], qoffs, i0 * qstride_b);
+    issue_tile(OT{}, ors, sm.ring.t.dO[slot], ooffs, i0 * dostride_b);
+    if constexpr (SPLIT) issue_tile(OT{}, orsl, sm.ring.t.dOl[slot], ooffs, i0 * dostride_b);
   };
   // Reversed rab_pos window of step u: W[y] = rab_pos[pb - y] with
   // pb = (N-1) + min(j0 + 127, n_h) - min(i0, n_h), so that a pair's entry
@@ -356,15 +356,18 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
   const int Pk = min(j0 + BN - 1, n_h);
   auto issue_win = [&](int u) {
     const int pb = (N - 1) + Pk - min(row0(u), n_h);
+    uint32_t l[3], off[3];
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-      const int op = 3 * wave + k, c = op / 3, ch = op % 3;
-      dma_to_lds4_asm(prs, &sm.sWin[u & 3][c][Sh::kWinPad + 64 * ch],
-                  (uint32_t)(pb - 64 * ch - lane - c) * 4u);
+    for (int ch = 0; ch < 3; ch++) {
+      l[ch] = lds_addr(&sm.sWin[u & 3][wave][Sh::kWinPad + 64 * ch]);
+      off[ch] = (uint32_t)(pb - 64 * ch - lane - wave) * 4u;
     }
+    dma_to_lds4_asm(prs, l, off);
   };
   auto issue_ts = [&](int u) {
-    dma_to_lds4_asm(trs, sm.sT[u & 7], (uint32_t)row0(u) * 8u + 4u * (uint32_t)lane);
+    const uint32_t l[1] = {lds_addr(sm.sT[u & 7])};
+    const uint32_t off[1] = {(uint32_t)row0(u) * 8u + 4u * (uint32_t)lane};
+    dma_to_lds4_asm(trs, l, off);
   };
   // Wave 0: rebased row timestamps of a staged step and their range (zeros
   // past the sequence end only enter steps that are never full).
@@ -1055,36 +1058,39 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
   };
   tile_offs(QT{}, qoffs, qstride_b);
   tile_offs(OT{}, ooffs, dostride_b);
-  auto issue_tiles = [&](int u) {
-    const int i0 = row0(u), slot = u % kSlots;
+  auto issue_tile = [&](auto tile_tag, const u32x4& rs, const uint8_t* tile, const uint32_t* offs,
+                        uint32_t first) {
+    using T = decltype(tile_tag);
+    uint32_t l[T::OPW], off[T::OPW];
 #pragma unroll
-    for (int k = 0; k < QT::OPW; k++)
-      dma_to_lds16_asm(qrs, sm.ring.t.q[slot] + QT::op_base(min(wave * QT::OPW + k, QT::OPS - 1)),
-                       qoffs[k] + (uint32_t)i0 * qstride_b);
-#pragma unroll
-    for (int k = 0; k < OT::OPW; k++)
-      dma_to_lds16_asm(ors, sm.ring.t.dO[slot] + OT::op_base(min(wave * OT::OPW + k, OT::OPS - 1)),
-                       ooffs[k] + (uint32_t)i0 * dostride_b);
-    if constexpr (SPLIT) {
-#pragma unroll
-      for (int k = 0; k < OT::OPW; k++)
-        dma_to_lds16_asm(orsl,
-                         sm.ring.t.dOl[slot] + OT::op_base(min(wave * OT::OPW + k, OT::OPS - 1)),
-                         ooffs[k] + (uint32_t)i0 * dostride_b);
+    for (int k = 0; k < T::OPW; k++) {
+      l[k] = lds_addr(tile + T::op_base(min(wave * T::OPW + k, T::OPS - 1)));
+      off[k] = offs[k] + first;
     }
+    dma_to_lds16_asm(rs, l, off);
+  };
+  auto issue_tiles = [&](int u) {
+    const uint32_t i0 = (uint32_t)row0(u);
+    const int slot = u % kSlots;
+    issue_tile(QT{}, qrs, sm.ring.t.q[slot], qoffs, i0 * qstride_b);
+    issue_tile(OT{}, ors, sm.ring.t.dO[slot], ooffs, i0 * dostride_b);
+    if constexpr (SPLIT) issue_tile(OT{}, orsl, sm.ring.t.dOl[slot], ooffs, i0 * dostride_b);
   };
   const int Pk = min(j0 + BN - 1, n_h);
   auto issue_win = [&](int u) {
     const int pb = (N - 1) + Pk - min(row0(u), n_h);
+    uint32_t l[3], off[3];
 #pragma unroll
-    for (int k = 0; k < 3; k++) {
-      const int op = 3 * wave + k, c = op / 3, ch = op % 3;
-      dma_to_lds4_asm(prs, &sm.sWin[u & 3][c][Sh::kWinPad + 64 * ch],
-                      (uint32_t)(pb - 64 * ch - lane - c) * 4u);
+    for (int ch = 0; ch < 3; ch++) {
+      l[ch] = lds_addr(&sm.sWin[u & 3][wave][Sh::kWinPad + 64 * ch]);
+      off[ch] = (uint32_t)(pb - 64 * ch - lane - wave) * 4u;
     }
+    dma_to_lds4_asm(prs, l, off);
   };
   auto issue_ts = [&](int u) {
-    dma_to_lds4_asm(trs, sm.sT[u & 7], (uint32_t)row0(u) * 8u + 4u * (uint32_t)lane);
+    const uint32_t l[1] = {lds_addr(sm.sT[u & 7])};
+    const uint32_t off[1] = {(uint32_t)row0(u) * 8u + 4u * (uint32_t)lane};
+    dma_to_lds4_asm(trs, l, off);
   };
 
   // ---- bias path of a (wave, step) tile (as in bwd_item) ----

@@ -140,21 +140,51 @@ __device__ __forceinline__ u32x4 rsrc_words(const void* base, uint32_t bytes) {
   return u32x4{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, bytes, 0x00020000u};
 }
 
-__device__ __forceinline__ void dma_to_lds16_asm(u32x4 r, void* lds, uint32_t off) {
-  const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(l), "v"(off), "s"(r)
-               : "memory");
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const void*)p;
 }
 
-__device__ __forceinline__ void dma_to_lds4_asm(u32x4 r, void* lds, uint32_t off) {
-  const uint32_t l = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds"
-               :
-               : "s"(l), "v"(off), "s"(r)
-               : "memory");
+// N operations of one resource, to the LDS addresses l[] from byte offsets
+// off[].  The assembler takes the string as it stands, so the wait states the
+// compiler would see to are written out: one between a write of M0 and the
+// load that uses it, and five between a scalar register that the vector unit
+// wrote (a spilled descriptor coming back by v_readlane) and a buffer
+// instruction that reads it; the group pays the five once.
+#define HSTU_DMA_FIRST(L, O, OP) "s_mov_b32 m0, %" L "\n\ts_nop 3\n\t" OP " %" O ", %0, 0 offen lds"
+#define HSTU_DMA_NEXT(L, O, OP) \
+  "\n\ts_mov_b32 m0, %" L "\n\ts_nop 0\n\t" OP " %" O ", %0, 0 offen lds"
+#define HSTU_DMA_GROUP(OP)                                                                     \
+  static_assert(N >= 1 && N <= 4, "one to four operations");                                   \
+  if constexpr (N == 1)                                                                        \
+    asm volatile(HSTU_DMA_FIRST("1", "2", OP) : : "s"(r), "s"(l[0]), "v"(off[0]) : "memory");  \
+  else if constexpr (N == 2)                                                                   \
+    asm volatile(HSTU_DMA_FIRST("1", "3", OP) HSTU_DMA_NEXT("2", "4", OP)                      \
+                 : : "s"(r), "s"(l[0]), "s"(l[1]), "v"(off[0]), "v"(off[1]) : "memory");       \
+  else if constexpr (N == 3)                                                                   \
+    asm volatile(HSTU_DMA_FIRST("1", "4", OP) HSTU_DMA_NEXT("2", "5", OP)                      \
+                 HSTU_DMA_NEXT("3", "6", OP)                                                   \
+                 : : "s"(r), "s"(l[0]), "s"(l[1]), "s"(l[2]), "v"(off[0]), "v"(off[1]),        \
+                 "v"(off[2]) : "memory");                                                      \
+  else                                                                                         \
+    asm volatile(HSTU_DMA_FIRST("1", "5", OP) HSTU_DMA_NEXT("2", "6", OP)                      \
+                 HSTU_DMA_NEXT("3", "7", OP) HSTU_DMA_NEXT("4", "8", OP)                       \
+                 : : "s"(r), "s"(l[0]), "s"(l[1]), "s"(l[2]), "s"(l[3]), "v"(off[0]),          \
+                 "v"(off[1]), "v"(off[2]), "v"(off[3]) : "memory");
+
+template <int N>
+__device__ __forceinline__ void dma_to_lds16_asm(u32x4 r, const uint32_t (&l)[N],
+                                                 const uint32_t (&off)[N]) {
+  HSTU_DMA_GROUP("buffer_load_dwordx4")
 }
+
+template <int N>
+__device__ __forceinline__ void dma_to_lds4_asm(u32x4 r, const uint32_t (&l)[N],
+                                                const uint32_t (&off)[N]) {
+  HSTU_DMA_GROUP("buffer_load_dword")
+}
+#undef HSTU_DMA_GROUP
+#undef HSTU_DMA_NEXT
+#undef HSTU_DMA_FIRST
 
 // s_waitcnt vmcnt(VM) lgkmcnt(0) (gfx9 encoding: vmcnt in bits 3:0 and
 // 15:14, expcnt in 6:4, lgkmcnt in 11:8).

@@ -95,9 +95,13 @@ struct Operand {
   // Issues the wave's share of the k-step starting at k0 into tile `t`.
   __device__ __forceinline__ void issue(uint16_t* t, int k0, int wave) const {
     const uint32_t kb = KMAJOR ? (uint32_t)k0 * ld_b : 2u * (uint32_t)k0;
+    uint32_t l[kOps], o[kOps];
 #pragma unroll
-    for (int e = 0; e < kOps; e++)
-      dma_to_lds16_asm(rs, t + 512 * (wave * kOps + e), off[e] + kb);
+    for (int e = 0; e < kOps; e++) {
+      l[e] = lds_addr(t + 512 * (wave * kOps + e));
+      o[e] = off[e] + kb;
+    }
+    dma_to_lds16_asm(rs, l, o);
   }
   // MFMA operand of the 32 rows of block `blk` for the half step s: lane ->
   // row lane % 32, k = 16 s + 8 (lane / 32) .. +7.
