@@ -163,14 +163,14 @@ __global__ __launch_bounds__(128 * WN, 2) void gemm_bf16_kernel(GemmArgs g) {
 #pragma unroll
       for (int q = 0; q < 16; q++) acc[i][j][q] = 0.0f;
 
-  // Row panels start at different steps of a k-contiguous contraction: rows
-  // lie a power of two apart, so that panels in step would all read the same
-  // few memory channels.
-  int kx = A_KM ? 0 : (m0 / BM * 3) % max(nk, 1);
+  // Steps go in ascending order in every tile and tile size: an output row of
+  // the maps then has the same bits wherever it lies in a batch, as keys and
+  // values cached from one batch and used with another need.
+  int k_next = kb;
   auto issue = [&](int st) {
-    oa.issue(sm.t[st], kb + kx * kGBK, wave);
-    ob.issue(sm.t[st] + Sh::kA, kb + kx * kGBK, wave);
-    kx = kx + 1 == nk ? 0 : kx + 1;
+    oa.issue(sm.t[st], k_next, wave);
+    ob.issue(sm.t[st] + Sh::kA, k_next, wave);
+    k_next += kGBK;
   };
 
   u32x4 af[2][MB], bf[2][2];
