@@ -439,7 +439,9 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
   };
 
   // ---- bias seed of step u (lane = key, rows 8g + 4*half + m) ----
-  const int a_y = Pk - my_j + 4 * half;  // window entry of (row i0 + 4*half, key) on a full tile
+  // Window entry of (row i0 + 4*half, key) on a full tile.  Keys past Pk (past
+  // the sequence end, or candidates) read entry 0 on: no valid pair uses them.
+  const int a_y = max(Pk - my_j, 0) + 4 * half;
   auto win_reads = [&](int u, float (&w)[16]) {
     const int c = a_y & 3;
     const float* wp = &sm.sWin[u & 3][c][Sh::kWinPad + a_y - c];
@@ -1128,7 +1130,9 @@ __device__ __forceinline__ void bwd_role_a(BwdSharedRS<DQK, DV, SPLIT>& sm, cons
                   sm.sTab[63 - bfar]};
     }
   };
-  const int a_y = Pk - my_j + 4 * half;
+  // (keys past Pk, past the sequence end or candidates, would lie before the
+  // window: they read from entry 0, and no valid pair uses what they read)
+  const int a_y = max(Pk - my_j, 0) + 4 * half;
   auto win_reads = [&](int u, float (&w)[16]) {
     const int c = a_y & 3;
     const float* wp = &sm.sWin[u & 3][c][Sh::kWinPad + a_y - c];
