@@ -75,8 +75,8 @@ struct TileRegs {
         v[e] = *reinterpret_cast<const f32x4*>(base + (int64_t)r * stride + 4 * (c % (D / 4)));
     }
   }
-  // Stores the tile; sets *bad if it holds an infinity or a NaN.
-  __device__ __forceinline__ void store(float* t, int tid, int* bad) const {
+  // Stores the tile; sets *special if it holds an infinity or a NaN.
+  __device__ __forceinline__ void store(float* t, int tid, int* special) const {
     bool b = false;
 #pragma unroll
     for (int e = 0; e < kPer; e++) {
@@ -85,7 +85,7 @@ struct TileRegs {
 #pragma unroll
       for (int m = 0; m < 4; m++) b |= not_finite(v[e][m]);
     }
-    if (b) *bad = 1;
+    if (b) *special = 1;
   }
 };
 
@@ -108,13 +108,15 @@ __device__ __forceinline__ f32x4 dot_tile(const float* a, const float* b, int la
 // acc[f] += sum over x of w[m][x] t[x][f] for 16 rows m of the score tile w
 // and the wave's D / 2 features of the 32 tile rows x (acc element r of
 // block nb: row 4 (lane / 16) + r, feature 16 nb + lane % 16).  A pair that
-// the mask drops has w = 0, which a non-finite t would turn into NaN, so a
-// tile holding one takes the plain loop over the pairs that `keep(r, x)`s.
+// the mask drops has w = 0, which a non-finite t would turn into NaN: in a
+// tile holding one (`special`) those elements enter the product as 0, and
+// the pairs that `keep(r, x)`s add theirs afterwards.  So what a dropped
+// pair holds never reaches a bit of the result.
 template <int D, typename Keep>
 __device__ __forceinline__ void outer_tile(const float* w, const float* t, int f0, int lane,
-                                           bool plain, Keep&& keep, f32x4 (&acc)[D / 32]) {
+                                           bool special, Keep&& keep, f32x4 (&acc)[D / 32]) {
   const int n = lane & 15, g = lane >> 4;
-  if (!plain) {
+  auto product = [&](auto&& value) {
 #pragma unroll
     for (int s = 0; s < 2; s++) {
       const f32x4 a = *reinterpret_cast<const f32x4*>(w + n * kScoreLd + 16 * s + 4 * g);
@@ -122,18 +124,24 @@ __device__ __forceinline__ void outer_tile(const float* w, const float* t, int f
       for (int e = 0; e < 4; e++)
 #pragma unroll
         for (int nb = 0; nb < D / 32; nb++)
-          acc[nb] = mfma16x16x4(a[e], t[(16 * s + 4 * g + e) * (D + 4) + f0 + 16 * nb + n],
-                                acc[nb]);
+          acc[nb] = mfma16x16x4(
+              a[e], value(t[(16 * s + 4 * g + e) * (D + 4) + f0 + 16 * nb + n]), acc[nb]);
     }
-  } else {
-    for (int x = 0; x < kRows; x++)
+  };
+  if (!special) {
+    product([](float v) { return v; });
+    return;
+  }
+  product([](float v) { return not_finite(v) ? 0.0f : v; });
+  for (int x = 0; x < kRows; x++)
+#pragma unroll
+    for (int nb = 0; nb < D / 32; nb++) {
+      const float v = t[x * (D + 4) + f0 + 16 * nb + n];
+      if (!not_finite(v)) continue;
 #pragma unroll
       for (int r = 0; r < 4; r++)
-        if (keep(4 * g + r, x))
-#pragma unroll
-          for (int nb = 0; nb < D / 32; nb++)
-            acc[nb][r] += w[(4 * g + r) * kScoreLd + x] * t[x * (D + 4) + f0 + 16 * nb + n];
-  }
+        if (keep(4 * g + r, x)) acc[nb][r] += w[(4 * g + r) * kScoreLd + x] * v;
+    }
 }
 
 // The (sequence, tile) pairs a workgroup visits: rows r0 .. r0 + 31 (global
@@ -229,7 +237,9 @@ struct FwdLds {
   int64_t t[kRows];
   float win[64];
   float tab[256];
-  int bad;
+  // Whether the tile of this parity holds an infinity or a NaN: set before a
+  // tile's first barrier, read after its second, cleared between the next's.
+  int special[2];
 };
 
 template <int DQK, int DV>
@@ -261,7 +271,7 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
     qr.store(sm.q, tid, &ignored);
   }
   if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
-  if (tid == 0) sm.bad = 0;
+  if (tid < 2) sm.special[tid] = 0;
   __syncthreads();
   const int64_t my_r = r0 + 16 * wr + n;
   const int64_t ti = ja.timestamps[min(my_r, T - 1)];
@@ -273,10 +283,11 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
   // one), timestamps and window to LDS; scores; their weights to LDS; O.
   for (int par = 0; !w.done(); par ^= 1) {
     const Walk cur = w;
-    kr.store(sm.k, tid, &sm.bad);
-    vr.store(sm.v[par], tid, &sm.bad);
+    kr.store(sm.k, tid, &sm.special[par]);
+    vr.store(sm.v[par], tid, &sm.special[par]);
     sr.store(sm.t, sm.win, tid);
     __syncthreads();
+    if (tid == 0) sm.special[par ^ 1] = 0;
     w.next(ja);
     if (!w.done()) load(w);
     const f32x4 s = dot_tile<DQK>(sm.k + 16 * wc * (DQK + 4), sm.q + 16 * wr * (DQK + 4), lane,
@@ -299,7 +310,8 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
     }
     *reinterpret_cast<f32x4*>(sm.p + (16 * wr + n) * kScoreLd + 16 * wc + 4 * g) = p;
     __syncthreads();
-    outer_tile<DV>(sm.p + 16 * wr * kScoreLd, sm.v[par], wc * (DV / 2), lane, sm.bad != 0,
+    const bool special = __builtin_amdgcn_readfirstlane(sm.special[par]) != 0;
+    outer_tile<DV>(sm.p + 16 * wr * kScoreLd, sm.v[par], wc * (DV / 2), lane, special,
                    [&](int row, int x) {
                      const int ii = (int)(r0 + 16 * wr + row - cur.o);
                      return ii >= 0 && ii < cur.L && pair_valid(ii, cur.x0 + x, cur.n_h);
@@ -331,7 +343,9 @@ struct BwdLds {
   float win[64];
   float tab[256];
   double time_acc[256];
-  int bad;
+  // Whether the tile of this parity holds an infinity or a NaN: set before a
+  // tile's first barrier, read after its second, cleared between the next's.
+  int special[2];
 };
 
 // Weight SiLU(s) and dS = dP SiLU'(s) of one pair (0, 0 if masked).
@@ -376,7 +390,7 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
   }
   if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
   sm.time_acc[tid] = 0.0;
-  if (tid == 0) sm.bad = 0;
+  if (tid < 2) sm.special[tid] = 0;
   __syncthreads();
   const int64_t my_r = r0 + 16 * wr + n;
   const int64_t ti = ja.timestamps[min(my_r, T - 1)];
@@ -393,10 +407,11 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
 
   for (int par = 0; !w.done(); par ^= 1) {
     const Walk cur = w;
-    kr.store(sm.tile_qk[par], tid, &sm.bad);
-    vr.store(sm.tile_v[0], tid, &sm.bad);
+    kr.store(sm.tile_qk[par], tid, &sm.special[par]);
+    vr.store(sm.tile_v[0], tid, &sm.special[par]);
     sr.store(sm.t, sm.win, tid);
     __syncthreads();
+    if (tid == 0) sm.special[par ^ 1] = 0;
     w.next(ja);
     if (!w.done()) load(w);
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -427,8 +442,8 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     }
     *reinterpret_cast<f32x4*>(sm.ds + (16 * wr + n) * kScoreLd + 16 * wc + 4 * g) = dsv;
     __syncthreads();
-    outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane,
-                    sm.bad != 0,
+    const bool special = __builtin_amdgcn_readfirstlane(sm.special[par]) != 0;
+    outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane, special,
                     [&](int row, int x) {
                       const int ii = (int)(r0 + 16 * wr + row - cur.o);
                       return ii >= 0 && ii < cur.L && pair_valid(ii, cur.x0 + x, cur.n_h);
@@ -524,7 +539,7 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     vr.store(sm.own_v, tid, &ignored);
   }
   if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
-  if (tid == 0) sm.bad = 0;
+  if (tid < 2) sm.special[tid] = 0;
   __syncthreads();
   const int64_t my_r = r0 + 16 * wr + n;  // the lane's key
   const int64_t tj = ja.timestamps[min(my_r, T - 1)];
@@ -536,10 +551,11 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
 
   for (int par = 0; !w.done(); par ^= 1) {
     const Walk cur = w;
-    qr.store(sm.tile_qk[par], tid, &sm.bad);
-    gr.store(sm.tile_v[par], tid, &sm.bad);
+    qr.store(sm.tile_qk[par], tid, &sm.special[par]);
+    gr.store(sm.tile_v[par], tid, &sm.special[par]);
     sr.store(sm.t, sm.win, tid);
     __syncthreads();
+    if (tid == 0) sm.special[par ^ 1] = 0;
     w.next(ja);
     if (!w.done()) load(w);
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -566,14 +582,14 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     *reinterpret_cast<f32x4*>(sm.p + so) = pv;
     *reinterpret_cast<f32x4*>(sm.ds + so) = dsv;
     __syncthreads();
-    const bool plain = sm.bad != 0;
+    const bool special = __builtin_amdgcn_readfirstlane(sm.special[par]) != 0;
     auto keep = [&](int row, int x) {
       const int jj = (int)(r0 + 16 * wr + row - cur.o), i = cur.x0 + x;
       return jj >= 0 && i < cur.L && pair_valid(i, jj, cur.n_h);
     };
-    outer_tile<DV>(sm.p + 16 * wr * kScoreLd, sm.tile_v[par], wc * (DV / 2), lane, plain, keep,
+    outer_tile<DV>(sm.p + 16 * wr * kScoreLd, sm.tile_v[par], wc * (DV / 2), lane, special, keep,
                    av);
-    outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane, plain,
+    outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane, special,
                     keep, ak);
   }
   const float invN = 1.0f / (float)N;

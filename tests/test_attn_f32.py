@@ -74,3 +74,36 @@ def test_f32_masked_pairs_do_not_spread_infinities(hs, name, value):
         assert (a[~r, 1] - b[~r, 1]).abs().max() <= 1e-5 * a.abs().max()
         if r.any():
             assert not torch.isfinite(b[r, 1]).all()
+
+
+@pytest.mark.parametrize("name", ["v", "k", "q", "do"])
+@pytest.mark.parametrize("value", [np.inf, np.nan])
+def test_f32_masked_infinities_leave_the_bits(hs, name, value):
+    """What a masked pair holds changes no bit: a batch with one token not
+    finite gives, twice, the finite batch's bits in every output that no kept
+    pair with that token reaches, in its own tile, in the tiles after it and
+    in the sequences that share its 32-row blocks."""
+    lengths, tok = (20, 90, 9, 40), 20 + 40
+    batch = inputs.make_batch(2, seed=11, lengths=lengths, num_heads=2, d_qk=64, d_v=32,
+                              max_seq_len=90, dtype="f32", num_targets=(0, 30, 0, 0))
+    d = gu.dev_inputs(batch)
+    ref = [gu.gpu_fwd(hs, d, batch), *gu.gpu_bwd(hs, d, batch)[:3]]
+    d[name] = d[name].clone()
+    d[name][tok] = value
+    rows = torch.arange(sum(lengths), device="cuda")
+    reached = (rows >= 20) & (rows < 110)  # at most the token's own sequence
+    sees = reached & (rows >= tok)
+    seen = reached & (rows <= tok)
+    own = rows == tok
+    none = torch.zeros_like(own)
+    reach = {"v": (sees, sees, own, none), "k": (sees, sees, own, own),
+             "q": (own, own, seen, seen), "do": (none, own, seen, seen)}[name]
+    first = None
+    for _ in range(3):
+        got = [gu.gpu_fwd(hs, d, batch), *gu.gpu_bwd(hs, d, batch)[:3]]
+        torch.cuda.synchronize()
+        for a, b, r in zip(ref, got, reach):
+            assert torch.equal(a[~r], b[~r])
+        first = first or got
+        for a, b in zip(first, got):
+            assert torch.equal(a.nan_to_num(nan=7.0), b.nan_to_num(nan=7.0))
