@@ -120,15 +120,17 @@ def _ptr(t: Optional[torch.Tensor]):
     return None if t is None else t.data_ptr()
 
 
-_current_raw_stream = torch._C._cuda_getCurrentRawStream
-_current_device = torch._C._cuda_getDevice
+# The handle of the current stream without a Stream object around it.  Both are
+# torch's own, undocumented: where one is missing the public call serves.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_raw_device = getattr(torch._C, "_cuda_getDevice", None)
 
 
 def _stream(stream=None):
     if stream is not None:
         return stream.cuda_stream
-    if torch.cuda.is_initialized():
-        return _current_raw_stream(_current_device())
+    if _raw_stream is not None and _raw_device is not None and torch.cuda.is_initialized():
+        return _raw_stream(_raw_device())
     return torch.cuda.current_stream().cuda_stream
 
 
@@ -286,9 +288,9 @@ def hstu_layer_fwd(q, k, v, u, seq_offsets, timestamps, rab_pos, rab_time, max_s
     if y is None:
         y = q.new_empty((T, D))
     if ln_mean is None:
-        ln_mean = attn_out.new_empty(T)
+        ln_mean = q.new_empty(T, dtype=torch.float32)
     if ln_rstd is None:
-        ln_rstd = attn_out.new_empty(T)
+        ln_rstd = q.new_empty(T, dtype=torch.float32)
     if ws is None:
         ws = workspace(p, q.device)
     _check(lib.hstu_layer_fwd(ctypes.byref(p), ctypes.byref(j), _ptr(q), _row_stride(q), _ptr(k),
