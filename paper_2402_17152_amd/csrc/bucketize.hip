@@ -42,6 +42,7 @@ constexpr int kBktWaves = kBktThreads / 64;
 constexpr int kBktStep = 16;                // rows a wave takes together are this far apart
 constexpr int kBktMaxRows = 4 * kBktStep;   // rows per workgroup, at most
 constexpr int kBktCols = 8192;  // columns staged per slab
+constexpr int kBktShort = 64;   // longest sequence that goes unstaged
 // Entry y of a copy sits at y + 4 (y >> kPadShift); y <= kBktCols.
 constexpr int kPadShift = 6;
 __device__ __forceinline__ int bkt_pidx(int y) { return y + 4 * (y >> kPadShift); }
@@ -191,6 +192,17 @@ __device__ __forceinline__ void bucketize_rows(BktShared& sm, int nb, const int6
                                                int L, int64_t base, int r0, int rows,
                                                uint8_t* __restrict__ out, int tid, int wave,
                                                int lane) {
+  // Short sequences: a wave holds every timestamp, a lane writes a byte of
+  // each row; no staging and no barrier, of which a workgroup would otherwise
+  // have three for each of its many sequences.
+  if (L <= kBktShort) {
+    const int64_t tj = t[min(lane, L - 1)];
+    for (int x = wave; x < rows; x += kBktWaves) {
+      const int64_t dt = readlane64(tj, r0 + x) - tj;
+      if (lane < L) out[base + (int64_t)(r0 + x) * L + lane] = (uint8_t)time_bucket64(dt, nb);
+    }
+    return;
+  }
   // 32-bit form: timestamps as offsets from t[0] - 2^30; it applies when
   // every offset the workgroup touches lies in [0, 2^31), so that two of
   // them differ by less than 2^31.  A slab's timestamps are loaded before
@@ -220,17 +232,17 @@ __device__ __forceinline__ void bucketize_rows(BktShared& sm, int nb, const int6
     }
     const bool fast = __syncthreads_and(ok);  // also: previous slab fully consumed
     if (fast) {
+      // (columns past the slab's are not read: a short sequence, one of many
+      // in its workgroup, skips their stores)
 #pragma unroll
       for (int e = 0; e < kPer; e++) {
+        if (e * kBktThreads >= ncols) break;
         const int x = tid + e * kBktThreads;
         sm.t32[0][bkt_pidx(x)] = cur[e];
         sm.t32[1][bkt_pidx(x + 1)] = cur[e];
       }
     } else {
-      for (int e = 0; e < kPer; e++) {
-        const int x = tid + e * kBktThreads;
-        sm.t64[x] = x < ncols ? t[c0 + x] : t0;
-      }
+      for (int x = tid; x < ncols; x += kBktThreads) sm.t64[x] = t[c0 + x];
     }
     __syncthreads();
     // A wave takes rows x, x + 16, ... for x = wave, wave + 8; row set-up is

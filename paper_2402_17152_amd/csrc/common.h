@@ -64,6 +64,13 @@ __device__ __forceinline__ u32x4 zero_u32x4() {
   return z;
 }
 
+// The 64-bit value of one lane (uniform) in every lane.
+__device__ __forceinline__ int64_t readlane64(int64_t v, int lane) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)((uint64_t)v >> 32), lane);
+  return (int64_t)((uint64_t)hi << 32 | lo);
+}
+
 // Packs two floats into two bf16 (round to nearest even) in one dword.
 __device__ __forceinline__ uint32_t pack_bf16x2(float lo, float hi) {
   bf16x2 r;

@@ -40,3 +40,11 @@ def test_bucketize_row_groups(lengths, nb, gap):
         assert np.array_equal(got[o:o + n * n].reshape(n, n), ref), f"sequence {b} of {n} tokens"
         o += n * n
     assert o == got.size
+
+
+@pytest.mark.parametrize("lengths", [tuple(range(60, 84)) * 2, (1,) * 700 + (2,) * 300 + (64,) * 9])
+@pytest.mark.parametrize("nb,gap", [(128, 600), (9, 600), (64, 1 << 34)])
+def test_bucketize_short_sequences(lengths, nb, gap):
+    """Both sides of the 64 tokens up to which a sequence goes unstaged, at
+    every alignment, and workgroups that meet many short sequences."""
+    test_bucketize_row_groups(lengths, nb, gap)
