@@ -86,6 +86,14 @@ __device__ __forceinline__ float silu(float x) {
   return x * __builtin_amdgcn_rcpf(1.0f + e);
 }
 
+// Workgroups per CU that the registers are held to: two above heads of 64,
+// three up to 64 (at most 168 registers: the two-term instance spills 13 for
+// it, 1.73 ms per layer step of 62 K tokens against 1.81 at two), four for
+// the one-term instances at 32 (at most 128; at 135 and three, batches of
+// short sequences took 10 to 19 % longer).
+template <int DQK, int DV, bool SPLIT>
+constexpr int kFwdPerCu = DQK > 64 || DV > 64 ? 2 : DQK > 32 || DV > 32 || SPLIT ? 3 : 4;
+
 // SPLIT: P enters the second contraction as two bf16 terms, hi = bf16(P)
 // and lo = bf16(P - hi) (two MFMAs per V operand), which leaves O with
 // about 2^-17 relative error instead of bf16's 2^-9; used where O is
@@ -363,52 +371,55 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     }
   };
   // Per-pair bias.  Branch-free, with every LDS lookup issued before any
-  // is consumed, so the lookups of the 16 pairs overlap.  Time term on the
-  // fast path: |t_i - t_j| < 2^31 by one v_sad_u32, its leading-zero count
-  // z by v_ffbh_u32 (-1 for 0), then tab32[z] = tab[32 + z]; entry -1
-  // (= tab[31], unused by the fast path) holds bucket 0, the bucket of
-  // |dt| <= 1.
-  auto time_terms = [&](int u, float (&tv)[16]) {
+  // is consumed, so the lookups of the 16 pairs overlap (of 8 at a time
+  // where four workgroups share a CU: 16 take registers past that).  Time
+  // term on the fast path: |t_i - t_j| < 2^31 by one v_sad_u32, its
+  // leading-zero count z by v_ffbh_u32 (-1 for 0), then tab32[z] = tab[32 +
+  // z]; entry -1 (= tab[31], unused by the fast path) holds bucket 0, the
+  // bucket of |dt| <= 1.
+  constexpr int kParts = kFwdPerCu<DQK, DV, SPLIT> == 4 ? 2 : 1;
+  constexpr int kPairs = 16 / kParts, kRuns = 4 / kParts;
+  auto time_terms = [&](int u, int part, float (&tv)[kPairs]) {
     // The lane's 16 keys are 4 runs of 4: jl = 8g + 4*half + m.
     if constexpr (FAST) {
-      const uint32_t* tp = sm.sTr[u & 7] + 4 * half;
-      uint32_t tj[16];
+      const uint32_t* tp = sm.sTr[u & 7] + 4 * half + 8 * kRuns * part;
+      uint32_t tj[kPairs];
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
+      for (int g = 0; g < kRuns; g++) {
         const u32x4 v = *reinterpret_cast<const u32x4*>(tp + 8 * g);
 #pragma unroll
         for (int m = 0; m < 4; m++) tj[4 * g + m] = v[m];
       }
-      int z[16];
+      int z[kPairs];
 #pragma unroll
-      for (int q = 0; q < 16; q++) {
+      for (int q = 0; q < kPairs; q++) {
         uint32_t d, zz;
         asm("v_sad_u32 %0, %1, %2, 0" : "=v"(d) : "v"(tir), "v"(tj[q]));
         asm("v_ffbh_u32 %0, %1" : "=v"(zz) : "v"(d));
         z[q] = (int)zz;
       }
 #pragma unroll
-      for (int q = 0; q < 16; q++) tv[q] = tab32[z[q]];
+      for (int q = 0; q < kPairs; q++) tv[q] = tab32[z[q]];
     } else {
       // Staged as int64: each run of 4 keys is 8 dwords.
-      const uint32_t* tp = sm.sT[u & 7] + 2 * (4 * half);
-      uint32_t w[32];
+      const uint32_t* tp = sm.sT[u & 7] + 2 * (4 * half) + 16 * kRuns * part;
+      uint32_t w[2 * kPairs];
 #pragma unroll
-      for (int g = 0; g < 4; g++)
+      for (int g = 0; g < kRuns; g++)
 #pragma unroll
         for (int h = 0; h < 2; h++) {
           const u32x4 v = *reinterpret_cast<const u32x4*>(tp + 16 * g + 4 * h);
 #pragma unroll
           for (int e = 0; e < 4; e++) w[8 * g + 4 * h + e] = v[e];
         }
-      int sl[16];
+      int sl[kPairs];
 #pragma unroll
-      for (int q = 0; q < 16; q++) {
+      for (int q = 0; q < kPairs; q++) {
         const int64_t tj = (int64_t)(((uint64_t)w[2 * q + 1] << 32) | w[2 * q]);
         sl[q] = slot64(ti64 - tj);
       }
 #pragma unroll
-      for (int q = 0; q < 16; q++) tv[q] = sm.sTab[sl[q]];
+      for (int q = 0; q < kPairs; q++) tv[q] = sm.sTab[sl[q]];
     }
   };
   auto seed_general = [&](int u, f32x16& acc) {
@@ -420,51 +431,55 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
       for (int q = 0; q < 16; q++) acc[q] = kMaskedBias;
       return;
     }
-    float tv[16], wv[16];
-    if (full) {
-      // Several buckets: position term as on uniform tiles, time term per pair.
+    auto window = [&](int part, float (&wv)[kPairs]) {
       const int c = a_win & 3;
-      const float* wp = &sm.sWin[ks][c][Sh::kWinPad + a_win - c];
+      const float* wp = &sm.sWin[ks][c][Sh::kWinPad + a_win - c] + 8 * kRuns * part;
 #pragma unroll
-      for (int g = 0; g < 4; g++) {
+      for (int g = 0; g < kRuns; g++) {
         const f32x4 w = *reinterpret_cast<const f32x4*>(wp + 8 * g);
 #pragma unroll
         for (int m = 0; m < 4; m++) wv[4 * g + m] = w[m];
       }
-      time_terms(u, tv);
+    };
+    if (full) {
+      // Several buckets: position term as on uniform tiles, time term per pair.
 #pragma unroll
-      for (int q = 0; q < 16; q++) acc[q] = wv[q] + tv[q];
+      for (int part = 0; part < kParts; part++) {
+        float tv[kPairs], wv[kPairs];
+        window(part, wv);
+        time_terms(u, part, tv);
+#pragma unroll
+        for (int q = 0; q < kPairs; q++) acc[kPairs * part + q] = wv[q] + tv[q];
+      }
     } else {
       // Masked, ragged or candidate pairs.  History keys (position = index)
       // by the window reads of full tiles (they stay inside the window for
       // every lane, valid or not); candidate keys (all at position n_h) entry
       // by entry, invalid pairs reading entry 0.
-      bool ok[16];
 #pragma unroll
-      for (int q = 0; q < 16; q++) {
-        const int j = j0 + 8 * (q >> 2) + 4 * half + (q & 3);
-        ok[q] = pair_kept(j);
-      }
-      if (!TGT || j0 + BN - 1 < n_h) {
-        const int c = a_win & 3;
-        const float* wp = &sm.sWin[ks][c][Sh::kWinPad + a_win - c];
+      for (int part = 0; part < kParts; part++) {
+        float tv[kPairs], wv[kPairs];
+        bool ok[kPairs];
 #pragma unroll
-        for (int g = 0; g < 4; g++) {
-          const f32x4 w = *reinterpret_cast<const f32x4*>(wp + 8 * g);
-#pragma unroll
-          for (int m = 0; m < 4; m++) wv[4 * g + m] = w[m];
+        for (int q = 0; q < kPairs; q++) {
+          const int j = j0 + 8 * kRuns * part + 8 * (q >> 2) + 4 * half + (q & 3);
+          ok[q] = pair_kept(j);
         }
-      } else {
-        const int pb = min(j0, n_h);
+        if (!TGT || j0 + BN - 1 < n_h) {
+          window(part, wv);
+        } else {
+          const int pb = min(j0, n_h);
 #pragma unroll
-        for (int q = 0; q < 16; q++) {
-          const int j = j0 + 8 * (q >> 2) + 4 * half + (q & 3);
-          wv[q] = sm.sWin[ks][0][Sh::kWinPad + (ok[q] ? bias_pos(j, n_h) - pb + R - pi : 0)];
+          for (int q = 0; q < kPairs; q++) {
+            const int j = j0 + 8 * kRuns * part + 8 * (q >> 2) + 4 * half + (q & 3);
+            wv[q] = sm.sWin[ks][0][Sh::kWinPad + (ok[q] ? bias_pos(j, n_h) - pb + R - pi : 0)];
+          }
         }
-      }
-      time_terms(u, tv);
+        time_terms(u, part, tv);
 #pragma unroll
-      for (int q = 0; q < 16; q++) acc[q] = ok[q] ? wv[q] + tv[q] : kMaskedBias;
+        for (int q = 0; q < kPairs; q++)
+          acc[kPairs * part + q] = ok[q] ? wv[q] + tv[q] : kMaskedBias;
+      }
     }
   };
 
@@ -610,14 +625,10 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
   }
 }
 
-// Three workgroups per CU for heads up to 64 (at most 168 registers: the
-// two-term instance spills 13 for it, 1.73 ms per layer step of 62 K tokens
-// against 1.81 at two), two above.
 template <int DQK, int DV, bool SPLIT, bool TGT>
-__global__ __launch_bounds__(256, DQK <= 64 && DV <= 64 ? 3 : 2) void attn_fwd_bf16_kernel(JaggedArgs ja, Tensors t,
-                                                               void* __restrict__ out, int out_f32,
-                                                               const WorkItem* __restrict__ items,
-                                                               const int32_t* __restrict__ count) {
+__global__ __launch_bounds__(256, (kFwdPerCu<DQK, DV, SPLIT>)) void attn_fwd_bf16_kernel(
+    JaggedArgs ja, Tensors t, void* __restrict__ out, int out_f32,
+    const WorkItem* __restrict__ items, const int32_t* __restrict__ count) {
   using Sh = FwdShared<DQK, DV>;
   __shared__ Sh sm;
   // Workgroup id = item * H + head: the dispatcher walks the (longest
