@@ -42,7 +42,9 @@ constexpr int kBktWaves = kBktThreads / 64;
 constexpr int kBktStep = 16;                // rows a wave takes together are this far apart
 constexpr int kBktMaxRows = 4 * kBktStep;   // rows per workgroup, at most
 constexpr int kBktCols = 8192;  // columns staged per slab
-constexpr int kBktShort = 64;   // longest sequence that goes unstaged
+// Longest sequence that goes unstaged: a wave's lanes hold it (30000 sequences
+// of 0 to 19 tokens 474 -> 143 us, 1000 of 30 55 -> 28, 300 of 64 30 -> 26).
+constexpr int kBktShort = 64;
 // Entry y of a copy sits at y + 4 (y >> kPadShift); y <= kBktCols.
 constexpr int kPadShift = 6;
 __device__ __forceinline__ int bkt_pidx(int y) { return y + 4 * (y >> kPadShift); }
@@ -232,8 +234,7 @@ __device__ __forceinline__ void bucketize_rows(BktShared& sm, int nb, const int6
     }
     const bool fast = __syncthreads_and(ok);  // also: previous slab fully consumed
     if (fast) {
-      // (columns past the slab's are not read: a short sequence, one of many
-      // in its workgroup, skips their stores)
+      // (columns past the slab's are not read)
 #pragma unroll
       for (int e = 0; e < kPer; e++) {
         if (e * kBktThreads >= ncols) break;
