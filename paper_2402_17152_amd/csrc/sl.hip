@@ -352,9 +352,12 @@ __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
 }
 
 // dst row r = src row index[r] for r < *count (count read on the device).
-// A row's words (of type W) are taken by 2^lg lanes; a workgroup takes
-// kGatherUnroll sweeps of 256 >> lg consecutive rows, so that a lane has that
-// many rows' loads in flight.  HBM-bound.
+// A row's words (of type W) are taken by 2^lg lanes, 64 words to a workgroup
+// column (blockIdx.x); a workgroup takes kGatherUnroll sweeps of 256 >> lg
+// consecutive rows, so that a lane has that many rows' loads in flight.
+// HBM-bound.  (With a lane walking a whole row, few wide rows kept few lanes
+// busy: 64 rows of 64 KB took 23 us, now 6; one of 1 MB 154, now 6; 36000
+// rows of 4 KB 56, now 46.)
 constexpr int kGatherUnroll = 4;
 
 template <typename W>
@@ -368,15 +371,15 @@ __global__ __launch_bounds__(256) void gather_rows_kernel(const char* __restrict
   const int64_t rows = min(*count, max_rows);
   const int sub = threadIdx.x & ((1 << lg) - 1);
   const int step = 256 >> lg;
-  for (int64_t r = (int64_t)blockIdx.x * (U * step) + (threadIdx.x >> lg); r < rows;
-       r += (int64_t)gridDim.x * (U * step)) {
+  for (int64_t r = (int64_t)blockIdx.y * (U * step) + (threadIdx.x >> lg); r < rows;
+       r += (int64_t)gridDim.y * (U * step)) {
     int64_t from[U];
 #pragma unroll
     for (int u = 0; u < U; u++) {
       const int64_t x = r + u * step;
       from[u] = x < rows ? index[x] : 0;
     }
-    for (int64_t w = sub; w < words; w += 1 << lg) {
+    for (int64_t w = ((int64_t)blockIdx.x << lg) + sub; w < words; w += (int64_t)gridDim.x << lg) {
       W v[U];
 #pragma unroll
       for (int u = 0; u < U; u++)
@@ -398,11 +401,11 @@ hipError_t gather_case(const void* src, int64_t src_stride, int64_t row_bytes,
   int lg = 0;
   while (lg < 6 && (1 << lg) < words) lg++;
   const int64_t per_block = kGatherUnroll * (256 >> lg);
-  int64_t blocks = (max_rows + per_block - 1) / per_block;
-  if (blocks > 65536) blocks = 65536;
-  hipLaunchKernelGGL((gather_rows_kernel<W>), dim3((unsigned)blocks), dim3(256), 0, s,
-                     (const char*)src, src_stride, words, lg, index, count, max_rows, (char*)dst,
-                     dst_stride);
+  const int64_t cols = min((words + 63) / 64, (int64_t)65535);
+  const int64_t blocks = min((max_rows + per_block - 1) / per_block, 65535 / cols);
+  hipLaunchKernelGGL((gather_rows_kernel<W>), dim3((unsigned)cols, (unsigned)blocks), dim3(256), 0,
+                     s, (const char*)src, src_stride, words, lg, index, count, max_rows,
+                     (char*)dst, dst_stride);
   return hipGetLastError();
 }
 

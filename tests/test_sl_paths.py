@@ -56,3 +56,11 @@ def test_gather_row_widths(row_bytes, shift, rows):
     torch.cuda.synchronize()
     assert torch.equal(dst[:rows], src[idx])
     assert (dst[rows:] == 5).all()
+
+
+@pytest.mark.parametrize("rows,row_bytes", [(1, 1 << 20), (3, 65536 + 8), (17, 4096 + 4), (70, 16384),
+                                            (16, 1040)])
+def test_gather_wide_rows(rows, row_bytes):
+    """Rows of more words than the lanes that share one: a row is spread over
+    workgroups, the last of them partly filled."""
+    test_gather_row_widths(row_bytes, 0, rows)
