@@ -35,8 +35,17 @@ constexpr int kSlWaves = kSlThreads / 64;
 constexpr int kSlHeld = 8;  // keys a thread holds
 // Up to this many sequences a select workgroup adds up the new lengths of
 // the sequences before its own by itself, four per thread, instead of two
-// launches before it (the keep decisions, their prefix sum: 9 us of 141).
+// launches before it (the keep decisions, their prefix sum: about 7 us).
 constexpr int32_t kSlFusedSeqs = 4 * kSlThreads;
+
+// log2 of the sequences per workgroup.  A CU holds one workgroup, so beyond a
+// few times 256 sequences their number costs more than what they overlap: a
+// workgroup then takes several sequences, copies those that stay whole side
+// by side and shortens the others one after the other.  Sequences of 0 to 39
+// tokens that all stay whole, one to a workgroup against several: 2048 of
+// them 19.5 against 7.5 us, 4096 39.5 / 14.7, 60000 333 / 111; of 200 tokens
+// shortened to 64: 55 / 44, 114 / 86, 1343 / 1105.
+inline int sl_group_lg(int32_t B) { return B <= 1024 ? 0 : B <= kSlFusedSeqs ? 2 : 4; }
 
 __device__ __forceinline__ bool keep_whole(int64_t n, int64_t t, int32_t L, double keep_num,
                                            double u) {
@@ -279,75 +288,99 @@ __device__ void select_tokens(SlShared& sm, const SlKey& key, int nh, int L, int
   __syncthreads();
 }
 
-// One workgroup per sequence.  FUSED: it also adds up the new lengths before
-// its own and writes its new offset; else new_offs holds them.
+// One workgroup per 2^lg sequences (2^lg <= its waves).  FUSED: it also adds
+// up the new lengths before its own and writes its new offsets; else new_offs
+// holds them.
 template <bool FUSED>
 __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
-    int32_t B, const int64_t* __restrict__ offs, const int64_t* __restrict__ ts,
+    int32_t B, int lg, const int64_t* __restrict__ offs, const int64_t* __restrict__ ts,
     const int64_t* __restrict__ nt, int32_t L, double keep_num, int32_t mode,
     const double* __restrict__ u_keep, const double* __restrict__ e_rand,
     int64_t* __restrict__ new_offs, int64_t* __restrict__ gather) {
   __shared__ SlShared sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  for (int b = blockIdx.x; b < B; b += gridDim.x) {
-    const int64_t o = offs[b];
-    const int n = (int)(offs[b + 1] - o);
-    const int t = nt ? (int)nt[b] : 0;
-    const int nh = n - t;
-    const bool whole = keep_whole(n, t, L, keep_num, u_keep[b]);
-    int64_t start;
+  for (int64_t first = (int64_t)blockIdx.x << lg; first < B; first += (int64_t)gridDim.x << lg) {
+    const int b0 = (int)first, seqs = min(1 << lg, B - b0);
+    // Lane l of every wave: sequence b0 + l.
+    int64_t o_l = 0, start_l = 0;
+    int n_l = 0, t_l = 0;
+    bool whole_l = false;
+    if (lane < seqs) {
+      o_l = offs[b0 + lane];
+      n_l = (int)(offs[b0 + lane + 1] - o_l);
+      t_l = nt ? (int)nt[b0 + lane] : 0;
+      whole_l = keep_whole(n_l, t_l, L, keep_num, u_keep[b0 + lane]);
+      if constexpr (!FUSED) start_l = new_offs[b0 + lane];
+    }
     if constexpr (FUSED) {
       int64_t sum = 0;
-      for (int x = tid; x < b; x += kSlThreads) {
+      for (int x = tid; x < b0; x += kSlThreads) {
         const int64_t xn = offs[x + 1] - offs[x], xt = nt ? nt[x] : 0;
         sum += keep_whole(xn, xt, L, keep_num, u_keep[x]) ? xn : (int64_t)L + xt;
       }
-      start = block_add(sm, 0, sum);
-      if (tid == 0) {
-        if (b == 0) new_offs[0] = 0;
-        new_offs[b + 1] = start + (whole ? n : (int64_t)L + t);
+      const int64_t len = lane >= seqs ? 0 : whole_l ? n_l : (int64_t)L + t_l;
+      int64_t run = len;
+      for (int off = 1; off < 1 << lg; off <<= 1) {
+        const int64_t x = __shfl_up(run, off, 64);
+        if (lane >= off) run += x;
       }
-    } else {
-      start = new_offs[b];
+      start_l = block_add(sm, 0, sum) + run - len;
+      if (wave == 0 && lane < seqs) {
+        if (b0 + lane == 0) new_offs[0] = 0;
+        new_offs[b0 + lane + 1] = start_l + len;
+      }
     }
-    int64_t* out = gather + start;
-    if (whole) {
-      for (int i = tid; i < n; i += kSlThreads) out[i] = o + i;
-      __syncthreads();
-      continue;
+    // Whole sequences, each by its share of the threads.
+    {
+      const int sh = 10 - lg;  // 1024 >> lg threads, whole waves, each
+      const int k = __builtin_amdgcn_readfirstlane(tid >> sh);
+      if (__builtin_amdgcn_readlane(whole_l, k)) {
+        const int64_t o = readlane64(o_l, k);
+        const int n = __builtin_amdgcn_readlane(n_l, k);
+        int64_t* out = gather + readlane64(start_l, k);
+        for (int i = tid & ((1 << sh) - 1); i < n; i += 1 << sh) out[i] = o + i;
+      }
     }
-    // Candidates follow the L chosen history tokens.
-    for (int c = tid; c < t; c += kSlThreads) out[L + c] = o + nh + c;
+    for (uint64_t left = __ballot(lane < seqs && !whole_l); left; left &= left - 1) {
+      const int k = __builtin_ctzll(left);
+      const int64_t o = readlane64(o_l, k);
+      const int n = __builtin_amdgcn_readlane(n_l, k), t = __builtin_amdgcn_readlane(t_l, k);
+      const int nh = n - t;
+      int64_t* out = gather + readlane64(start_l, k);
+      // Candidates follow the L chosen history tokens.
+      for (int c = tid; c < t; c += kSlThreads) out[L + c] = o + nh + c;
 
-    // t_max and (feature-weighted) F = sum of t_max - t_i over the history;
-    // random selection reads no timestamps.
-    const int64_t* th = ts + o;
-    int64_t tmax = 0, F = 0;
-    if (mode != kSlRandom) {
-      int64_t mx = (int64_t)(~0ull >> 1) * -1 - 1;
-      for (int i = tid; i < nh; i += kSlThreads) mx = th[i] > mx ? th[i] : mx;
+      // t_max and (feature-weighted) F = sum of t_max - t_i over the history;
+      // random selection reads no timestamps.
+      const int64_t* th = ts + o;
+      int64_t tmax = 0, F = 0;
+      if (mode != kSlRandom) {
+        int64_t mx = (int64_t)(~0ull >> 1) * -1 - 1;
+        for (int i = tid; i < nh; i += kSlThreads) mx = th[i] > mx ? th[i] : mx;
 #pragma unroll
-      for (int off = 32; off > 0; off >>= 1) {
-        const int64_t x = __shfl_xor(mx, off, 64);
-        mx = x > mx ? x : mx;
+        for (int off = 32; off > 0; off >>= 1) {
+          const int64_t x = __shfl_xor(mx, off, 64);
+          mx = x > mx ? x : mx;
+        }
+        if (lane == 0) sm.red[1][wave] = mx;
+        __syncthreads();
+        tmax = sm.red[1][0];
+#pragma unroll
+        for (int w = 1; w < kSlWaves; w++) tmax = max(tmax, sm.red[1][w]);
+        __syncthreads();
       }
-      if (lane == 0) sm.red[1][wave] = mx;
-      __syncthreads();
-      tmax = sm.red[1][0];
-#pragma unroll
-      for (int w = 1; w < kSlWaves; w++) tmax = max(tmax, sm.red[1][w]);
-      __syncthreads();
+      if (mode == kSlWeighted) {
+        int64_t sum = 0;
+        for (int i = tid; i < nh; i += kSlThreads) sum += tmax - th[i];
+        F = block_add(sm, 1, sum);
+      }
+      const SlKey key{th, e_rand ? e_rand + o : nullptr, tmax, F, mode};
+      if (nh <= kSlHeld * kSlThreads)
+        select_tokens<true>(sm, key, nh, L, o, out);
+      else
+        select_tokens<false>(sm, key, nh, L, o, out);
     }
-    if (mode == kSlWeighted) {
-      int64_t sum = 0;
-      for (int i = tid; i < nh; i += kSlThreads) sum += tmax - th[i];
-      F = block_add(sm, 1, sum);
-    }
-    const SlKey key{th, e_rand ? e_rand + o : nullptr, tmax, F, mode};
-    if (nh <= kSlHeld * kSlThreads)
-      select_tokens<true>(sm, key, nh, L, o, out);
-    else
-      select_tokens<false>(sm, key, nh, L, o, out);
+    __syncthreads();  // sm.red is written again
   }
 }
 
@@ -416,9 +449,11 @@ hipError_t launch_stochastic_length(int32_t B, const int64_t* offs, const int64_
                                     const double* u_keep, const double* e_rand, int64_t* new_len,
                                     int64_t* new_offs, int64_t* gather, hipStream_t s) {
   if (B <= 0) return hipSuccess;
-  const dim3 grid((unsigned)(B < 65535 ? B : 65535));
+  const int lg = sl_group_lg(B);
+  const int groups = (B + (1 << lg) - 1) >> lg;
+  const dim3 grid((unsigned)(groups < 65535 ? groups : 65535));
   if (B <= kSlFusedSeqs) {
-    hipLaunchKernelGGL(sl_select_kernel<true>, grid, dim3(kSlThreads), 0, s, B, offs, ts, nt, L,
+    hipLaunchKernelGGL(sl_select_kernel<true>, grid, dim3(kSlThreads), 0, s, B, lg, offs, ts, nt, L,
                        keep_num, mode, u_keep, e_rand, new_offs, gather);
     return hipGetLastError();
   }
@@ -429,7 +464,7 @@ hipError_t launch_stochastic_length(int32_t B, const int64_t* offs, const int64_
   if (e != hipSuccess) return e;
   e = launch_complete_cumsum(B, new_len, new_offs, 0, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sl_select_kernel<false>, grid, dim3(kSlThreads), 0, s, B, offs, ts, nt, L,
+  hipLaunchKernelGGL(sl_select_kernel<false>, grid, dim3(kSlThreads), 0, s, B, lg, offs, ts, nt, L,
                      keep_num, mode, u_keep, e_rand, new_offs, gather);
   return hipGetLastError();
 }

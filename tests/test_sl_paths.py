@@ -64,3 +64,19 @@ def test_gather_wide_rows(rows, row_bytes):
     """Rows of more words than the lanes that share one: a row is spread over
     workgroups, the last of them partly filled."""
     test_gather_row_widths(row_bytes, 0, rows)
+
+
+@pytest.mark.parametrize("mode", ts.MODES)
+@pytest.mark.parametrize("count", [1024, 1025, 1027, 4096, 4097])
+def test_sl_sequences_per_workgroup(oracle_mod, mode, count):
+    """Batches on both sides of the sizes where a workgroup takes 1, 4 and 16
+    sequences, of which some stay whole and some are shortened, long ones and
+    empty ones among them, the last group partly filled."""
+    rng = np.random.default_rng(count)
+    lengths = rng.integers(0, 60, count)
+    lengths[[3, 100, 101, 255, count - 1]] = (1025, 4097, 0, 9000, 2000)
+    nt = np.minimum(lengths, rng.integers(0, 30, count))
+    offs, t = ts._batch(lengths, 9, dup_ts=True)
+    u, e = inputs.make_sl_draws(count, offs[-1], seed=count)
+    e[:] = np.floor(e * 8.0)  # few distinct keys: ties across threads
+    ts._check(ts._hs(), oracle_mod, offs, t, nt, 20, 20.0 ** 2.1, mode, u, e)
