@@ -168,8 +168,9 @@ struct Walk {
       ra = (int)max(r0 - o, (int64_t)0);
       rb = (int)min(r0 + kRows - 1 - o, (int64_t)L - 1);
       if (rb < ra) continue;
+      // Tiles start at multiples of 32 of the sequence, whatever the rows.
       if (rows_are_keys) {
-        x0 = ra;
+        x0 = ra & ~(kRows - 1);
         xend = ra >= n_h ? rb + 1 : L;  // a candidate key is seen by itself only
       } else {
         x0 = 0;

@@ -107,3 +107,24 @@ def test_f32_masked_infinities_leave_the_bits(hs, name, value):
         first = first or got
         for a, b in zip(first, got):
             assert torch.equal(a.nan_to_num(nan=7.0), b.nan_to_num(nan=7.0))
+
+
+def test_f32_rows_do_not_depend_on_their_place(hs):
+    """out, dq, dk and dv of a sequence have the same bits wherever it lies in
+    a batch and whatever lies beside it."""
+    lengths = (5, 100, 16, 17, 1, 64, 33, 12)
+    nt = (2, 40, 16, 0, 0, 1, 30, 0)
+    batch = inputs.make_batch(2, seed=21, lengths=lengths, num_heads=2, d_qk=64, d_v=32,
+                              max_seq_len=100, dtype="f32", num_targets=nt)
+    outs = {}
+    for order in (range(8), (7, 6, 5, 4, 3, 2, 1, 0), (4, 1), (0, 2, 4, 7, 5), (4, 4, 3, 6)):
+        part = gu.sub_batch(batch, list(order))
+        d = gu.dev_inputs(part)
+        got = [gu.gpu_fwd(hs, d, part), *gu.gpu_bwd(hs, d, part)[:3]]
+        torch.cuda.synchronize()
+        o = 0
+        for b in order:
+            rows = [g[o:o + lengths[b]] for g in got]
+            o += lengths[b]
+            for name, x, y in zip(("out", "dq", "dk", "dv"), outs.setdefault(b, rows), rows):
+                assert torch.equal(x, y), f"{name} of sequence {b} in {list(order)}"
