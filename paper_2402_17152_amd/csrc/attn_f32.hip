@@ -24,8 +24,10 @@
 // Bound by the latency of one tile after another: a tile's loads (operand
 // rows, timestamps, the 64 entries of rab_pos it can use) are issued while
 // the tile before is computed.  One thread per (row, head) with the keys
-// one by one, as before, took 47 + 58 + 60 us (forward, dQ, dK / dV) on four
-// sequences of up to 128 tokens (2 heads of 32).
+// one by one took 47 + 58 + 60 us (forward, dQ, dK / dV) on four sequences
+// of up to 128 tokens (2 heads of 32).  Rows of sequences of at most 16
+// tokens, of which a workgroup can hold 32, go row by row instead, 8 threads
+// to a row.
 #include "kernels.h"
 
 namespace hstu {
@@ -35,6 +37,7 @@ namespace {
 constexpr int kRows = 32;      // token rows of a workgroup, and width of a tile
 constexpr int kScoreLd = 36;   // row pitch of the score tiles
 constexpr int kThreads = 256;
+constexpr int kBuckets = 64;   // time buckets that a 64-bit difference can reach
 
 __device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
@@ -42,21 +45,6 @@ __device__ __forceinline__ f32x4 mfma16x16x4(float a, float b, f32x4 c) {
 
 __device__ __forceinline__ bool not_finite(float x) {
   return (__float_as_uint(x) & 0x7f800000u) == 0x7f800000u;
-}
-
-// Last sequence b with seq_offsets[b] <= r (64 probes at a time).
-__device__ __forceinline__ int find_seq(const JaggedArgs& ja, int64_t r) {
-  const int lane = threadIdx.x & 63;
-  int lo = 0, hi = ja.num_seqs;  // seq_offsets[lo] <= r < seq_offsets[hi]
-  while (hi - lo > 1) {
-    const int step = (hi - lo + 63) >> 6;
-    const int x = min(lo + (lane + 1) * step, hi);
-    const uint64_t above = __ballot(ja.seq_offsets[x] > r);  // lane 63's probe is hi: never empty
-    const int f = __builtin_ctzll(above);
-    hi = min(lo + (f + 1) * step, hi);
-    lo = lo + f * step;
-  }
-  return __builtin_amdgcn_readfirstlane(lo);
 }
 
 // One operand tile of 32 rows of D floats: global -> registers -> LDS rows
@@ -144,60 +132,118 @@ __device__ __forceinline__ void outer_tile(const float* w, const float* t, int f
     }
 }
 
+// Rows of a workgroup in sequences of at most kShort tokens go row by row
+// (short_* below), the others by tiles.  The line depends on the sequence
+// alone, so a row's sums run in one order wherever it lies in a batch.  By
+// tiles, 32 rows of one-token sequences took 32 passes: 596 against 37 us
+// forward for 20000 such tokens (8 heads of 64), 99 against 50 at 8 tokens;
+// at 16 tokens the tiles are ahead, 59 against 74.
+constexpr int kShort = 16;
+
+__device__ __forceinline__ int pack_short(int L, int n_h, int i) { return L | n_h << 8 | i << 16; }
+
+// The sequences that a workgroup's 32 rows belong to.
+struct Seqs {
+  // Those that go by tiles, in order (two full ones do not fit the rows).
+  static constexpr int kLong = (kRows - 2) / (kShort + 1) + 2;
+  int64_t o[kLong];
+  int L[kLong], n_h[kLong];
+  int short_row[kRows];  // rows of the others (see pack_short), 0 elsewhere
+};
+
 // The (sequence, tile) pairs a workgroup visits: rows r0 .. r0 + 31 (global
 // tokens), tiles of 32 of the other side.  All values are uniform.
 struct Walk {
-  int seq, seq_end;        // sequence index; B
   int64_t o, r0;           // first token of the sequence; of the rows
   int L, n_h;              // its length and history tokens
   int ra, rb;              // rows of this sequence: indices ra .. rb
   int x0, xend;            // current tile's first index, end of the tiles
-  bool rows_are_keys;
+  int seq, seqs;           // which of the sequences that go by tiles; their number
+  bool rows_are_keys, any_short;
 
-  __device__ __forceinline__ void enter(const JaggedArgs& ja) {
-    for (;; seq++) {
-      if (seq >= seq_end) return;
-      o = ja.seq_offsets[seq];
-      if (o > r0 + kRows - 1) {
-        seq = seq_end;
-        return;
+  // Fills q from the offsets and enters the first sequence.  64 sequences at
+  // a time, one per lane: first probes for the one of row r0, until what is
+  // left of the search is one such chunk, then that chunk and, while the
+  // rows go on, the ones after it.  Wave 0 writes (read after a barrier).
+  __device__ __forceinline__ void start(const JaggedArgs& ja, int64_t first_row, bool keys,
+                                        Seqs& q) {
+    const int lane = threadIdx.x & 63, B = ja.num_seqs;
+    rows_are_keys = keys;
+    r0 = first_row;
+    seq = seqs = 0;
+    any_short = false;
+    if (threadIdx.x < kRows) q.short_row[threadIdx.x] = 0;
+    int lo = 0, hi = B;  // seq_offsets[lo] <= r0 < seq_offsets[hi]
+    int64_t base = 0;    // seq_offsets[lo]
+    while (hi - lo > 64) {
+      const int step = (hi - lo + 63) >> 6;
+      const int64_t at = ja.seq_offsets[min(lo + (lane + 1) * step, hi)];
+      // (lane 63's probe is hi: some lane's lies above)
+      const int f = __builtin_amdgcn_readfirstlane(__builtin_ctzll(__ballot(at > r0)));
+      base = f ? readlane64(at, f - 1) : base;
+      hi = min(lo + (f + 1) * step, hi);
+      lo += f * step;
+    }
+    for (;;) {
+      const int s = lo + lane;
+      const int64_t end = ja.seq_offsets[min(s + 1, B)];
+      const int64_t before = __shfl_up(end, 1, 64), so = lane ? before : base;
+      const int len = s < B && end > r0 && so < r0 + kRows ? (int)(end - so) : 0;
+      int nh = len;
+      if (len && ja.num_targets) nh -= (int)ja.num_targets[s];
+      if (threadIdx.x < 64 && len > 0 && len <= kShort) {
+        const int first = (int)(so - r0);
+        for (int i = max(-first, 0); i < len && first + i < kRows; i++)
+          q.short_row[first + i] = pack_short(len, nh, i);
       }
-      L = (int)(ja.seq_offsets[seq + 1] - o);
-      if (L <= 0) continue;
-      n_h = L - (ja.num_targets ? (int)ja.num_targets[seq] : 0);
-      ra = (int)max(r0 - o, (int64_t)0);
-      rb = (int)min(r0 + kRows - 1 - o, (int64_t)L - 1);
-      if (rb < ra) continue;
-      // Tiles start at multiples of 32 of the sequence, whatever the rows.
-      if (rows_are_keys) {
-        x0 = ra & ~(kRows - 1);
-        xend = ra >= n_h ? rb + 1 : L;  // a candidate key is seen by itself only
-      } else {
-        x0 = 0;
-        xend = rb + 1;
-        skip();
+      any_short |= __ballot(len > 0 && len <= kShort) != 0;
+      for (uint64_t m = __ballot(len > kShort); m; m &= m - 1) {
+        const int f = __builtin_ctzll(m);
+        const int64_t fo = readlane64(so, f);
+        const int fl = __builtin_amdgcn_readlane(len, f), fh = __builtin_amdgcn_readlane(nh, f);
+        if (seqs == 0) enter(fo, fl, fh);
+        if (threadIdx.x == 0) {
+          q.o[seqs] = fo;
+          q.L[seqs] = fl;
+          q.n_h[seqs] = fh;
+        }
+        seqs++;
       }
-      return;
+      base = readlane64(end, 63);
+      lo += 64;
+      if (lo >= B || base >= r0 + kRows) break;
+    }
+  }
+  __device__ __forceinline__ void enter(int64_t first, int len, int hist) {
+    o = first;
+    L = len;
+    n_h = hist;
+    ra = (int)max(r0 - o, (int64_t)0);
+    rb = (int)min(r0 + kRows - 1 - o, (int64_t)L - 1);
+    // Tiles start at multiples of 32 of the sequence, whatever the rows.
+    if (rows_are_keys) {
+      x0 = ra & ~(kRows - 1);
+      xend = ra >= n_h ? rb + 1 : L;  // a candidate key is seen by itself only
+    } else {
+      x0 = 0;
+      xend = rb + 1;
+      skip();
     }
   }
   // Key tiles made only of candidates before every row: nothing is kept.
   __device__ __forceinline__ void skip() {
     if (!rows_are_keys && x0 >= n_h && x0 + kRows - 1 < ra) x0 = max(x0, ra & ~(kRows - 1));
   }
-  __device__ __forceinline__ void start(const JaggedArgs& ja, int64_t first_row, bool keys) {
-    rows_are_keys = keys;
-    r0 = first_row;
-    seq_end = ja.num_seqs;
-    seq = find_seq(ja, first_row);
-    enter(ja);
-  }
-  __device__ __forceinline__ bool done() const { return seq >= seq_end; }
-  __device__ __forceinline__ void next(const JaggedArgs& ja) {
+  __device__ __forceinline__ bool done() const { return seq >= seqs; }
+  __device__ __forceinline__ void next(const Seqs& q) {
     x0 += kRows;
     skip();
-    if (x0 >= xend) {
-      seq++;
-      enter(ja);
+    if (x0 >= xend && ++seq < seqs) {
+      const uint64_t fo = (uint64_t)q.o[seq];
+      const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)fo);
+      const uint32_t hi = __builtin_amdgcn_readfirstlane((int)(uint32_t)(fo >> 32));
+      enter((int64_t)((uint64_t)hi << 32 | lo), __builtin_amdgcn_readfirstlane(q.L[seq]),
+            __builtin_amdgcn_readfirstlane(q.n_h[seq]));
     }
   }
   // Index of rab_pos that entry 0 of the tile's 64-entry window holds:
@@ -237,11 +283,120 @@ struct FwdLds {
   __align__(16) float p[kRows * kScoreLd];
   int64_t t[kRows];
   float win[64];
-  float tab[256];
+  float tab[kBuckets];
   // Whether the tile of this parity holds an infinity or a NaN: set before a
   // tile's first barrier, read after its second, cleared between the next's.
   int special[2];
+  Seqs seqs;
 };
+
+// ---- rows of short sequences: 8 threads each, a wave 8 rows ----
+// Thread `sub` of a row holds features 4 (sub + 8 e) .. +3 of it.
+
+struct ShortRow {
+  int L, n_h, i;     // its sequence (L = 0: not a short one), its index there
+  int64_t r;         // the token (r0 for a row that is none)
+  __device__ __forceinline__ ShortRow(const int* short_row, int64_t r0) {
+    const int x = threadIdx.x >> 3, v = short_row[x];
+    L = v & 255;
+    n_h = v >> 8 & 255;
+    i = v >> 16;
+    r = L ? r0 + x : r0;
+  }
+};
+
+template <int D>
+__device__ __forceinline__ void load_slice(const float* row, int sub, f32x4 (&v)[D / 32]) {
+#pragma unroll
+  for (int e = 0; e < D / 32; e++) v[e] = *reinterpret_cast<const f32x4*>(row + 4 * (sub + 8 * e));
+}
+
+template <int D>
+__device__ __forceinline__ void store_slice(float* row, int sub, const f32x4 (&v)[D / 32],
+                                            float scale) {
+#pragma unroll
+  for (int e = 0; e < D / 32; e++)
+    *reinterpret_cast<f32x4*>(row + 4 * (sub + 8 * e)) = v[e] * scale;
+}
+
+// Dot product over the row's 8 threads, in each of them.
+template <int D>
+__device__ __forceinline__ float dot_slices(const f32x4 (&a)[D / 32], const f32x4 (&b)[D / 32]) {
+  float s = 0.0f;
+#pragma unroll
+  for (int e = 0; e < D / 32; e++)
+#pragma unroll
+    for (int m = 0; m < 4; m++) s = __builtin_fmaf(a[e][m], b[e][m], s);
+#pragma unroll
+  for (int off = 1; off < 8; off <<= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
+template <int D>
+__device__ __forceinline__ void add_slice(f32x4 (&acc)[D / 32], float w, const f32x4 (&v)[D / 32]) {
+#pragma unroll
+  for (int e = 0; e < D / 32; e++)
+#pragma unroll
+    for (int m = 0; m < 4; m++) acc[e][m] = __builtin_fmaf(w, v[e][m], acc[e][m]);
+}
+
+// Largest of the wave's 8 rows' counts.
+__device__ __forceinline__ int rows_max(int v) {
+#pragma unroll
+  for (int off = 8; off < 64; off <<= 1) v = max(v, __shfl_xor(v, off, 64));
+  return __builtin_amdgcn_readfirstlane(v);
+}
+
+// Key of row i at distance d in position: itself, then the history backwards.
+__device__ __forceinline__ int key_at(const ShortRow& w, int d) {
+  return d ? min(w.i, w.n_h) - d : w.i;
+}
+__device__ __forceinline__ int keys_of(const ShortRow& w) {
+  return !w.L ? 0 : w.i < w.n_h ? w.i + 1 : w.n_h + 1;
+}
+
+// Pairs in flight: as many as leave the registers of the tile loop unchanged.
+template <int DQK, int DV>
+constexpr int kShortStep = DQK + DV <= 128 ? 4 : 2;
+
+template <int DQK, int DV, typename Lds>
+__device__ __forceinline__ void short_fwd(const Lds& sm, const JaggedArgs& ja, const Tensors& t,
+                                          float* __restrict__ out, int64_t r0, int head) {
+  const ShortRow w(sm.seqs.short_row, r0);
+  const int steps = rows_max(keys_of(w));
+  if (!steps) return;
+  constexpr int U = kShortStep<DQK, DV>;
+  const int sub = threadIdx.x & 7, H = ja.num_heads, N = ja.max_seq_len;
+  const float* kg = (const float*)t.k + head * DQK;
+  const float* vg = (const float*)t.v + head * DV;
+  f32x4 q[DQK / 32], acc[DV / 32];
+  load_slice<DQK>(sm.q + (threadIdx.x >> 3) * (DQK + 4), sub, q);
+#pragma unroll
+  for (int e = 0; e < DV / 32; e++) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t ti = ja.timestamps[w.r];
+  for (int d0 = 0; d0 < steps; d0 += U) {
+    f32x4 k[U][DQK / 32], v[U][DV / 32];
+    int64_t tj[U];
+    float pos[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      ok[u] = d0 + u < keys_of(w);
+      const int64_t r = ok[u] ? w.r + key_at(w, d0 + u) - w.i : w.r;
+      load_slice<DQK>(kg + r * t.k_stride, sub, k[u]);
+      load_slice<DV>(vg + r * t.v_stride, sub, v[u]);
+      tj[u] = ja.timestamps[r];
+      pos[u] = ja.rab_pos[max(N - 1 - d0 - u, 0)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const float s = dot_slices<DQK>(q, k[u]) +
+                      (pos[u] + sm.tab[time_bucket64(ti - tj[u], ja.num_buckets)]);
+      if (ok[u]) add_slice<DV>(acc, s * sigmoid_fast(s), v[u]);
+    }
+  }
+  if (w.L) store_slice<DV>(out + (w.r * H + head) * DV, sub, acc, 1.0f / (float)N);
+}
 
 template <int DQK, int DV>
 __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensors t,
@@ -254,7 +409,7 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
   const float* kg = (const float*)t.k + head * DQK;
   const float* vg = (const float*)t.v + head * DV;
   Walk w;
-  w.start(ja, r0, false);
+  w.start(ja, r0, false, sm.seqs);
   TileRegs<DQK> kr;
   TileRegs<DV> vr;
   SideRegs sr;
@@ -271,7 +426,7 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
             (int)min((int64_t)kRows, T - r0), tid);
     qr.store(sm.q, tid, &ignored);
   }
-  if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
+  if (tid < min(ja.num_buckets, kBuckets)) sm.tab[tid] = ja.rab_time[tid];
   if (tid < 2) sm.special[tid] = 0;
   __syncthreads();
   const int64_t my_r = r0 + 16 * wr + n;
@@ -289,7 +444,7 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
     sr.store(sm.t, sm.win, tid);
     __syncthreads();
     if (tid == 0) sm.special[par ^ 1] = 0;
-    w.next(ja);
+    w.next(sm.seqs);
     if (!w.done()) load(w);
     const f32x4 s = dot_tile<DQK>(sm.k + 16 * wc * (DQK + 4), sm.q + 16 * wr * (DQK + 4), lane,
                                   f32x4{0.0f, 0.0f, 0.0f, 0.0f});
@@ -319,11 +474,15 @@ __global__ __launch_bounds__(kThreads) void fwd_f32_kernel(JaggedArgs ja, Tensor
                    },
                    acc);
   }
+  if (w.any_short) {
+    __syncthreads();
+    short_fwd<DQK, DV>(sm, ja, t, out, r0, head);
+  }
   const float invN = 1.0f / (float)N;
 #pragma unroll
   for (int r = 0; r < 4; r++) {
     const int64_t row = r0 + 16 * wr + 4 * g + r;
-    if (row < T)
+    if (row < T && !(w.any_short && sm.seqs.short_row[16 * wr + 4 * g + r]))
 #pragma unroll
       for (int nb = 0; nb < DV / 32; nb++)
         out[(row * H + head) * DV + wc * (DV / 2) + 16 * nb + n] = acc[nb][r] * invN;
@@ -342,11 +501,13 @@ struct BwdLds {
   __align__(16) float ds[kRows * kScoreLd];
   int64_t t[kRows];
   float win[64];
-  float tab[256];
-  double time_acc[256];
+  float tab[kBuckets];
+  double time_acc[kBuckets];
+  double short_pos[kShort];
   // Whether the tile of this parity holds an infinity or a NaN: set before a
   // tile's first barrier, read after its second, cleared between the next's.
   int special[2];
+  Seqs seqs;
 };
 
 // Weight SiLU(s) and dS = dP SiLU'(s) of one pair (0, 0 if masked).
@@ -354,6 +515,128 @@ __device__ __forceinline__ void pair_grad(float s, float dp, float* p, float* ds
   const float sg = sigmoid_fast(s);
   *p = s * sg;
   *ds = dp * (sg + *p * (1.0f - sg));
+}
+
+// dQ and the bias gradients of short rows: position sums by distance into
+// sm.short_pos, time sums as in the tile loop.
+template <int DQK, int DV>
+__device__ __forceinline__ void short_bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& ja,
+                                               const Tensors& t, float* __restrict__ dq,
+                                               int64_t r0, int head) {
+  const ShortRow w(sm.seqs.short_row, r0);
+  const int steps = rows_max(keys_of(w));
+  if (!steps) return;
+  constexpr int U = kShortStep<DQK, DV>;
+  const int sub = threadIdx.x & 7, H = ja.num_heads, N = ja.max_seq_len;
+  const float* kg = (const float*)t.k + head * DQK;
+  const float* vg = (const float*)t.v + head * DV;
+  f32x4 q[DQK / 32], g[DV / 32], acc[DQK / 32];
+  load_slice<DQK>(sm.own_qk + (threadIdx.x >> 3) * (DQK + 4), sub, q);
+  load_slice<DV>(sm.own_v + (threadIdx.x >> 3) * (DV + 4), sub, g);
+#pragma unroll
+  for (int e = 0; e < DQK / 32; e++) acc[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t ti = ja.timestamps[w.r];
+  int run_b = -1;
+  double run = 0.0;
+  for (int d0 = 0; d0 < steps; d0 += U) {
+    f32x4 k[U][DQK / 32], v[U][DV / 32];
+    int64_t tj[U];
+    float pos[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      ok[u] = d0 + u < keys_of(w);
+      const int64_t r = ok[u] ? w.r + key_at(w, d0 + u) - w.i : w.r;
+      load_slice<DQK>(kg + r * t.k_stride, sub, k[u]);
+      load_slice<DV>(vg + r * t.v_stride, sub, v[u]);
+      tj[u] = ja.timestamps[r];
+      pos[u] = ja.rab_pos[max(N - 1 - d0 - u, 0)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const int b = time_bucket64(ti - tj[u], ja.num_buckets);
+      const float s = dot_slices<DQK>(q, k[u]) + (pos[u] + sm.tab[b]);
+      const float dp = dot_slices<DV>(g, v[u]);
+      double sum = 0.0;  // of the wave's rows
+      if (ok[u]) {
+        float p, ds;
+        pair_grad(s, dp, &p, &ds);
+        add_slice<DQK>(acc, ds, k[u]);
+        sum = (double)ds;
+        if (sub == 0) {
+          if (b != run_b) {
+            if (run_b >= 0) unsafeAtomicAdd(&sm.time_acc[run_b], run);
+            run_b = b;
+            run = 0.0;
+          }
+          run += sum;
+        }
+      }
+#pragma unroll
+      for (int off = 8; off < 64; off <<= 1) sum += __shfl_xor(sum, off, 64);
+      if ((threadIdx.x & 63) == 0 && d0 + u < steps)
+        unsafeAtomicAdd(&sm.short_pos[d0 + u], sum);
+    }
+  }
+  if (run_b >= 0) unsafeAtomicAdd(&sm.time_acc[run_b], run);
+  if (w.L) store_slice<DQK>(dq + (w.r * H + head) * DQK, sub, acc, 1.0f / (float)N);
+}
+
+// dK and dV of short rows (as keys).
+template <int DQK, int DV>
+__device__ __forceinline__ void short_bwd_keys(const BwdLds<DQK, DV>& sm, const JaggedArgs& ja,
+                                               const Tensors& t, const float* __restrict__ dO,
+                                               float* __restrict__ dk, float* __restrict__ dv,
+                                               int64_t r0, int head) {
+  const ShortRow w(sm.seqs.short_row, r0);
+  const int count = !w.L ? 0 : w.i < w.n_h ? w.L - w.i : 1;  // rows that see the key
+  const int steps = rows_max(count);
+  if (!steps) return;
+  constexpr int U = kShortStep<DQK, DV>;
+  const int sub = threadIdx.x & 7, H = ja.num_heads, N = ja.max_seq_len;
+  const float* qg = (const float*)t.q + head * DQK;
+  const float* gg = dO + head * DV;
+  const int64_t g_stride = (int64_t)H * DV;
+  f32x4 k[DQK / 32], v[DV / 32], ak[DQK / 32], av[DV / 32];
+  load_slice<DQK>(sm.own_qk + (threadIdx.x >> 3) * (DQK + 4), sub, k);
+  load_slice<DV>(sm.own_v + (threadIdx.x >> 3) * (DV + 4), sub, v);
+#pragma unroll
+  for (int e = 0; e < DQK / 32; e++) ak[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+  for (int e = 0; e < DV / 32; e++) av[e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int64_t tj = ja.timestamps[w.r];
+  for (int d0 = 0; d0 < steps; d0 += U) {
+    f32x4 q[U][DQK / 32], g[U][DV / 32];
+    int64_t ti[U];
+    float pos[U];
+    bool ok[U];
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      ok[u] = d0 + u < count;
+      const int i = ok[u] ? w.i + d0 + u : w.i;
+      const int64_t r = w.r + i - w.i;
+      load_slice<DQK>(qg + r * t.q_stride, sub, q[u]);
+      load_slice<DV>(gg + r * g_stride, sub, g[u]);
+      ti[u] = ja.timestamps[r];
+      pos[u] = ja.rab_pos[(N - 1) + bias_pos(w.i, w.n_h) - bias_pos(i, w.n_h)];
+    }
+#pragma unroll
+    for (int u = 0; u < U; u++) {
+      const float s = dot_slices<DQK>(q[u], k) +
+                      (pos[u] + sm.tab[time_bucket64(ti[u] - tj, ja.num_buckets)]);
+      const float dp = dot_slices<DV>(g[u], v);
+      if (ok[u]) {
+        float p, ds;
+        pair_grad(s, dp, &p, &ds);
+        add_slice<DV>(av, p, g[u]);
+        add_slice<DQK>(ak, ds, q[u]);
+      }
+    }
+  }
+  if (w.L) {
+    store_slice<DQK>(dk + (w.r * H + head) * DQK, sub, ak, 1.0f / (float)N);
+    store_slice<DV>(dv + (w.r * H + head) * DV, sub, av, 1.0f / (float)N);
+  }
 }
 
 // Kind (a): dQ and the bias gradients of 32 query rows.
@@ -369,7 +652,7 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
   const float* kg = (const float*)t.k + head * DQK;
   const float* vg = (const float*)t.v + head * DV;
   Walk w;
-  w.start(ja, r0, false);
+  w.start(ja, r0, false, sm.seqs);
   TileRegs<DQK> kr;
   TileRegs<DV> vr;
   SideRegs sr;
@@ -389,8 +672,9 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     qr.store(sm.own_qk, tid, &ignored);
     gr.store(sm.own_v, tid, &ignored);
   }
-  if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
-  sm.time_acc[tid] = 0.0;
+  if (tid < min(ja.num_buckets, kBuckets)) sm.tab[tid] = ja.rab_time[tid];
+  if (tid < kBuckets) sm.time_acc[tid] = 0.0;
+  if (tid < kShort) sm.short_pos[tid] = 0.0;
   if (tid < 2) sm.special[tid] = 0;
   __syncthreads();
   const int64_t my_r = r0 + 16 * wr + n;
@@ -413,7 +697,7 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     sr.store(sm.t, sm.win, tid);
     __syncthreads();
     if (tid == 0) sm.special[par ^ 1] = 0;
-    w.next(ja);
+    w.next(sm.seqs);
     if (!w.done()) load(w);
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     const f32x4 s = dot_tile<DQK>(sm.tile_qk[par] + 16 * wc * (DQK + 4),
@@ -474,7 +758,7 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
       // (sum may be NaN: it compares unequal to 0 and is added)
       carry = before;
       // The walk's last tile of this sequence: what was carried is complete.
-      if (w.done() || w.seq != cur.seq || w.x0 != cur.x0 + kRows) {
+      if (w.seq != cur.seq || w.x0 != cur.x0 + kRows) {
         const int last = off - 32;
         if (lane < 32 && carry != 0.0 && last >= 0 && last < N)
           unsafeAtomicAdd(&pos_acc[(N - 1) - last], carry);
@@ -491,18 +775,24 @@ __device__ __forceinline__ void bwd_rows(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     }
   }
   if (run_b >= 0) unsafeAtomicAdd(&sm.time_acc[run_b], run);
+  if (w.any_short) {
+    __syncthreads();
+    short_bwd_rows<DQK, DV>(sm, ja, t, dq, r0, head);
+  }
   const float invN = 1.0f / (float)N;
 #pragma unroll
   for (int r = 0; r < 4; r++) {
     const int64_t row = r0 + 16 * wr + 4 * g + r;
-    if (row < T)
+    if (row < T && !(w.any_short && sm.seqs.short_row[16 * wr + 4 * g + r]))
 #pragma unroll
       for (int nb = 0; nb < DQK / 32; nb++)
         dq[(row * H + head) * DQK + wc * (DQK / 2) + 16 * nb + n] = acc[nb][r] * invN;
   }
   __syncthreads();
-  const double tsum = sm.time_acc[tid];
-  if (tsum != 0.0) unsafeAtomicAdd(&time_acc[tid], tsum);
+  if (tid < kBuckets && sm.time_acc[tid] != 0.0)
+    unsafeAtomicAdd(&time_acc[tid], sm.time_acc[tid]);
+  if (tid < kShort && sm.short_pos[tid] != 0.0)
+    unsafeAtomicAdd(&pos_acc[(N - 1) - tid], sm.short_pos[tid]);
 }
 
 // Kind (b): dK and dV of 32 key rows.
@@ -519,7 +809,7 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
   const float* gg = dO + head * DV;
   const int64_t g_stride = (int64_t)H * DV;
   Walk w;
-  w.start(ja, r0, true);
+  w.start(ja, r0, true, sm.seqs);
   TileRegs<DQK> qr;
   TileRegs<DV> gr;
   SideRegs sr;
@@ -539,7 +829,7 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     kr.store(sm.own_qk, tid, &ignored);
     vr.store(sm.own_v, tid, &ignored);
   }
-  if (tid < ja.num_buckets) sm.tab[tid] = ja.rab_time[tid];
+  if (tid < min(ja.num_buckets, kBuckets)) sm.tab[tid] = ja.rab_time[tid];
   if (tid < 2) sm.special[tid] = 0;
   __syncthreads();
   const int64_t my_r = r0 + 16 * wr + n;  // the lane's key
@@ -557,7 +847,7 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     sr.store(sm.t, sm.win, tid);
     __syncthreads();
     if (tid == 0) sm.special[par ^ 1] = 0;
-    w.next(ja);
+    w.next(sm.seqs);
     if (!w.done()) load(w);
     const f32x4 zero = {0.0f, 0.0f, 0.0f, 0.0f};
     const f32x4 s = dot_tile<DQK>(sm.tile_qk[par] + 16 * wc * (DQK + 4),
@@ -593,11 +883,15 @@ __device__ __forceinline__ void bwd_keys(BwdLds<DQK, DV>& sm, const JaggedArgs& 
     outer_tile<DQK>(sm.ds + 16 * wr * kScoreLd, sm.tile_qk[par], wc * (DQK / 2), lane, special,
                     keep, ak);
   }
+  if (w.any_short) {
+    __syncthreads();
+    short_bwd_keys<DQK, DV>(sm, ja, t, dO, dk, dv, r0, head);
+  }
   const float invN = 1.0f / (float)N;
 #pragma unroll
   for (int r = 0; r < 4; r++) {
     const int64_t row = r0 + 16 * wr + 4 * g + r;
-    if (row < T) {
+    if (row < T && !(w.any_short && sm.seqs.short_row[16 * wr + 4 * g + r])) {
 #pragma unroll
       for (int nb = 0; nb < DQK / 32; nb++)
         dk[(row * H + head) * DQK + wc * (DQK / 2) + 16 * nb + n] = ak[nb][r] * invN;

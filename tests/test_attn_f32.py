@@ -109,6 +109,32 @@ def test_f32_masked_infinities_leave_the_bits(hs, name, value):
             assert torch.equal(a.nan_to_num(nan=7.0), b.nan_to_num(nan=7.0))
 
 
+SHORT = {
+    "line": dict(lengths=(16, 17, 15, 18, 16, 1, 0, 33, 2, 17, 16, 40, 16)),
+    "line_candidates": dict(lengths=(16, 17, 16, 20, 3, 5, 16, 1, 2), num_targets=(
+        15, 16, 1, 20, 3, 1, 16, 1, 0)),
+    "empties": dict(lengths=(3,) + (0,) * 130 + (20, 4) + (0,) * 70 + (16, 31, 2)),
+    "ones": dict(lengths=(1,) * 97),
+    "twos": dict(lengths=(2,) * 50 + (70,) + (2,) * 7, num_targets=(1, 0) * 25 + (30,) + (2,) * 7),
+}
+
+
+@pytest.mark.parametrize("dqk,dv", [(32, 32), (64, 64), (128, 128), (32, 128), (128, 32)])
+@pytest.mark.parametrize("case", sorted(SHORT))
+def test_f32_short_sequences(hs, oracle_mod, case, dqk, dv):
+    """Sequences on both sides of the 16 tokens up to which rows go one by
+    one, mixed inside 32-row blocks, with runs of empty ones between them."""
+    c = SHORT[case]
+    batch = inputs.make_batch(2, seed=70 + len(case), num_heads=2, d_qk=dqk, d_v=dv,
+                              max_seq_len=max(c["lengths"]), dtype="f32", **c)
+    d = gu.dev_inputs(batch)
+    gu.assert_close("out", gu.to_f64(gu.gpu_fwd(hs, d, batch)), gu.oracle_fwd(oracle_mod, batch),
+                    1e-5, "f32")
+    for name, g, r in zip(("dq", "dk", "dv", "d_rab_pos", "d_rab_time"), gu.gpu_bwd(hs, d, batch),
+                          gu.oracle_bwd(oracle_mod, batch)):
+        gu.assert_close(name, gu.to_f64(g), r, 1e-5, "f32")
+
+
 def test_f32_rows_do_not_depend_on_their_place(hs):
     """out, dq, dk and dv of a sequence have the same bits wherever it lies in
     a batch and whatever lies beside it."""
