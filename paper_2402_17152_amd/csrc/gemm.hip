@@ -7,22 +7,24 @@
 // accumulation on v_mfma_f32_32x32x16_bf16.  An operand is stored either
 // k-contiguous (A[m][k], B[n][k]: activations and [out][in] weights in the
 // forward) or k-major (A[k][m], B[k][n]: the transposed operands of the
-// gradients).  A workgroup of 4 waves computes a 256 x 128 tile (128 x 128
-// when the larger ones would not fill the chip), each wave 128 x 64 (64 x
-// 64), over k-steps of 32.  A k-contiguous tile gives a lane its 8
+// gradients).  A workgroup computes a 256 x 256 tile with 8 waves (the
+// products without a SiLU), a 256 x 128 tile with 4 (f_1's forward), or, when
+// those would not fill the chip, a 128 x 128 tile with 4; each wave 128 x 64
+// (64 x 64), over k-steps of 32.  A k-contiguous tile gives a lane its 8
 // contraction elements in one 16-byte LDS read; a k-major tile is read with
 // two transposing reads (ds_read_b64_tr_b16) that return the same 8 elements
 // in the same order.  The products are computed transposed (B's fragment as
 // the matrix core's first operand), so a lane owns one output row and 4
 // consecutive columns per register group.
 //
-// Staging: LDS DMA into a ring of three k-steps, issued two to three steps
-// ahead, in a layout without padding whose 16-byte chunks are permuted so
-// that every LDS read spreads over all banks.  The fragments of a half step
-// are read while the matrix cores work on the half step before, across the
-// one barrier per step, so neither the LDS nor the memory latency is in the
-// chain; two workgroups per CU overlap one's epilogue with the other's
-// products.
+// Staging: LDS DMA into a ring of three k-steps (four, 131 KB, for 256 x 256
+// tiles), issued as many steps ahead less at most one, in a layout without
+// padding whose 16-byte chunks are permuted so that every LDS read spreads
+// over all banks.  The fragments of a half step are read while the matrix
+// cores work on the half step before, across the one barrier per step, so
+// neither the LDS nor the memory latency is in the chain.  Of the 4-wave
+// tiles two workgroups share a CU and overlap one's epilogue with the
+// other's products; a 256 x 256 tile has a CU to itself.
 //
 // Weight gradients split the contraction over the tokens; each split
 // writes an fp32 slab and an ordered reduction sums the slabs, so results
@@ -366,22 +368,6 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgsF32 g) {
     }
 }
 
-template <bool BF16>
-__device__ __forceinline__ float ld_e(const void* p, int64_t i) {
-  if constexpr (BF16)
-    return bf16_bits_to_f32(((const uint16_t*)p)[i]);
-  else
-    return ((const float*)p)[i];
-}
-
-template <bool BF16>
-__device__ __forceinline__ void st_e(void* p, int64_t i, float v) {
-  if constexpr (BF16)
-    ((uint16_t*)p)[i] = f32_to_bf16_bits(v);
-  else
-    ((float*)p)[i] = v;
-}
-
 // dpre = dZ * SiLU'(pre), dZ = [dU | dV | dQ | dK] from four dense
 // [T][h][d] gradients, and partial column sums of the fp32 dpre for the
 // bias gradient, one row of partials per block of kColRows token rows.
@@ -584,7 +570,8 @@ __global__ __launch_bounds__(256) void reduce_cols_kernel(int n, int S,
 int gemm_num_splits(int M, int N, int64_t K, int* k_split) {
   const int tiles = ((M + 255) / 256) * ((N + 255) / 256);
   int64_t want = (256 + tiles - 1) / tiles;
-  // At least 256 contraction rows per split, and at least one split.
+  // About 256 contraction rows per split at least (K = 257 makes splits of
+  // 160 and 97), and at least one split.
   const int64_t max_splits = K > 256 ? (K + 255) / 256 : 1;
   want = want < 1 ? 1 : want > max_splits ? max_splits : want;
   int64_t ks = (K + want - 1) / want;
@@ -610,18 +597,20 @@ hipError_t gemm_case(const GemmArgs& g, int splits, hipStream_t s) {
   const bool stream =
       EPI != kEpiSlab && 2ll * g.M * g.N * (g.c2 ? 2 : 1) > (128ll << 20);
   constexpr bool kStream = EPI != kEpiSlab;
-  // The largest tile that (nearly) fills the chip: one 256 x 256 workgroup or
-  // two of 256 x 128 per CU.  Against the smaller one the large tile reads a
-  // third less from the L2 per product (f_1's backward at 60 K tokens 430
-  // against 448 us); f_1's forward, half of whose time is its stores, keeps
-  // two workgroups per CU, one storing while the other computes (194 against
-  // 199 us).
-  if (EPI != kEpiSilu && tiles(256, 256) * splits >= 224)
-    return stream ? launch(gemm_bf16_kernel<4, 4, 4, A_KM, B_KM, EPI, kStream>, 256, 256)
-                  : launch(gemm_bf16_kernel<4, 4, 4, A_KM, B_KM, EPI, false>, 256, 256);
-  if (tiles(256, 128) * splits >= 448)
-    return stream ? launch(gemm_bf16_kernel<4, 2, 3, A_KM, B_KM, EPI, kStream>, 256, 128)
-                  : launch(gemm_bf16_kernel<4, 2, 3, A_KM, B_KM, EPI, false>, 256, 128);
+  // The largest tile that (nearly) fills the chip: one 256 x 256 workgroup per
+  // CU, which reads a third less from the L2 per product than two of 256 x
+  // 128 (f_1's backward at 60 K tokens 430 against 448 us); f_1's forward,
+  // half of whose time is its stores, takes the two, one storing while the
+  // other computes (194 against 199 us).
+  if constexpr (EPI != kEpiSilu) {
+    if (tiles(256, 256) * splits >= 224)
+      return stream ? launch(gemm_bf16_kernel<4, 4, 4, A_KM, B_KM, EPI, kStream>, 256, 256)
+                    : launch(gemm_bf16_kernel<4, 4, 4, A_KM, B_KM, EPI, false>, 256, 256);
+  } else {
+    if (tiles(256, 128) * splits >= 448)
+      return stream ? launch(gemm_bf16_kernel<4, 2, 3, A_KM, B_KM, EPI, kStream>, 256, 128)
+                    : launch(gemm_bf16_kernel<4, 2, 3, A_KM, B_KM, EPI, false>, 256, 128);
+  }
   return launch(gemm_bf16_kernel<2, 2, 3, A_KM, B_KM, EPI, false>, 128, 128);
 }
 

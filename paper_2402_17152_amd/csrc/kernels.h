@@ -219,8 +219,8 @@ struct GemmArgs {
 hipError_t launch_gemm_bf16(const GemmArgs& g, int a_kmajor, int b_kmajor, int epi, int splits,
                             hipStream_t s);
 // Contraction splits for a k-major x k-major product of M x N outputs over
-// K rows: about 256 workgroups of 256 x 256 outputs, at least 256 rows per
-// split.
+// K rows: about 256 workgroups of 256 x 256 outputs, about 256 rows per split
+// at least.
 int gemm_num_splits(int M, int N, int64_t K, int* k_split);
 
 // fp32 operands with arbitrary element strides (A(m, k) = a[m sam + k sak],

@@ -62,3 +62,11 @@ def test_proj_tiles(T, D, h, dqk, dv):
     _close("dx", dx, dpre @ w1.double() + dy.double(), (2e-2, True))
     _close("dw1", dw1, dpre.t() @ x.double(), (2e-2, False))
     _close("db1", db1, dpre.sum(0), (1e-5, False))
+
+
+@pytest.mark.parametrize("T,D,h,dqk,dv", [(70001, 1024, 1, 32, 64), (70001, 64, 16, 32, 64)])
+def test_proj_streamed_sums(T, D, h, dqk, dv):
+    """y (with its residual) and dx (with dx_add), then dg, past half of the
+    last-level cache, with a ragged last tile: the stores of the products
+    without a SiLU that bypass the cache."""
+    test_proj_tiles(T, D, h, dqk, dv)
