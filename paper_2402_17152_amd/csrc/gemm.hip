@@ -376,10 +376,14 @@ __global__ __launch_bounds__(256) void gemm_f32_kernel(GemmArgsF32 g) {
 // straddle two) of kColRows / 4 rows, all of whose loads are in flight at
 // once; its workgroup's four row groups meet in LDS.  (One thread per 8
 // columns and 32 rows: 27 us on 4.8 K tokens of 1024 columns, too few loads
-// in flight.)  NT: inputs larger than the last-level cache are read past it,
-// so that it keeps what the products read next (62 K tokens of 2048 columns:
-// the whole backward 571 against 586 us; on cached inputs it costs 10 us of
-// 70).
+// in flight.)
+// NT: inputs of half the last-level cache and more are read past it, so that
+// it keeps what the products read next.  The whole backward with ordinary
+// against such reads (us; 1024, 2048, 4096 columns), by the inputs' MB, the
+// same whether the gradients were just written or not:
+//   96: 92 / 96, 114 / 116, 160 / 163     112: level
+//   128: 116 / 111, 141 / 140, 203 / 200  192: 165 / 146, 205 / 189, 295 / 280
+//   512: 355 / 342, 439 / 434, 646 / 636
 constexpr int kColRows = 32;
 
 template <bool BF16>
@@ -591,9 +595,13 @@ hipError_t gemm_case(const GemmArgs& g, int splits, hipStream_t s) {
     hipLaunchKernelGGL(kernel, grid, dim3(2 * bn), 0, s, g);
     return hipGetLastError();
   };
-  // Outputs past half of the 256 MB last-level cache bypass the caches (f_1's
-  // forward at 60 K tokens, 495 MB: 200 us against 244); smaller ones may be
-  // read from them by the next call.
+  // Outputs past half of the 256 MB last-level cache bypass the caches; smaller
+  // ones may be read from them by the next call.  f_1's forward at 2048 columns
+  // with ordinary against bypassing stores (us), alone, then with a pass that
+  // reads z after it, by the MB of z and z_pre:
+  //   64: 30 / 29, 43 / 44      128: 55 / 53, 76 / 76    192: 81 / 80, 122 / 110
+  //   256: 123 / 102, 164 / 162    512: 259 / 200, 344 / 337
+  // f_2's y, alone: 64 MB 34 / 31, 160 MB 90 / 69, 384 MB 203 / 199.
   const bool stream =
       EPI != kEpiSlab && 2ll * g.M * g.N * (g.c2 ? 2 : 1) > (128ll << 20);
   constexpr bool kStream = EPI != kEpiSlab;
@@ -653,7 +661,7 @@ hipError_t launch_silu_bwd(int is_bf16, int64_t T, int F, int hv, int hq, const 
   };
   if (!is_bf16)
     launch(silu_bwd_kernel<false, false>);
-  else if (4 * T * F > (256ll << 20))
+  else if (4 * T * F >= (128ll << 20))
     launch(silu_bwd_kernel<true, true>);
   else
     launch(silu_bwd_kernel<true, false>);
