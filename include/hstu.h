@@ -57,13 +57,15 @@
  *            gradients are fp32; offsets and timestamps int64.
  *   Determinism  hstu_attn_fwd, hstu_layer_fwd, hstu_time_bucketize and
  *            hstu_complete_cumsum are bitwise deterministic, and so are
- *            dQ, dK and dV of hstu_attn_bwd for HSTU_BF16 (dQ is summed
- *            from per-key-block partials in a fixed order), and of
- *            hstu_layer_bwd for HSTU_BF16 with d_qk, d_v <= 64; the
- *            layer-norm parameter gradients are summed in a fixed order from
- *            those calls' dO.  The bias gradients, and dQ of
- *            hstu_layer_bwd at d_qk or d_v = 128, are accumulated with
- *            atomics, so their last bits may vary between runs.
+ *            dQ, dK and dV of hstu_attn_bwd (for HSTU_BF16, dQ is summed
+ *            from per-key-block partials in a fixed order), dQ, dK and dV of
+ *            hstu_layer_bwd for HSTU_F32 and for HSTU_BF16 with d_qk, d_v <=
+ *            64, and, for both dtypes and all head sizes, d_ln_weight and
+ *            d_ln_bias.  The bias gradients, and dQ of hstu_layer_bwd for
+ *            HSTU_BF16 with d_qk or d_v = 128, are accumulated with
+ *            atomics, so their last bits may vary between runs.  A token's
+ *            rows of z, z_pre, y, dg and dx of the linear maps have the
+ *            same bits wherever the token lies in a batch.
  */
 #ifndef HSTU_H_
 #define HSTU_H_

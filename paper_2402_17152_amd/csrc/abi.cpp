@@ -527,8 +527,7 @@ double hstu_sl_keep_numerator(int32_t max_seq_len, double alpha) {
 
 size_t hstu_sl_workspace_bytes(int32_t num_seqs) {
   if (num_seqs < 1) return 0;
-  return align_up(sizeof(int64_t) * (size_t)num_seqs) +
-         align_up(sizeof(int32_t) * (size_t)num_seqs);
+  return align_up(sizeof(int64_t) * (size_t)num_seqs);
 }
 
 hstu_status_t hstu_stochastic_length(int32_t num_seqs, const int64_t* seq_offsets,

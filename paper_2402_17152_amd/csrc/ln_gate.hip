@@ -6,10 +6,10 @@
 //
 // HBM-bound: one wave per token (several tokens per wave for D <= 256), each
 // lane holds its 8-element chunks in registers (16-byte loads for bf16),
-// two-pass mean/variance in fp32 with wave reductions, one pass of stores.  The attention output x is read in
-// fp32 for both dtypes: normalising divides by the row's spread, which can
-// be far smaller than its magnitude, so a bf16-rounded x would carry
-// errors of several percent into Y.
+// two-pass mean/variance in fp32 with wave reductions, one pass of stores.
+// The attention output x is read in fp32 for both dtypes: normalising divides
+// by the row's spread, which can be far smaller than its magnitude, so a
+// bf16-rounded x would carry errors of several percent into Y.
 #include "kernels.h"
 
 namespace hstu {
