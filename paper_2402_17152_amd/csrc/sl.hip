@@ -288,17 +288,83 @@ __device__ void select_tokens(SlShared& sm, const SlKey& key, int nh, int L, int
   __syncthreads();
 }
 
-// One workgroup per 2^lg sequences (2^lg <= its waves).  FUSED: it also adds
-// up the new lengths before its own and writes its new offsets; else new_offs
-// holds them.
-template <bool FUSED>
+// The L chosen history tokens of a sequence (tokens o .. o + n - 1, t of them
+// candidates) and, after them, its candidates.
+__device__ __forceinline__ void shorten(SlShared& sm, const int64_t* __restrict__ ts,
+                                        const double* __restrict__ e_rand, int32_t L, int32_t mode,
+                                        int64_t o, int n, int t, int64_t* __restrict__ out) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nh = n - t;
+  for (int c = tid; c < t; c += kSlThreads) out[L + c] = o + nh + c;
+
+  // t_max and (feature-weighted) F = sum of t_max - t_i over the history;
+  // random selection reads no timestamps.
+  const int64_t* th = ts + o;
+  int64_t tmax = 0, F = 0;
+  if (mode != kSlRandom) {
+    int64_t mx = (int64_t)(~0ull >> 1) * -1 - 1;
+    for (int i = tid; i < nh; i += kSlThreads) mx = th[i] > mx ? th[i] : mx;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) {
+      const int64_t x = __shfl_xor(mx, off, 64);
+      mx = x > mx ? x : mx;
+    }
+    if (lane == 0) sm.red[1][wave] = mx;
+    __syncthreads();
+    tmax = sm.red[1][0];
+#pragma unroll
+    for (int w = 1; w < kSlWaves; w++) tmax = max(tmax, sm.red[1][w]);
+    __syncthreads();
+  }
+  if (mode == kSlWeighted) {
+    int64_t sum = 0;
+    for (int i = tid; i < nh; i += kSlThreads) sum += tmax - th[i];
+    F = block_add(sm, 1, sum);
+  }
+  const SlKey key{th, e_rand ? e_rand + o : nullptr, tmax, F, mode};
+  if (nh <= kSlHeld * kSlThreads)
+    select_tokens<true>(sm, key, nh, L, o, out);
+  else
+    select_tokens<false>(sm, key, nh, L, o, out);
+}
+
+// FUSED: a workgroup adds up the new lengths of the sequences before its own
+// and writes its new offsets; else new_offs holds them.  GROUP: 2^lg sequences
+// (at most one per wave) to a workgroup; else one (FUSED only).
+template <bool FUSED, bool GROUP>
 __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
     int32_t B, int lg, const int64_t* __restrict__ offs, const int64_t* __restrict__ ts,
     const int64_t* __restrict__ nt, int32_t L, double keep_num, int32_t mode,
     const double* __restrict__ u_keep, const double* __restrict__ e_rand,
     int64_t* __restrict__ new_offs, int64_t* __restrict__ gather) {
+  static_assert(FUSED || GROUP, "single sequences are few enough to be fused");
   __shared__ SlShared sm;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto new_len_before = [&](int b0) {
+    int64_t sum = 0;
+    for (int x = tid; x < b0; x += kSlThreads) {
+      const int64_t xn = offs[x + 1] - offs[x], xt = nt ? nt[x] : 0;
+      sum += keep_whole(xn, xt, L, keep_num, u_keep[x]) ? xn : (int64_t)L + xt;
+    }
+    return block_add(sm, 0, sum);
+  };
+  if constexpr (!GROUP) {
+    const int b = blockIdx.x;
+    const int64_t o = offs[b];
+    const int n = (int)(offs[b + 1] - o), t = nt ? (int)nt[b] : 0;
+    const bool whole = keep_whole(n, t, L, keep_num, u_keep[b]);
+    const int64_t start = new_len_before(b);
+    if (tid == 0) {
+      if (b == 0) new_offs[0] = 0;
+      new_offs[b + 1] = start + (whole ? n : (int64_t)L + t);
+    }
+    int64_t* out = gather + start;
+    if (whole) {
+      for (int i = tid; i < n; i += kSlThreads) out[i] = o + i;
+    } else {
+      shorten(sm, ts, e_rand, L, mode, o, n, t, out);
+    }
+    return;
+  }
   for (int64_t first = (int64_t)blockIdx.x << lg; first < B; first += (int64_t)gridDim.x << lg) {
     const int b0 = (int)first, seqs = min(1 << lg, B - b0);
     // Lane l of every wave: sequence b0 + l.
@@ -313,26 +379,21 @@ __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
       if constexpr (!FUSED) start_l = new_offs[b0 + lane];
     }
     if constexpr (FUSED) {
-      int64_t sum = 0;
-      for (int x = tid; x < b0; x += kSlThreads) {
-        const int64_t xn = offs[x + 1] - offs[x], xt = nt ? nt[x] : 0;
-        sum += keep_whole(xn, xt, L, keep_num, u_keep[x]) ? xn : (int64_t)L + xt;
-      }
       const int64_t len = lane >= seqs ? 0 : whole_l ? n_l : (int64_t)L + t_l;
       int64_t run = len;
       for (int off = 1; off < 1 << lg; off <<= 1) {
         const int64_t x = __shfl_up(run, off, 64);
         if (lane >= off) run += x;
       }
-      start_l = block_add(sm, 0, sum) + run - len;
+      start_l = new_len_before(b0) + run - len;
       if (wave == 0 && lane < seqs) {
         if (b0 + lane == 0) new_offs[0] = 0;
         new_offs[b0 + lane + 1] = start_l + len;
       }
     }
-    // Whole sequences, each by its share of the threads.
+    // Whole sequences, each by its share of the threads (whole waves).
     {
-      const int sh = 10 - lg;  // 1024 >> lg threads, whole waves, each
+      const int sh = 10 - lg;  // 1024 >> lg threads
       const int k = __builtin_amdgcn_readfirstlane(tid >> sh);
       if (__builtin_amdgcn_readlane(whole_l, k)) {
         const int64_t o = readlane64(o_l, k);
@@ -343,42 +404,8 @@ __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
     }
     for (uint64_t left = __ballot(lane < seqs && !whole_l); left; left &= left - 1) {
       const int k = __builtin_ctzll(left);
-      const int64_t o = readlane64(o_l, k);
-      const int n = __builtin_amdgcn_readlane(n_l, k), t = __builtin_amdgcn_readlane(t_l, k);
-      const int nh = n - t;
-      int64_t* out = gather + readlane64(start_l, k);
-      // Candidates follow the L chosen history tokens.
-      for (int c = tid; c < t; c += kSlThreads) out[L + c] = o + nh + c;
-
-      // t_max and (feature-weighted) F = sum of t_max - t_i over the history;
-      // random selection reads no timestamps.
-      const int64_t* th = ts + o;
-      int64_t tmax = 0, F = 0;
-      if (mode != kSlRandom) {
-        int64_t mx = (int64_t)(~0ull >> 1) * -1 - 1;
-        for (int i = tid; i < nh; i += kSlThreads) mx = th[i] > mx ? th[i] : mx;
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          const int64_t x = __shfl_xor(mx, off, 64);
-          mx = x > mx ? x : mx;
-        }
-        if (lane == 0) sm.red[1][wave] = mx;
-        __syncthreads();
-        tmax = sm.red[1][0];
-#pragma unroll
-        for (int w = 1; w < kSlWaves; w++) tmax = max(tmax, sm.red[1][w]);
-        __syncthreads();
-      }
-      if (mode == kSlWeighted) {
-        int64_t sum = 0;
-        for (int i = tid; i < nh; i += kSlThreads) sum += tmax - th[i];
-        F = block_add(sm, 1, sum);
-      }
-      const SlKey key{th, e_rand ? e_rand + o : nullptr, tmax, F, mode};
-      if (nh <= kSlHeld * kSlThreads)
-        select_tokens<true>(sm, key, nh, L, o, out);
-      else
-        select_tokens<false>(sm, key, nh, L, o, out);
+      shorten(sm, ts, e_rand, L, mode, readlane64(o_l, k), __builtin_amdgcn_readlane(n_l, k),
+              __builtin_amdgcn_readlane(t_l, k), gather + readlane64(start_l, k));
     }
     __syncthreads();  // sm.red is written again
   }
@@ -452,11 +479,13 @@ hipError_t launch_stochastic_length(int32_t B, const int64_t* offs, const int64_
   const int lg = sl_group_lg(B);
   const int groups = (B + (1 << lg) - 1) >> lg;
   const dim3 grid((unsigned)(groups < 65535 ? groups : 65535));
-  if (B <= kSlFusedSeqs) {
-    hipLaunchKernelGGL(sl_select_kernel<true>, grid, dim3(kSlThreads), 0, s, B, lg, offs, ts, nt, L,
-                       keep_num, mode, u_keep, e_rand, new_offs, gather);
+  auto select = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(kSlThreads), 0, s, B, lg, offs, ts, nt, L, keep_num, mode,
+                       u_keep, e_rand, new_offs, gather);
     return hipGetLastError();
-  }
+  };
+  if (lg == 0) return select(sl_select_kernel<true, false>);
+  if (B <= kSlFusedSeqs) return select(sl_select_kernel<true, true>);
   const int blocks = (B + 255) / 256 < 1024 ? (B + 255) / 256 : 1024;
   hipLaunchKernelGGL(sl_lengths_kernel, dim3(blocks), dim3(256), 0, s, B, offs, nt, L, keep_num,
                      u_keep, new_len);
@@ -464,9 +493,7 @@ hipError_t launch_stochastic_length(int32_t B, const int64_t* offs, const int64_
   if (e != hipSuccess) return e;
   e = launch_complete_cumsum(B, new_len, new_offs, 0, s);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(sl_select_kernel<false>, grid, dim3(kSlThreads), 0, s, B, lg, offs, ts, nt, L,
-                     keep_num, mode, u_keep, e_rand, new_offs, gather);
-  return hipGetLastError();
+  return select(sl_select_kernel<false, true>);
 }
 
 hipError_t launch_gather_rows(const void* src, int64_t src_stride, int64_t row_bytes,
