@@ -401,6 +401,8 @@ __device__ __forceinline__ void bwd_item(BwdShared<DQK, DV, SPLIT>& sm, const Bw
   auto full_tile = [&](int i0) {
     return (jw0 + 31 <= i0) && (i0 + BM - 1 < L) && (i0 + BM - 1 < n_h);
   };
+  // (Branches, where role A below computes the same without: there the
+  // straight line is faster, here it timed 0.2 % slower.)
   auto classify = [&](int u) -> Path {
     Path r{kGeneral, 0.0f, 0.0f};
     if (u >= nsteps) {
