@@ -178,8 +178,9 @@ struct Walk {
     while (hi - lo > 64) {
       const int step = (hi - lo + 63) >> 6;
       const int64_t at = ja.seq_offsets[min(lo + (lane + 1) * step, hi)];
-      // (lane 63's probe is hi: some lane's lies above)
-      const int f = __builtin_amdgcn_readfirstlane(__builtin_ctzll(__ballot(at > r0)));
+      // (lane 63's probe is hi, which lies above)
+      const uint64_t above = __ballot(at > r0) | 1ull << 63;
+      const int f = __builtin_amdgcn_readfirstlane(__builtin_ctzll(above));
       base = f ? readlane64(at, f - 1) : base;
       hi = min(lo + (f + 1) * step, hi);
       lo += f * step;
@@ -197,7 +198,7 @@ struct Walk {
           q.short_row[first + i] = pack_short(len, nh, i);
       }
       any_short |= __ballot(len > 0 && len <= kShort) != 0;
-      for (uint64_t m = __ballot(len > kShort); m; m &= m - 1) {
+      for (uint64_t m = __ballot(len > kShort); m && seqs < Seqs::kLong; m &= m - 1) {
         const int f = __builtin_ctzll(m);
         const int64_t fo = readlane64(so, f);
         const int fl = __builtin_amdgcn_readlane(len, f), fh = __builtin_amdgcn_readlane(nh, f);
