@@ -412,12 +412,15 @@ __global__ __launch_bounds__(kSlThreads) void sl_select_kernel(
 }
 
 // dst row r = src row index[r] for r < *count (count read on the device).
-// A row's words (of type W) are taken by 2^lg lanes, 64 words to a workgroup
-// column (blockIdx.x); a workgroup takes kGatherUnroll sweeps of 256 >> lg
-// consecutive rows, so that a lane has that many rows' loads in flight.
-// HBM-bound.  (With a lane walking a whole row, few wide rows kept few lanes
-// busy: 64 rows of 64 KB took 23 us, now 6; one of 1 MB 154, now 6; 36000
-// rows of 4 KB 56, now 46.)
+// A row's words (of type W) are taken by 2^lg lanes (up to the whole
+// workgroup), longer rows by as many columns of workgroups (blockIdx.x) as
+// they have full ones, the first lanes taking what is left over; a workgroup
+// takes kGatherUnroll sweeps of 256 >> lg consecutive rows, so that a lane has
+// that many rows' loads in flight.  HBM-bound.  (With 64 lanes walking a whole
+// row, few wide rows kept few lanes busy: 64 rows of 64 KB took 23 us, now 5;
+// one of 1 MB 154, now 5; 36000 rows of 4 KB 56, now 46.  Columns of 64 words:
+// 64 rows of 1 MB 24.1 us against 21.2, 36000 rows of 4112 bytes 54 against
+// 49; a column of its own for what is left over: 76.)
 constexpr int kGatherUnroll = 4;
 
 template <typename W>
@@ -459,9 +462,9 @@ hipError_t gather_case(const void* src, int64_t src_stride, int64_t row_bytes,
                        int64_t dst_stride, hipStream_t s) {
   const int64_t words = row_bytes / (int64_t)sizeof(W);
   int lg = 0;
-  while (lg < 6 && (1 << lg) < words) lg++;
+  while (lg < 8 && (1 << lg) < words) lg++;
   const int64_t per_block = kGatherUnroll * (256 >> lg);
-  const int64_t cols = min((words + 63) / 64, (int64_t)65535);
+  const int64_t cols = max(min(words >> lg, (int64_t)65535), (int64_t)1);
   const int64_t blocks = min((max_rows + per_block - 1) / per_block, 65535 / cols);
   hipLaunchKernelGGL((gather_rows_kernel<W>), dim3((unsigned)cols, (unsigned)blocks), dim3(256), 0,
                      s, (const char*)src, src_stride, words, lg, index, count, max_rows,

@@ -58,11 +58,11 @@ def test_gather_row_widths(row_bytes, shift, rows):
     assert (dst[rows:] == 5).all()
 
 
-@pytest.mark.parametrize("rows,row_bytes", [(1, 1 << 20), (3, 65536 + 8), (17, 4096 + 4), (70, 16384),
-                                            (16, 1040)])
+@pytest.mark.parametrize("rows,row_bytes", [(1, 1 << 20), (3, 65536 + 8), (17, 4096 + 4),
+                                            (70, 16384), (16, 1040), (5, 2080), (9, 4112)])
 def test_gather_wide_rows(rows, row_bytes):
-    """Rows of more words than the lanes that share one: a row is spread over
-    workgroups, the last of them partly filled."""
+    """Rows of more words than a wave: up to the whole workgroup shares one,
+    longer ones are spread over workgroups, with words left over or not."""
     test_gather_row_widths(row_bytes, 0, rows)
 
 
