@@ -89,8 +89,10 @@ __device__ __forceinline__ float silu(float x) {
 // Workgroups per CU that the registers are held to: two above heads of 64,
 // three up to 64 (at most 168 registers: the two-term instance spills 13 for
 // it, 1.73 ms per layer step of 62 K tokens against 1.81 at two), four for
-// the one-term instances at 32 (at most 128; at 135 and three, batches of
-// short sequences took 10 to 19 % longer).
+// the one-term instances at 32 (at most 128).  Against three with 135
+// registers: 2000 sequences of 1-29 tokens 137 -> 116 us, 64 of 64-4096 225 ->
+// 200 (8 heads), 24 of 500-2000 103 -> 93; where few workgroups each walk a
+// long chain, 1 % more.
 template <int DQK, int DV, bool SPLIT>
 constexpr int kFwdPerCu = DQK > 64 || DV > 64 ? 2 : DQK > 32 || DV > 32 || SPLIT ? 3 : 4;
 
@@ -371,15 +373,17 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     }
   };
   // Per-pair bias.  Branch-free, with every LDS lookup issued before any
-  // is consumed, so the lookups of the 16 pairs overlap (of 8 at a time
-  // where four workgroups share a CU: 16 take registers past that).  Time
-  // term on the fast path: |t_i - t_j| < 2^31 by one v_sad_u32, its
-  // leading-zero count z by v_ffbh_u32 (-1 for 0), then tab32[z] = tab[32 +
-  // z]; entry -1 (= tab[31], unused by the fast path) holds bucket 0, the
-  // bucket of |dt| <= 1.
-  constexpr int kParts = kFwdPerCu<DQK, DV, SPLIT> == 4 ? 2 : 1;
-  constexpr int kPairs = 16 / kParts, kRuns = 4 / kParts;
-  auto time_terms = [&](int u, int part, float (&tv)[kPairs]) {
+  // is consumed, so the lookups of the 16 pairs overlap.  Time term on the
+  // fast path: |t_i - t_j| < 2^31 by one v_sad_u32, its leading-zero count
+  // z by v_ffbh_u32 (-1 for 0), then tab32[z] = tab[32 + z]; entry -1
+  // (= tab[31], unused by the fast path) holds bucket 0, the bucket of
+  // |dt| <= 1.  Where four workgroups share a CU the 16 go in two halves, as
+  // all at once take registers past that; on the full tiles of the instance
+  // with candidates they fit (in halves 3 % slower on a sequence of 5041).
+  constexpr int kMaskedParts = kFwdPerCu<DQK, DV, SPLIT> == 4 ? 2 : 1;
+  constexpr int kFullParts = TGT ? 1 : kMaskedParts;
+  auto time_terms = [&](int u, int part, auto& tv) {
+    constexpr int kPairs = sizeof(tv) / sizeof(float), kRuns = kPairs / 4;
     // The lane's 16 keys are 4 runs of 4: jl = 8g + 4*half + m.
     if constexpr (FAST) {
       const uint32_t* tp = sm.sTr[u & 7] + 4 * half + 8 * kRuns * part;
@@ -431,7 +435,8 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
       for (int q = 0; q < 16; q++) acc[q] = kMaskedBias;
       return;
     }
-    auto window = [&](int part, float (&wv)[kPairs]) {
+    auto window = [&](int part, auto& wv) {
+      constexpr int kRuns = sizeof(wv) / sizeof(f32x4);
       const int c = a_win & 3;
       const float* wp = &sm.sWin[ks][c][Sh::kWinPad + a_win - c] + 8 * kRuns * part;
 #pragma unroll
@@ -443,8 +448,9 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
     };
     if (full) {
       // Several buckets: position term as on uniform tiles, time term per pair.
+      constexpr int kPairs = 16 / kFullParts;
 #pragma unroll
-      for (int part = 0; part < kParts; part++) {
+      for (int part = 0; part < kFullParts; part++) {
         float tv[kPairs], wv[kPairs];
         window(part, wv);
         time_terms(u, part, tv);
@@ -456,29 +462,43 @@ __device__ __forceinline__ void fwd_item(FwdShared<DQK, DV>& sm, const JaggedArg
       // by the window reads of full tiles (they stay inside the window for
       // every lane, valid or not); candidate keys (all at position n_h) entry
       // by entry, invalid pairs reading entry 0.
+      auto masked = [&](auto by_entry) {
+        constexpr int kPairs = 16 / kMaskedParts, kRuns = kPairs / 4;
 #pragma unroll
-      for (int part = 0; part < kParts; part++) {
-        float tv[kPairs], wv[kPairs];
-        bool ok[kPairs];
-#pragma unroll
-        for (int q = 0; q < kPairs; q++) {
-          const int j = j0 + 8 * kRuns * part + 8 * (q >> 2) + 4 * half + (q & 3);
-          ok[q] = pair_kept(j);
-        }
-        if (!TGT || j0 + BN - 1 < n_h) {
-          window(part, wv);
-        } else {
-          const int pb = min(j0, n_h);
+        for (int part = 0; part < kMaskedParts; part++) {
+          float tv[kPairs], wv[kPairs];
+          bool ok[kPairs];
 #pragma unroll
           for (int q = 0; q < kPairs; q++) {
             const int j = j0 + 8 * kRuns * part + 8 * (q >> 2) + 4 * half + (q & 3);
-            wv[q] = sm.sWin[ks][0][Sh::kWinPad + (ok[q] ? bias_pos(j, n_h) - pb + R - pi : 0)];
+            ok[q] = pair_kept(j);
           }
-        }
-        time_terms(u, part, tv);
+          if (!by_entry) {
+            window(part, wv);
+          } else {
+            const int pb = min(j0, n_h);
 #pragma unroll
-        for (int q = 0; q < kPairs; q++)
-          acc[kPairs * part + q] = ok[q] ? wv[q] + tv[q] : kMaskedBias;
+            for (int q = 0; q < kPairs; q++) {
+              const int j = j0 + 8 * kRuns * part + 8 * (q >> 2) + 4 * half + (q & 3);
+              wv[q] = sm.sWin[ks][0][Sh::kWinPad + (ok[q] ? bias_pos(j, n_h) - pb + R - pi : 0)];
+            }
+          }
+          time_terms(u, part, tv);
+#pragma unroll
+          for (int q = 0; q < kPairs; q++)
+            acc[kPairs * part + q] = ok[q] ? wv[q] + tv[q] : kMaskedBias;
+        }
+      };
+      // (one copy of the code, or one for either kind of key: what costs the
+      // instance fewer registers)
+      const bool candidates = TGT && j0 + BN - 1 >= n_h;
+      if constexpr (kMaskedParts == 1) {
+        masked(candidates);
+      } else {
+        if (candidates)
+          masked(std::true_type{});
+        else
+          masked(std::false_type{});
       }
     }
   };
